@@ -142,7 +142,8 @@ struct hmd_batch {
   double* d_state[2][6] = {};       // x y z vx vy vz: current copy and reorder target
   int* d_tag[2] = {};               // atom id within its system
   float4* d_f4 = nullptr;           // force (w: potential energy) per slot
-  float4* d_pos4 = nullptr;         // cell path: cell-relative FP32 position (w: local cell id bits)
+  float4* d_pos4 = nullptr;         // cell path: cell-relative FP32 position (w: local cell id bits);
+                                    // tiled path: screening coordinates, fluid slots then wall atoms
   int4* d_pfix = nullptr;           // pair path: fixed-point positions, fluid slots then wall atoms
   int4* d_pbuild = nullptr;         // pair path: positions at the last list build
   uint32_t* d_slot_cell = nullptr;  // pair path: cell of each slot at the last build

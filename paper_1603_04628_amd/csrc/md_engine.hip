@@ -125,7 +125,7 @@ void launch_build(hmd_batch* b, hipStream_t s, const int* flag, StepRef R, State
   if (b->path == 2) {
     hipLaunchKernelGGL(b->uniform ? k_build_tiles<1> : k_build_tiles<0>, dim3(b->ntiles), dim3(TILE_THREADS), 0,
                        s, nt,
-                       b->list_ld, b->list_cap, b->d_tiles, b->d_sims, b->d_slot_cell, b->d_pfix,
+                       b->list_ld, b->list_cap, b->d_tiles, b->d_sims, b->d_slot_cell, b->d_pfix, b->d_pos4,
                        b->d_start, b->d_ncount, b->d_wstart, b->d_wcount, b->d_list, b->d_nlist,
                        b->d_tilerec, from, to, tag_from, tag_to, b->d_flag + 2, flag, R, rl2,
                        global_out || b->force_gather ? 1 : 0);
@@ -561,6 +561,8 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
         (rc = dalloc(ctx, &b->d_slot_cell, b->ntot)) || (rc = dalloc(ctx, &b->d_nlist, b->ntot)) ||
         (rc = dalloc(ctx, &b->d_list, int64_t(b->list_cap) * b->list_ld)))
       return fail(rc);
+    // screening reads whole blocks past the end of a range
+    if (b->path == 2 && (rc = dalloc(ctx, &b->d_pos4, b->ntot + b->nwall + SCREEN_PAD))) return fail(rc);
   }
   for (int w = 0; w < 2; ++w)
     for (int a = 0; a < 6; ++a)
@@ -654,8 +656,14 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
       const int cx = c % H.nx, cz = (c / H.nx) % H.nz, slab = c / (H.nx * H.nz);
       const double oy = slab == 0 ? -H.wy : double(H.ny) * H.wy;
       const double* p = &H.xw[3 * w];
-      wpos[slot] = make_float4(float(p[0] - double(cx) * H.wx), float(p[1] - oy), float(p[2] - double(cz) * H.wz),
-                               0.0f);
+      if (b->path == 2) {  // as k_reorder writes for the fluid
+        const float px = float(p[0] - cell_origin(cx, H.wx)), py = float(p[1] - 0.5 * H.h),
+                    pz = float(p[2] - cell_origin(cz, H.wz));
+        wpos[slot] = make_float4(px, py, pz, px * px + py * py + pz * pz);
+      } else {
+        wpos[slot] = make_float4(float(p[0] - double(cx) * H.wx), float(p[1] - oy),
+                                 float(p[2] - double(cz) * H.wz), 0.0f);
+      }
       wfix[slot] = make_int4(int(fix_axis_host(p[0], D.fix_x)), int(fix_axis_host(p[1] - D.y_lo, D.fix_y)),
                              int(fix_axis_host(p[2], D.fix_z)), 0);
     }
@@ -677,6 +685,10 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
       (rc = up(b->d_wcount, wcount.data(), 4 * b->nwcell)) || (rc = up(b->d_dstate, dstate, sizeof(dstate))))
     return fail(rc);
   if (b->path >= 1 && (rc = up(b->d_pfix + b->ntot, wfix.data(), sizeof(int4) * b->nwall))) return fail(rc);
+  if (b->path == 2) {
+    if ((rc = up(b->d_pos4 + b->ntot, wpos.data(), sizeof(float4) * b->nwall))) return fail(rc);
+    HMD_HIP(ctx, hipMemsetAsync(b->d_pos4 + b->ntot + b->nwall, 0, SCREEN_PAD * sizeof(float4), s));
+  }
   for (int a = 0; a < 6; ++a)
     if ((rc = up(b->d_state[0][a], hs[a].data(), 8 * b->ntot))) return fail(rc);
   HMD_HIP(ctx, hipMemsetAsync(b->d_accbuf, 0, sizeof(double) * nacc, s));

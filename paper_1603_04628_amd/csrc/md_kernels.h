@@ -57,12 +57,22 @@ constexpr int TILE_THREADS = 256;  // threads per tile workgroup
 constexpr int TILE_STAGE = 3072;
 // cells of a tile's neighbourhood listed in LDS by the list build
 constexpr int TILE_CTAB = 768;
+// entries of the screening coordinates the tiled list build may read past
+// the last one (blocks past the end of a range)
+constexpr int SCREEN_PAD = 128;
+// x and z origin of the screening coordinates of the tiled list build: the
+// centre of the cell's block of ORIGIN_CELLS cells of width w, so that the
+// coordinates stay short (and their FP32 rounding small) in any box
+constexpr int ORIGIN_CELLS = 16;
+__host__ __device__ inline double cell_origin(int c, double w) {
+  return (double(c / ORIGIN_CELLS * ORIGIN_CELLS) + 0.5 * ORIGIN_CELLS) * w;
+}
 // 32-bit words of a tile's range table, kept in memory from one list build
 // to the next
 constexpr int TILE_REC = 49;
 template <int UNI>
 __global__ void k_build_tiles(int ntot, int ld, int cap, const int4* tiles, const SimDev* sims,
-                              const uint32_t* slot_cell, const int4* pfix, const uint32_t* start,
+                              const uint32_t* slot_cell, const int4* pfix, const float4* pos4, const uint32_t* start,
                               const uint32_t* ncount, const uint32_t* wstart, const uint32_t* wcount,
                               uint32_t* list, uint32_t* nlist, uint32_t* tilerec, StateRef from, StateRef to,
                               const int* tag_from, int* tag_to, int* overflow, const int* flag, StepRef R,

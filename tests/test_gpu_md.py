@@ -104,6 +104,30 @@ def test_cell_sort_is_stable(path):
             assert np.all(np.diff(rank1[sub]) > 0), (c, oc)
 
 
+@pytest.mark.parametrize("h,skin,cell_w,params", [
+    (3.0, 0.3, 0.0, SMALL_L),  # one cell between the walls: every range of a column
+    (5.0, 0.25, 0.0, LARGE),   # thin and wide: columns on both sides of an origin block
+    (6.0, 0.3, 4.0, SMALL_L),  # three slabs and columns: tiles over the whole row, partial last groups
+    (9.0, 0.3, 6.0, SMALL),    # wide cells: ranges of more than one part
+    (8.0, 0.9, 0.0, SMALL),    # long lists: more entries than an atom's LDS row holds
+    (20.0, 0.35, 0.0, SMALL),  # tall columns
+    (60.0, 0.3, 0.2, SMALL_L)])
+def test_tiled_list_build_shapes(h, skin, cell_w, params):
+    # forces from lists screened on the matrix cores, against the oracle's
+    # forces: FP32 pair forces reach 1e-6 relative RMS, a lost pair in reach
+    # would show as a single-atom error (as _per_atom_ok)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=skin, cell_w=cell_w, **params))
+    g_sys, o_sys = hmd.System(ctx, h, 0.02, 8), omd.System(h, 0.02, 8, omd.Params(**params))
+    o_sys.run(60)
+    xo, vo = o_sys.get_state()
+    g_sys.set_state(xo, vo)
+    f, pe = g_sys.forces()
+    fo, peo = o_sys.forces_cells()
+    ok, info = _per_atom_ok(f, fo)
+    assert ok, info
+    assert pe == pytest.approx(peo, rel=1e-4)
+
+
 @pytest.mark.parametrize("path", [1, 2, 3])
 @pytest.mark.parametrize("h,params,steps", [(6.0, SMALL_L, 300), (4.0, SMALL_L, 100), (12.0, SMALL_L, 200),
                                             (15.0, SMALL, 200)])
