@@ -374,12 +374,14 @@ int gp_log_marginal(hmd_gp* gp, double* lml);
  * explicitly, in output units).  The evidence may have several local
  * maxima: a grid of 17 points per chosen parameter, a quarter decade apart
  * over two decades either side of the current values, picks the start of
- * cyclic golden-section searches over the logarithm of each chosen
- * parameter (bracket: a factor 10 either side of the current value), every
- * evaluation a refit on the device, until a cycle gains less than 1e-12
- * relative.  Cost: 17^m refits for m chosen parameters, then the search.  The GP is left fitted at the optimum;
- * *lml (nullable) receives the maximum.  Later appends keep the optimised
- * values. */
+ * cyclic line searches over the logarithm of each chosen parameter (bracket:
+ * a factor 10 either side of the current value; with several parameters a
+ * cycle ends with a search along the way it came), until a cycle gains less
+ * than 1e-12 relative.  The evidences of a grid or of a round of a line
+ * search are evaluated together on the device; beyond 128 points that takes
+ * a workspace of up to 8 GiB for the call (less where it cannot be had).
+ * The GP is left fitted at the optimum; *lml (nullable) receives the maximum.
+ * Later appends keep the optimised values. */
 int gp_optimize(hmd_gp* gp, int mask, double* lml);
 /* The hyperparameters in use (after gp_optimize, the optimised ones). */
 int gp_hyper_get(const hmd_gp* gp, hmd_gp_hyper* hyper);

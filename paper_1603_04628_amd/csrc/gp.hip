@@ -3,7 +3,7 @@
 //   covariance   C = sigma_f^2 exp(-d^2 / 2 l^2) + sigma_n^2 I
 //                (Eqs. quadraticKernelEq, d2Eq, covarianceEq)
 //   factor       C = L L^T (blocked right-looking Cholesky, panels of 32)
-//   weights      alpha = C^-1 y by two triangular solves
+//   weights      alpha = C^-1 y, carried through the factorisation
 //   prediction   mean = K* alpha (Eq. predMeanEq),
 //                var = sigma_f^2 - |L^-1 k*|^2 (diagonal of Eq. predVarEq), with
 //                L^-1 formed once per factorisation so that a query is a
@@ -12,9 +12,8 @@
 // Options: each point's own noise variance on the diagonal (heteroscedastic),
 // the periodic kernel of App. B (Eq. periodicKernel) on a single input, and
 // hyperparameters that maximise the evidence (gp_optimize).
-// Database sizes here are hundreds of points: the triangular solves are
-// latency bound, so one workgroup walks the columns with barriers; the
-// factorisation spreads each panel's update over many workgroups, and
+// One elimination gives the factor, its inverse and the weights, a launch per
+// panel; the evidence search factors many hyperparameter sets at once;
 // prediction gives each query a workgroup of its own.
 #include <hip/hip_runtime.h>
 
@@ -29,14 +28,17 @@ struct hmd_gp {
   hmd_ctx* ctx = nullptr;
   hmd_gp_hyper hyp{};
   int d = 0;
-  int n = 0, cap = 0;
+  int n = 0, cap = 0, ld = 0;  // points, columns reserved, leading dimension (cap + the tile row of y)
   std::vector<double> X, y, se;  // database (host copy)
+  std::vector<double> stage;     // its upload
+  double* slab = nullptr;        // the one allocation behind the pointers up to dnoise
   double scale[4] = {1, 1, 1, 1};
   double s_q = 1.0, sigma_n = 0.0;
   double* dX = nullptr;      // cap x 4, row-major
   double* dy = nullptr;      // scaled outputs
-  double* dL = nullptr;      // cap x cap, column-major (leading dimension cap)
+  double* dL = nullptr;      // ld x cap, column-major
   double* dLi = nullptr;     // L^-1, same layout (lower triangle)
+  double* ddinv = nullptr;   // inverses of L's diagonal tiles
   double* dalpha = nullptr;  // C^-1 y
   double* dtmp = nullptr;    // cap
   double* dnoise = nullptr;  // cap: per-point noise variances (heteroscedastic)
@@ -68,123 +70,350 @@ __device__ __forceinline__ double sqexp(const double* a, const double* b, const 
     return P.sf2 * exp(-4.0 * sn * sn * P.inv_2l2);
   }
   double d2 = 0.0;
-  for (int k = 0; k < P.d; ++k) {
+#pragma unroll
+  for (int k = 0; k < GP_MAXD; ++k) {  // inputs past d are zero on both sides
     const double t = (a[k] - b[k]) * P.inv_scale[k];
     d2 += t * t;
   }
   return P.sf2 * exp(-d2 * P.inv_2l2);
 }
 
-// Lower triangle (and diagonal) of C for rows/cols [0, n); the diagonal
-// takes noise[i] when given (per-point variances), else sn2.
-__global__ void k_gp_cov(int n, int ld, const double* __restrict__ X, KParams P, const double* __restrict__ noise,
-                         double* __restrict__ L) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = blockIdx.y;
-  if (i >= n || j >= n || i < j) return;
-  double c = sqexp(X + GP_MAXD * i, X + GP_MAXD * j, P);
-  if (i == j) c += noise ? noise[i] : P.sn2;
-  L[i + size_t(j) * ld] = c;
+// ---------------------------------------------------------------------------
+// Factorisation.  The matrix is taken in tiles of 32 x 32 (rows and columns
+// past n padded with the identity), the outputs y as one more tile row, and
+// one launch eliminates one panel p from everything to its right and below:
+//   S(i) = A(i,p) L_pp^-T                       (rows i > p: the factor's panel)
+//   A(i,j) -= S(i) S(j)^T                       (j > p: trailing matrix)
+//   W(i,j) -= S(i) Z(p,j), Z(p,j) = L_pp^-1 W(p,j), W(p,p) = I   (j <= p)
+// W starts as the identity, so the same elimination leaves L, L^-1 (rows Z),
+// L^-1 y (the y row of S) and -C^-1 y (the y row of W): no triangular solve
+// follows.  The workgroup of tile (p+1, p+1) factors and inverts it at once
+// for the next launch, so each panel costs one launch.  Up to ~1000 points
+// what bounds it is the chain of that launch, a tile update and a 32 x 32
+// factorisation: 12.8 us a panel, where a diagonal, a panel and an update
+// launch took 52 us and the substitutions after them two barriers per row
+// (one refit of 256 points: 840 -> 220 us).  At 3001 points it is the tiles'
+// passes over the matrix (30 us a panel; factor, weights and inverse together
+// 21 -> 2.9 ms).
+//
+// In place: A lives in L's array and W in L^-1's.  A panel's tiles are still
+// read by the whole launch that eliminates it, so S(i) and Z(p,j) replace
+// them one launch later (recomputed from the same inputs).
+//
+// All products are of the form F G^T with both factors column-major in LDS,
+// 16 x 16 x 4 FP64 matrix instructions, four wavefronts a tile.  The result
+// has rows along the lanes, so columns leave as contiguous 128-byte pieces.
+// ---------------------------------------------------------------------------
+constexpr int TB = 32;       // tile
+constexpr int TP = TB + 1;   // pitch of a tile in LDS
+constexpr int TILE_EL = TB * TP;
+
+using f64x4 = __attribute__((ext_vector_type(4))) double;
+
+// acc(r, c) += sum_k F(r, k) G(c, k) over 16 x 16 x K for one wavefront:
+// F(r, k) = f[k fs + r], G(c, k) = g[k gk + c gc]; lane l holds r = l % 16,
+// c = 4 t + l / 16 in element t.
+template <int K>
+__device__ __forceinline__ f64x4 tile_mma(const double* f, int fs, const double* g, int gk, int gc, double sign,
+                                          f64x4 acc) {
+  const int l = threadIdx.x & 63, m = l & 15, k = l >> 4;
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += 4) {
+    const double b = f[(k0 + k) * fs + m], a = sign * g[(k0 + k) * gk + m * gc];
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+  }
+  return acc;
 }
 
-// In-place blocked right-looking Cholesky of the lower triangle, panels of
-// CB columns, three launches per panel: the diagonal block factored in LDS
-// by one workgroup, the rows below it solved against it (one row per
-// thread), and the trailing lower triangle updated in CB x CB tiles.
-// info = 0 on success, k + 1 if the k-th pivot is not positive; once set,
-// the remaining launches return at once.
-constexpr int CB = 32;
+__device__ __forceinline__ void tile_load(double* lds, const double* __restrict__ src, size_t ld) {
+  for (int e = threadIdx.x; e < TB * TB; e += blockDim.x) lds[(e / TB) * TP + e % TB] = src[(e % TB) + (e / TB) * ld];
+}
 
-__global__ __launch_bounds__(256) void k_chol_diag(int n, int ld, double* __restrict__ A, int* __restrict__ info,
-                                                   int k0) {
-  __shared__ double a[CB][CB + 1];
+// A wavefront's quarter of a 32 x 32 result: rows 16 wr, columns 16 wc.
+struct Quarter {
+  int wr, wc, r, c;  // r: this lane's row, c: its first column (element t: column c + 4 t)
+  __device__ Quarter() {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    wr = w & 1;
+    wc = w >> 1;
+    r = 16 * wr + (l & 15);
+    c = 16 * wc + (l >> 4);
+  }
+};
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(b), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(uint64_t(b) >> 32), lane);
+  return __longlong_as_double(int64_t((uint64_t(hi) << 32) | lo));
+}
+
+// 1 / d to within rounding for normal d > 0 (the hardware estimate and two
+// Newton steps).
+__device__ __forceinline__ double reciprocal(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
+// L D L^T of a 32 x 32 tile by one wavefront: t (lower triangle) becomes the
+// unit factor U below the diagonal, inv U^-1 on and below it, piv the pivots.
+//
+// The quadrants (11, the transpose of 21, 22) stay in accumulators of the
+// 16 x 16 x 4 matrix instruction, element b of lane 16 k + m being row 4 b + k,
+// column m: by symmetry that is row m of column 4 b + k, so element b holds
+// four columns just as the instruction takes an operand of K = 4.  Four
+// columns at a time are eliminated among themselves (pivots and multipliers
+// by readlane, reciprocals instead of roots) and from the rows of the inverse
+// that starts as the identity; one instruction per quadrant then applies them
+// to all that follows.  The eight steps are one loop: the code is read from
+// memory once per launch, and unrolled it took longer to fetch than to run.
+// Returns the first pivot that is not positive, or -1.
+__device__ int tile_factor(double* t, double* inv, double* piv) {
+  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const bool g1 = (g & 1) != 0, g2 = (g & 2) != 0;
+  auto mine = [&](double v0, double v1, double v2, double v3) {  // this lane group's of four
+    const double lo = g1 ? v1 : v0, hi = g1 ? v3 : v2;
+    return g2 ? hi : lo;
+  };
+  auto block = [](const f64x4& v, int b) { return b < 2 ? (b == 0 ? v[0] : v[1]) : (b == 2 ? v[2] : v[3]); };
+  int bad = -1;
+  double own = 1.0;  // lane c: pivot of column c
+  f64x4 q, q12, q22, wd, w21;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int c = 4 * b + g, lo = min(c, m), hi = max(c, m);
+    q[b] = t[lo * TP + hi];
+    q12[b] = t[c * TP + 16 + m];
+    q22[b] = t[(16 + lo) * TP + 16 + hi];
+    wd[b] = c == m ? 1.0 : 0.0;
+    w21[b] = 0.0;
+  }
+#pragma unroll 1
+  for (int step = 0; step < 8; ++step) {
+    const int b = step & 3, half = step >> 2, r0 = 16 * half;
+    if (step == 4) {
+      q = q22;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        wd[k] = 4 * k + g == m ? 1.0 : 0.0;
+        q12[k] = 0.0;
+      }
+    }
+    const double qb = block(q, b), eb = block(q12, b), wb = block(wd, b), vb = block(w21, b);
+    double c[4], e[4], w[4], v[4], lc[4], le[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      c[k] = __shfl(qb, 16 * k + m);  // row m (e: 16 + m) of the four columns
+      e[k] = __shfl(eb, 16 * k + m);
+      w[k] = __shfl(wb, 16 * k + m);  // column m of the inverse's four rows
+      v[k] = __shfl(vb, 16 * k + m);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int col = r0 + 4 * b + k;
+      double d = lane_value(c[k], 4 * b + k);
+      if (!(d > 0.0)) {
+        if (bad < 0) bad = col;
+        d = 1.0;
+      }
+      own = lane == col ? d : own;
+      const double ri = reciprocal(d);
+      lc[k] = c[k] * ri;
+      le[k] = e[k] * ri;
+#pragma unroll
+      for (int k2 = k + 1; k2 < 4; ++k2) {
+        const double f = lane_value(c[k], 4 * b + k2), u = f * ri;  // U of row 4 b + k2
+        c[k2] = fma(-lc[k], f, c[k2]);
+        e[k2] = fma(-le[k], f, e[k2]);
+        w[k2] = fma(-u, w[k], w[k2]);
+        v[k2] = fma(-u, v[k], v[k2]);
+      }
+    }
+    const double x1 = -mine(c[0], c[1], c[2], c[3]), y1 = mine(lc[0], lc[1], lc[2], lc[3]);
+    const double x2 = -mine(e[0], e[1], e[2], e[3]), y2 = mine(le[0], le[1], le[2], le[3]);
+    const double zd = mine(w[0], w[1], w[2], w[3]), z21 = mine(v[0], v[1], v[2], v[3]);
+    const double below = m >= 4 * b + 4 ? -y1 : 0.0;  // rows after the four
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, q, 0, 0, 0);
+    q12 = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y2, q12, 0, 0, 0);
+    q22 = __builtin_amdgcn_mfma_f64_16x16x4f64(x2, y2, q22, 0, 0, 0);
+    wd = __builtin_amdgcn_mfma_f64_16x16x4f64(below, zd, wd, 0, 0, 0);
+    w21 = __builtin_amdgcn_mfma_f64_16x16x4f64(half ? below : -y2, half ? z21 : zd, w21, 0, 0, 0);
+    const int cc = 4 * b + g;  // this lane's column of U and row of U^-1
+    t[(r0 + cc) * TP + r0 + m] = y1;
+    inv[(r0 + m) * TP + r0 + cc] = zd;
+    if (half) inv[m * TP + 16 + cc] = z21;
+    else t[cc * TP + 16 + m] = y2;
+  }
+  if (lane < TB) piv[lane] = own;
+  return bad;
+}
+
+// One problem of a batch of factorisations (gp_optimize): strides between
+// problems; a single fit has one.
+struct Chol {
+  double* A;        // L (in place of C), tile rows up to the y row
+  double* W;        // L^-1 (INV), same layout
+  double* dinv;     // inverses of the diagonal tiles, TB x TB each
+  int* info;        // 0, or k + 1 for the first pivot k that is not positive
+  int ld, nt;       // leading dimension, column tiles
+  size_t stride, dstride;
+};
+
+// After its tile is final: Cholesky factor and inverse of diagonal tile `p`
+// (all threads; the tile is in t), scaled from L D L^T on the way out.
+__device__ void finish_diag(const Chol& M, int z, int p, bool inv_out, double* t, double* inv) {
   __shared__ int bad;
-  const int tid = threadIdx.x, kb = min(CB, n - k0);
-  if (k0 > 0 && *info != 0) return;  // an earlier pivot failed (uniform)
-  if (tid == 0) bad = 0;
-  for (int e = tid; e < kb * kb; e += blockDim.x) {
-    const int r = e / kb, c = e % kb;
-    a[r][c] = r >= c ? A[(k0 + r) + size_t(k0 + c) * ld] : 0.0;
+  __shared__ double piv[TB], root[TB], iroot[TB];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int b = tile_factor(t, inv, piv);
+    if (threadIdx.x == 0) bad = b;
+    if (threadIdx.x < TB) {
+      const double r = sqrt(piv[threadIdx.x]);
+      root[threadIdx.x] = r;
+      iroot[threadIdx.x] = 1.0 / r;
+    }
   }
   __syncthreads();
-  for (int c = 0; c < kb; ++c) {
-    if (tid == 0) {
-      const double d = a[c][c];
-      if (!(d > 0.0)) bad = k0 + c + 1;
-      else a[c][c] = sqrt(d);
-    }
-    __syncthreads();
-    if (bad) break;
-    if (tid > c && tid < kb) a[tid][c] /= a[c][c];
-    __syncthreads();
-    for (int e = tid; e < kb * kb; e += blockDim.x) {
-      const int r = e / kb, q = e % kb;
-      if (q > c && r >= q) a[r][q] -= a[r][c] * a[q][c];
-    }
-    __syncthreads();
+  double* const L = M.A + z * M.stride + size_t(p) * TB * (M.ld + 1);
+  double* const V = M.dinv + z * M.dstride + size_t(p) * TB * TB;
+  double* const Wd = M.W + (inv_out ? z * M.stride + size_t(p) * TB * (M.ld + 1) : 0);
+  for (int e = threadIdx.x; e < TB * TB; e += blockDim.x) {
+    const int r = e % TB, c = e / TB;
+    const double u = r == c ? 1.0 : (r > c ? t[c * TP + r] : 0.0);
+    const double ui = r >= c ? inv[c * TP + r] * iroot[r] : 0.0;
+    L[r + size_t(c) * M.ld] = u * root[c];
+    V[e] = ui;
+    if (inv_out) Wd[r + size_t(c) * M.ld] = ui;
   }
-  for (int e = tid; e < kb * kb; e += blockDim.x) {
-    const int r = e / kb, c = e % kb;
-    if (r >= c) A[(k0 + r) + size_t(k0 + c) * ld] = a[r][c];
-  }
-  if (tid == 0) *info = bad;
+  if (threadIdx.x == 0 && bad >= 0) M.info[z] = p * TB + bad + 1;
 }
 
-// Rows k0 + kb .. n - 1 of the panel: x L_kk^T = a, by forward substitution
-// along the row.
-__global__ __launch_bounds__(256) void k_chol_panel(int n, int ld, double* __restrict__ A,
-                                                    const int* __restrict__ info, int k0) {
-  __shared__ double l[CB][CB + 1];
-  if (*info != 0) return;
-  const int tid = threadIdx.x, kb = CB;  // a panel with rows below it is full width
-  for (int e = tid; e < kb * kb; e += blockDim.x) {
-    const int r = e / kb, c = e % kb;
-    l[r][c] = r >= c ? A[(k0 + r) + size_t(k0 + c) * ld] : 0.0;
+// Covariance tiles (i >= j) of every problem, padded with the identity, the
+// outputs y in tile row nt; the first diagonal tile is factored at once.
+// par (nullable): sigma_f^2, 1 / 2 l^2 and sigma_n^2 of each problem.  The
+// diagonal takes noise[i] when given (per-point variances), else sigma_n^2.
+template <bool INV>
+__global__ __launch_bounds__(256, 4) void k_gp_cov(int n, const double* __restrict__ X, const double* __restrict__ y,
+                                                KParams P, const double* __restrict__ par,
+                                                const double* __restrict__ noise, Chol M) {
+  __shared__ double t[TILE_EL], inv[TILE_EL];
+  const int z = blockIdx.y;
+  int i = int((sqrt(8.0 * double(blockIdx.x) + 1.0) - 1.0) * 0.5);
+  while ((i + 1) * (i + 2) / 2 <= int(blockIdx.x)) ++i;
+  while (i * (i + 1) / 2 > int(blockIdx.x)) --i;
+  const int j = int(blockIdx.x) - i * (i + 1) / 2;
+  double* const A = M.A + z * M.stride;
+  if (j >= M.nt) return;  // the y row has no diagonal tile
+  if (i == M.nt) {
+    if (threadIdx.x < TB) {
+      const int c = j * TB + threadIdx.x;
+      A[size_t(i) * TB + size_t(c) * M.ld] = c < n ? y[c] : 0.0;
+    }
+    return;
   }
-  __syncthreads();
-  const int i = k0 + kb + blockIdx.x * blockDim.x + tid;
-  if (i >= n) return;
-  double x[CB];
-#pragma unroll
-  for (int c = 0; c < CB; ++c) {
-    double t = A[i + size_t(k0 + c) * ld];
-#pragma unroll
-    for (int m = 0; m < c; ++m) t -= x[m] * l[c][m];
-    x[c] = t / l[c][c];
-    A[i + size_t(k0 + c) * ld] = x[c];
+  if (par) {
+    P.sf2 = par[3 * z];
+    P.inv_2l2 = par[3 * z + 1];
+    P.sn2 = par[3 * z + 2];
+  }
+  const bool first = i == 0 && j == 0;
+  for (int e = threadIdx.x; e < TB * TB; e += blockDim.x) {
+    const int r = i * TB + e % TB, c = j * TB + e / TB;
+    double v = r == c ? 1.0 : 0.0;
+    if (r < n && c < n) {
+      v = sqexp(X + GP_MAXD * r, X + GP_MAXD * c, P);
+      if (r == c) v += noise ? noise[r] : P.sn2;
+    }
+    if (first) t[(e / TB) * TP + e % TB] = v;
+    else A[r + size_t(c) * M.ld] = v;
+  }
+  if (first) {
+    if (threadIdx.x == 0) M.info[z] = 0;
+    finish_diag(M, z, 0, INV, t, inv);
   }
 }
 
-// Trailing update A_ij -= sum_c P_ic P_jc over the lower triangle from row
-// and column k0 + CB on, one CB x CB tile per workgroup (tiles numbered row
-// by row over the lower triangle of tiles).
-__global__ __launch_bounds__(256) void k_chol_update(int n, int ld, double* __restrict__ A,
-                                                     const int* __restrict__ info, int k0) {
-  __shared__ double pi[CB][CB + 1], pj[CB][CB + 1];
-  if (*info != 0) return;
-  const int t0 = k0 + CB, b = blockIdx.x;
-  int ti = int((sqrt(8.0 * double(b) + 1.0) - 1.0) * 0.5);
-  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-  while (ti * (ti + 1) / 2 > b) --ti;
-  const int tj = b - ti * (ti + 1) / 2;
-  const int i0 = t0 + ti * CB, j0 = t0 + tj * CB;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < CB * CB; e += blockDim.x) {
-    const int r = e % CB, c = e / CB;
-    pi[r][c] = i0 + r < n ? A[(i0 + r) + size_t(k0 + c) * ld] : 0.0;
-    pj[r][c] = j0 + r < n ? A[(j0 + r) + size_t(k0 + c) * ld] : 0.0;
+// Elimination of panel p (see above); launched for p = 0 .. nt with the tiles
+// (i, j), i >= max(p - 1, 0), j <= min(i, nt - 1), numbered row by row.  The
+// last launch only replaces panel nt - 1's tiles.  Without INV (the evidence
+// alone) there is no W and only the y row of S is kept.  alpha (INV) receives
+// C^-1 y.
+template <bool INV>
+__global__ __launch_bounds__(256, 4) void k_gp_panel(int p, Chol M, double* __restrict__ alpha) {
+  __shared__ double f[TILE_EL], g[TILE_EL], v[TILE_EL];
+  const int z = blockIdx.y;
+  if (M.info[z] != 0) return;
+  const int i0 = INV ? max(p - 1, 0) : p, first = i0 * (i0 + 1) / 2;
+  const int b = int(blockIdx.x) + first;
+  int i = int((sqrt(8.0 * double(b) + 1.0) - 1.0) * 0.5);
+  while ((i + 1) * (i + 2) / 2 <= b) ++i;
+  while (i * (i + 1) / 2 > b) --i;
+  const int j = b - i * (i + 1) / 2, nt = M.nt;
+  if (j >= nt || i > nt) return;
+  const size_t ld = M.ld;
+  double* const A = M.A + z * M.stride;
+  double* const W = M.W + z * M.stride;
+  auto tile = [&](double* base, int ti, int tj) { return base + size_t(ti) * TB + size_t(tj) * TB * ld; };
+  const Quarter Q;
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  // panel p - 1's tiles take their final values
+  const bool late_s = p > 0 && j == p - 1 && i >= p && (INV || i == nt);
+  const bool late_z = INV && p > 0 && i == p - 1 && j < p - 1;
+  if (late_s || late_z) {
+    const double* const dv = M.dinv + z * M.dstride + size_t(p - 1) * TB * TB;
+    tile_load(v, dv, TB);
+    double* const out = late_s ? tile(A, i, j) : tile(W, i, j);
+    tile_load(f, out, ld);
+    __syncthreads();
+    const f64x4 s = late_s ? tile_mma<TB>(f + 16 * Q.wr, TP, v + 16 * Q.wc, TP, 1, 1.0, zero)
+                           : tile_mma<TB>(v + 16 * Q.wr, TP, f + 16 * Q.wc * TP, 1, TP, 1.0, zero);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[Q.r + size_t(Q.c + 4 * k) * ld] = s[k];
+    __syncthreads();
+  }
+  if (INV && p == nt && i == nt) {  // the y row of W is complete
+    if (threadIdx.x < TB) alpha[j * TB + threadIdx.x] = -tile(W, nt, j)[size_t(threadIdx.x) * ld];
+    return;
+  }
+  if (p == nt || i <= p || (!INV && j <= p)) return;
+  const double* const dp = M.dinv + z * M.dstride + size_t(p) * TB * TB;
+  double* const out = j > p ? tile(A, i, j) : tile(W, i, j);
+  f64x4 acc = zero;
+  if (j != p) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] = out[Q.r + size_t(Q.c + 4 * k) * ld];
+  }
+  tile_load(v, dp, TB);
+  tile_load(f, tile(A, i, p), ld);
+  if (j > p && j < i) tile_load(g, tile(A, j, p), ld);
+  else if (j < p) tile_load(g, tile(W, p, j), ld);
+  __syncthreads();
+  // S(i), and S(j) or Z(p, j) kept as G(c, k) = [k][c]
+  const f64x4 si = tile_mma<TB>(f + 16 * Q.wr, TP, v + 16 * Q.wc, TP, 1, 1.0, zero);
+  f64x4 sj = zero;
+  if (j > p && j < i) sj = tile_mma<TB>(g + 16 * Q.wr, TP, v + 16 * Q.wc, TP, 1, 1.0, zero);
+  else if (j < p) sj = tile_mma<TB>(v + 16 * Q.wr, TP, g + 16 * Q.wc * TP, 1, TP, 1.0, zero);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    f[(Q.c + 4 * k) * TP + Q.r] = si[k];
+    if (j > p && j < i) g[(Q.c + 4 * k) * TP + Q.r] = sj[k];
+    else if (j < p) g[Q.r * TP + Q.c + 4 * k] = sj[k];
   }
   __syncthreads();
-  const int r = tid % CB;
-  for (int q = tid / CB; q < CB; q += blockDim.x / CB) {
-    const int i = i0 + r, j = j0 + q;
-    if (i < n && j <= i) {
-      double t = 0.0;
-#pragma unroll 8
-      for (int c = 0; c < CB; ++c) t += pi[r][c] * pj[q][c];
-      A[i + size_t(j) * ld] -= t;
-    }
+  if (j == p) acc = tile_mma<TB>(f + 16 * Q.wr, TP, v + 16 * Q.wc * TP, 1, TP, -1.0, acc);
+  else acc = tile_mma<TB>(f + 16 * Q.wr, TP, (j == i ? f : g) + 16 * Q.wc, TP, 1, -1.0, acc);
+  if (j > p && i == j && i == p + 1) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[(Q.c + 4 * k) * TP + Q.r] = acc[k];
+    finish_diag(M, z, p + 1, INV, g, v);
+    return;
   }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) out[Q.r + size_t(Q.c + 4 * k) * ld] = acc[k];
 }
 
 // x = L^-1 b (lower) then, if `both`, x = L^-T x: column-oriented
@@ -229,23 +458,6 @@ __global__ void k_gp_unpack(int m, int have_data, const double* __restrict__ res
   if (q >= m) return;
   mean[q] = have_data ? res[2 * q] * s_q : 0.0;
   var[q] = (have_data ? res[2 * q + 1] : sf2) * s_q * s_q;
-}
-
-// Column j of L^-1 per workgroup: forward substitution of L x = e_j, whose
-// entries above j are zero. x lives in LDS (dynamic, n doubles); every
-// thread derives the pivot value itself, so one barrier per step suffices.
-__global__ __launch_bounds__(256) void k_gp_tri_inv(int n, int ld, const double* __restrict__ L,
-                                                    double* __restrict__ Li) {
-  extern __shared__ double x[];
-  const int j = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-  for (int i = j + tid; i < n; i += nt) x[i] = i == j ? 1.0 : 0.0;
-  for (int k = j; k < n; ++k) {
-    __syncthreads();
-    const double xk = x[k] / L[k + size_t(k) * ld];
-    // the pivot slot is not rewritten in this step, the others only by their owner
-    for (int i = k + 1 + tid; i < n; i += nt) x[i] -= L[i + size_t(k) * ld] * xk;
-    if (tid == 0) Li[k + size_t(j) * ld] = xk;
-  }
 }
 
 // L grew by row r (its leading rows unchanged): row r of L^-1 is
@@ -340,6 +552,237 @@ __global__ __launch_bounds__(256) void k_gp_lml(int n, int ld, const double* __r
   }
 }
 
+// ---------------------------------------------------------------------------
+// Evidence of many hyperparameter sets at once (gp_optimize).
+// ---------------------------------------------------------------------------
+constexpr int EV_MAX = 256;   // sets of a launch: one per compute unit
+constexpr int EV_LDS_N = 128; // points whose covariance one workgroup keeps in LDS
+
+// State of the search on the device: logarithms of sigma_f, ell and sigma_n
+// (scaled) now and at the start of the cycle, the evidence now, and the
+// direction and bracket of the current line search.
+struct EvState {
+  double x[3], x0[3], best, dir[3], lo, hi;
+};
+
+// One round of a line search.  axis: parameter 0-2, 3 the direction the cycle
+// has taken so far (scaled to its largest component), -1 no line: set t is
+// pts[t].  Round 0 opens the bracket at the current point +- width; a later
+// round closes it around the best of the nb sets of the round before (between
+// its neighbours); the last one takes that best where it beats the point the
+// search started from.  Every wavefront that calls it computes the same.
+struct EvLine {
+  int axis, round, last, first_of_cycle, nb;
+  double width;
+  const double* pts;
+  const EvState* in;
+  EvState* out;
+  const double* lml_in;
+  double* lml_out;
+};
+
+__device__ __forceinline__ EvState ev_step(const EvLine& E) {
+  EvState S = *E.in;
+  if (E.round == 0) {
+    double big = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (E.first_of_cycle) S.x0[k] = S.x[k];
+      const double move = S.x[k] > -INFINITY ? S.x[k] - S.x0[k] : 0.0;
+      S.dir[k] = E.axis == 3 ? move : (E.axis == k ? 1.0 : 0.0);
+      big = fmax(big, fabs(S.dir[k]));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) S.dir[k] = big > 0.0 ? S.dir[k] / big : 0.0;
+    S.lo = -E.width;
+    S.hi = E.width;
+    return S;
+  }
+  const int lane = threadIdx.x & 63;
+  double f = -INFINITY;
+  int at = 0;
+  for (int t = lane; t < E.nb; t += 64) {  // largest, the first of equals
+    const double v = E.lml_in[t];
+    if (v > f) {
+      f = v;
+      at = t;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double v = __shfl_xor(f, o);
+    const int w = __shfl_xor(at, o);
+    if (v > f || (v == f && w < at)) {
+      f = v;
+      at = w;
+    }
+  }
+  const double h = (S.hi - S.lo) / double(E.nb + 1), c = S.lo + double(at + 1) * h;
+  if (E.last) {
+    if (f >= S.best) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) S.x[k] += S.dir[k] != 0.0 ? c * S.dir[k] : 0.0;
+      S.best = f;
+    }
+  } else {
+    S.lo = c - h;
+    S.hi = c + h;
+  }
+  return S;
+}
+
+// sigma_f^2, 1 / 2 l^2 and sigma_n^2 of set t; block 0 of the launch keeps
+// the state for the next one.
+__device__ __forceinline__ void ev_set(const EvLine& E, int t, bool keep, double& sf2, double& i2l2, double& sn2) {
+  double x[3];
+  if (E.axis < 0) {
+    for (int k = 0; k < 3; ++k) x[k] = E.pts[3 * t + k];
+  } else {
+    const EvState S = ev_step(E);
+    if (keep) *E.out = S;
+    const double c = S.lo + double(t + 1) * ((S.hi - S.lo) / double(E.nb + 1));
+    for (int k = 0; k < 3; ++k) x[k] = S.x[k] + (S.dir[k] != 0.0 ? c * S.dir[k] : 0.0);
+  }
+  sf2 = exp(2.0 * x[0]);
+  i2l2 = 0.5 * exp(-2.0 * x[1]);
+  sn2 = exp(2.0 * x[2]);
+}
+
+// Parameters of the sets of a round (panel elimination), or the end of a line
+// search (E.last: the state only).
+__global__ __launch_bounds__(EV_MAX) void k_gp_ev_line(EvLine E, double* __restrict__ par) {
+  const int t = threadIdx.x;
+  if (E.last) {
+    const EvState S = ev_step(E);
+    if (t == 0) *E.out = S;
+    return;
+  }
+  double a, b, c;
+  ev_set(E, t < E.nb ? t : 0, t == 0, a, b, c);
+  if (t < E.nb) {
+    par[3 * t] = a;
+    par[3 * t + 1] = b;
+    par[3 * t + 2] = c;
+  }
+}
+
+// Evidence of set blockIdx.x by one workgroup (n <= EV_LDS_N): C with y as one
+// more row, eliminated as L D L^T one column at a time -- only reciprocals of
+// the pivots on the way, and
+//   y^T C^-1 y = sum z_k^2 / d_k, log det C = sum log d_k
+// need no back-substitution.  The matrix stays in registers: thread (tx, ty)
+// of TX x 16 holds rows tx + TX a and columns ty + 16 b; LDS carries the
+// current column (two buffers, one barrier a column).  What bounds it is the
+// chain of a column (LDS, reciprocal, update, barrier): 22 us for 256 sets of
+// 48 points, where one set took 82 us in eight launches and two read-backs.
+template <int TX, int A, int B>
+__global__ __launch_bounds__(TX * 16) void k_gp_ev_lds(int n, const double* __restrict__ X,
+                                                       const double* __restrict__ y, KParams P,
+                                                       const double* __restrict__ noise, EvLine E) {
+  __shared__ double col[2][TX * A];
+  __shared__ double piv[16 * B], zz[16 * B];
+  const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+  ev_set(E, blockIdx.x, blockIdx.x == 0 && tid == 0, P.sf2, P.inv_2l2, P.sn2);
+  double v[A][B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int j = ty + 16 * b;
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      const int i = tx + TX * a;
+      v[a][b] = 0.0;
+      if (TX * (a + 1) <= 16 * b) continue;  // above the diagonal
+      if (i >= j && j < n && i <= n) {
+        if (i == n) {
+          v[a][b] = y[j];
+        } else {
+          v[a][b] = sqexp(X + GP_MAXD * i, X + GP_MAXD * j, P);
+          if (i == j) v[a][b] += noise ? noise[i] : P.sn2;
+        }
+      }
+      if (b == 0 && ty == 0) col[0][i] = v[a][0];
+    }
+  }
+  __syncthreads();
+  bool ok = true;
+#pragma unroll
+  for (int kb = 0; kb < B; ++kb) {
+    for (int kk = 0; kk < 16; ++kk) {
+      const int k = 16 * kb + kk;
+      if (k >= n) break;  // uniform
+      const double* const c = col[k & 1];
+      const double d = c[k];
+      ok = ok && d > 0.0;
+      const double ri = reciprocal(d);
+      if (tid == 0) {
+        piv[k] = d;
+        zz[k] = c[n];
+      }
+      double ci[A];
+#pragma unroll
+      for (int a = 0; a < A; ++a) ci[a] = c[tx + TX * a];
+      double* const nx = col[(k + 1) & 1];
+#pragma unroll
+      for (int b = kb; b < B; ++b) {
+        const double fj = c[ty + 16 * b] * ri;  // columns up to k are not used again
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+          if (TX * (a + 1) <= 16 * b) continue;
+          v[a][b] = fma(-ci[a], fj, v[a][b]);
+        }
+        if (b <= kb + 1 && ty + 16 * b == k + 1) {
+#pragma unroll
+          for (int a = 0; a < A; ++a) nx[tx + TX * a] = v[a][b];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (tid < 64) {
+    double q = 0.0, lg = 0.0;
+    for (int k = tid; k < n; k += 64) {
+      q += zz[k] * zz[k] / piv[k];
+      lg += log(piv[k]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      q += __shfl_xor(q, o);
+      lg += __shfl_xor(lg, o);
+    }
+    if (tid == 0) E.lml_out[blockIdx.x] = ok ? -0.5 * q - 0.5 * lg - 0.5 * double(n) * log(2.0 * M_PI) : -INFINITY;
+  }
+}
+
+// Evidence of set blockIdx.x from its factor and the y row of S.
+__global__ __launch_bounds__(256) void k_gp_ev_sum(int n, Chol M, double* __restrict__ lml) {
+  __shared__ double red[2][4];
+  const double* const A = M.A + blockIdx.x * M.stride;
+  const int tid = threadIdx.x;
+  double q = 0.0, lg = 0.0;
+  for (int k = tid; k < n; k += blockDim.x) {
+    const double z = A[size_t(M.nt) * TB + size_t(k) * M.ld];
+    q += z * z;
+    lg += log(A[k + size_t(k) * M.ld]);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    q += __shfl_xor(q, o);
+    lg += __shfl_xor(lg, o);
+  }
+  if ((tid & 63) == 0) {
+    red[0][tid >> 6] = q;
+    red[1][tid >> 6] = lg;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w) {
+      q += red[0][w];
+      lg += red[1][w];
+    }
+    lml[blockIdx.x] = M.info[blockIdx.x] == 0 ? -0.5 * q - lg - 0.5 * double(n) * log(2.0 * M_PI) : -INFINITY;
+  }
+}
+
 // New last row of L for the point at index n: row = L^-1 c, then the pivot.
 __global__ __launch_bounds__(1024) void k_gp_append_row(int n, int ld, const double* __restrict__ X, KParams P,
                                                         double* __restrict__ L, double* __restrict__ row,
@@ -399,9 +842,13 @@ void normalise(hmd_gp* g) {
     const double fallback = 0.25 * g->hyp.range[k];
     double m = 0.0;
     if (g->hyp.scale_mode == 0 && n >= 2) {
+      // sum of |x_i - x_j| over pairs: in ascending order, x_i is the larger
+      // of i pairs; from the smallest value on, so that no part cancels
+      std::vector<double> v(n);
+      for (int i = 0; i < n; ++i) v[i] = g->X[size_t(i) * d + k];
+      std::sort(v.begin(), v.end());
       double s = 0.0;
-      for (int i = 0; i < n; ++i)
-        for (int j = i + 1; j < n; ++j) s += std::fabs(g->X[size_t(i) * d + k] - g->X[size_t(j) * d + k]);
+      for (int i = 1; i < n; ++i) s += (v[i] - v[i - 1]) * (double(i) * double(n - i));
       m = s / (0.5 * double(n) * double(n - 1));
     }
     g->scale[k] = m > 0.0 ? m : fallback;
@@ -422,92 +869,95 @@ void normalise(hmd_gp* g) {
   }
 }
 
+// Device memory for `need` points: one allocation, grown by doubling.
 int reserve(hmd_gp* g, int need) {
   hmd_ctx* ctx = g->ctx;
   if (need <= g->cap) return HMD_OK;
   int cap = g->cap > 0 ? g->cap : 64;
   while (cap < need) cap *= 2;
-  for (double* p : {g->dX, g->dy, g->dL, g->dLi, g->dalpha, g->dtmp, g->dnoise})
-    if (p) (void)hipFree(p);
-  HMD_HIP(ctx, hipMalloc(&g->dX, sizeof(double) * GP_MAXD * cap));
-  HMD_HIP(ctx, hipMalloc(&g->dy, sizeof(double) * cap));
-  HMD_HIP(ctx, hipMalloc(&g->dL, sizeof(double) * size_t(cap) * cap));
-  HMD_HIP(ctx, hipMalloc(&g->dLi, sizeof(double) * size_t(cap) * cap));
-  HMD_HIP(ctx, hipMalloc(&g->dalpha, sizeof(double) * cap));
-  HMD_HIP(ctx, hipMalloc(&g->dtmp, sizeof(double) * (cap + 1)));
-  HMD_HIP(ctx, hipMalloc(&g->dnoise, sizeof(double) * cap));
+  if (g->slab) (void)hipFree(g->slab);
+  g->slab = nullptr;
+  g->cap = 0;
+  const int ld = cap + TB;
+  const size_t mat = size_t(ld) * cap;
+  HMD_HIP(ctx, hipMalloc(&g->slab, sizeof(double) * (2 * mat + size_t(TB) * cap + size_t(GP_MAXD + 5) * cap)));
+  g->dL = g->slab;
+  g->dLi = g->dL + mat;
+  g->ddinv = g->dLi + mat;
+  g->dalpha = g->ddinv + size_t(TB) * cap;
+  g->dtmp = g->dalpha + cap;
+  g->dX = g->dtmp + 2 * cap;  // inputs, outputs and noise variances, packed by upload_db
   g->cap = cap;
+  g->ld = ld;
   return HMD_OK;
 }
 
+// Database to the device as one copy: inputs (padded to GP_MAXD columns),
+// scaled outputs, noise variances.  The host buffer lives as long as the GP,
+// and every call that comes here waits for the stream before it returns.
 int upload_db(hmd_gp* g) {
   hmd_ctx* ctx = g->ctx;
-  std::vector<double> xs(size_t(GP_MAXD) * g->n, 0.0), ys(g->n), nz(g->n);
-  for (int i = 0; i < g->n; ++i) {
-    for (int k = 0; k < g->d; ++k) xs[size_t(i) * GP_MAXD + k] = g->X[size_t(i) * g->d + k];
-    ys[i] = g->y[i] / g->s_q;
+  const size_t n = size_t(g->n);
+  g->stage.assign((GP_MAXD + 2) * n, 0.0);
+  for (size_t i = 0; i < n; ++i) {
+    for (int k = 0; k < g->d; ++k) g->stage[i * GP_MAXD + k] = g->X[i * g->d + k];
+    g->stage[GP_MAXD * n + i] = g->y[i] / g->s_q;
     const double e = g->se[i] / g->s_q;
-    nz[i] = e * e;
+    g->stage[(GP_MAXD + 1) * n + i] = e * e;
   }
-  HMD_HIP(ctx, hipMemcpyAsync(g->dX, xs.data(), 8 * xs.size(), hipMemcpyHostToDevice, ctx->stream));
-  HMD_HIP(ctx, hipMemcpyAsync(g->dy, ys.data(), 8 * ys.size(), hipMemcpyHostToDevice, ctx->stream));
-  HMD_HIP(ctx, hipMemcpyAsync(g->dnoise, nz.data(), 8 * nz.size(), hipMemcpyHostToDevice, ctx->stream));
-  // the host staging vectors end with this function
-  HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  g->dy = g->dX + GP_MAXD * n;
+  g->dnoise = g->dy + n;
+  HMD_HIP(ctx, hipMemcpyAsync(g->dX, g->stage.data(), 8 * g->stage.size(), hipMemcpyHostToDevice, ctx->stream));
   return HMD_OK;
 }
 
-int solve_alpha(hmd_gp* g, bool grown_by_row, bool inverse = true) {
+// After a row was appended to L: the weights, and L^-1's new row.
+int solve_alpha(hmd_gp* g) {
   hmd_ctx* ctx = g->ctx;
   hipStream_t s = ctx->stream;
   HMD_HIP(ctx, hipMemcpyAsync(g->dalpha, g->dy, 8 * size_t(g->n), hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_gp_solve, dim3(1), dim3(1024), 0, s, g->n, g->cap, g->dL, g->dalpha, 1);
+  hipLaunchKernelGGL(k_gp_solve, dim3(1), dim3(1024), 0, s, g->n, g->ld, g->dL, g->dalpha, 1);
   HMD_HIP(ctx, hipGetLastError());
-  if (!inverse) return HMD_OK;
-  // L^-1 follows the factor: extended by its new row, or formed anew
-  const size_t lds = sizeof(double) * size_t(g->n);
-  if (grown_by_row)
-    hipLaunchKernelGGL(k_gp_inv_append_row, dim3((g->n + 3) / 4), dim3(256), lds, s, g->n - 1, g->cap, g->dL,
-                       g->dLi);
-  else
-    hipLaunchKernelGGL(k_gp_tri_inv, dim3(g->n), dim3(256), lds, s, g->n, g->cap, g->dL, g->dLi);
+  hipLaunchKernelGGL(k_gp_inv_append_row, dim3((g->n + 3) / 4), dim3(256), sizeof(double) * size_t(g->n), s, g->n - 1,
+                     g->ld, g->dL, g->dLi);
   HMD_HIP(ctx, hipGetLastError());
   return HMD_OK;
 }
 
-// Full refit: normalisation, covariance, factorisation, weights and L^-1.
-// The evidence search refits at fixed data (upload false: the database and
-// its scaling are already on the device) and needs no L^-1 (inverse false).
-int refit(hmd_gp* g, bool upload = true, bool inverse = true) {
+// Queues covariance and elimination of M's problems (`nb` of them).
+template <bool INV>
+void enqueue_factor(const hmd_gp* g, const Chol& M, int nb, const double* par, double* alpha) {
+  hipStream_t s = g->ctx->stream;
+  const int nt = M.nt;
+  hipLaunchKernelGGL(k_gp_cov<INV>, dim3((nt + 1) * (nt + 2) / 2, nb), dim3(256), 0, s, g->n, g->dX, g->dy, kparams(g),
+                     par, g->hyp.noise_mode == 1 ? g->dnoise : nullptr, M);
+  for (int p = 0; p <= nt; ++p) {
+    const int i0 = INV ? std::max(p - 1, 0) : p;
+    hipLaunchKernelGGL(k_gp_panel<INV>, dim3((nt + 1) * (nt + 2) / 2 - i0 * (i0 + 1) / 2, nb), dim3(256), 0, s, p, M,
+                       alpha);
+  }
+}
+
+// Full refit: normalisation, covariance, factorisation, weights and L^-1
+// (upload false: the database and its scaling are already on the device).
+int refit(hmd_gp* g, bool upload = true) {
   hmd_ctx* ctx = g->ctx;
-  normalise(g);
+  if (upload) normalise(g);
   if (g->n == 0) return HMD_OK;
   int rc = reserve(g, g->n);
   if (rc != HMD_OK) return rc;
   if (upload && (rc = upload_db(g)) != HMD_OK) return rc;
-  hipStream_t s = ctx->stream;
-  const KParams P = kparams(g);
-  hipLaunchKernelGGL(k_gp_cov, dim3((g->n + 255) / 256, g->n), dim3(256), 0, s, g->n, g->cap, g->dX, P,
-                     g->hyp.noise_mode == 1 ? g->dnoise : nullptr, g->dL);
-  for (int k0 = 0; k0 < g->n; k0 += CB) {
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, s, g->n, g->cap, g->dL, g->dinfo, k0);
-    const int rest = g->n - k0 - CB;
-    if (rest > 0) {
-      const int nt = (rest + CB - 1) / CB;
-      hipLaunchKernelGGL(k_chol_panel, dim3((rest + 255) / 256), dim3(256), 0, s, g->n, g->cap, g->dL, g->dinfo, k0);
-      hipLaunchKernelGGL(k_chol_update, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, g->n, g->cap, g->dL, g->dinfo,
-                         k0);
-    }
-  }
+  const Chol M{g->dL, g->dLi, g->ddinv, g->dinfo, g->ld, (g->n + TB - 1) / TB, 0, 0};
+  enqueue_factor<true>(g, M, 1, nullptr, g->dalpha);
   HMD_HIP(ctx, hipGetLastError());
   int info = 0;
-  HMD_HIP(ctx, hipMemcpyAsync(&info, g->dinfo, sizeof(int), hipMemcpyDeviceToHost, s));
-  HMD_HIP(ctx, hipStreamSynchronize(s));
+  HMD_HIP(ctx, hipMemcpyAsync(&info, g->dinfo, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+  HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
   if (info != 0) {
     ctx->err = "gp: covariance not positive definite at pivot " + std::to_string(info - 1);
     return HMD_ENOTSPD;
   }
-  return solve_alpha(g, false, inverse);
+  return HMD_OK;
 }
 
 }  // namespace
@@ -605,13 +1055,13 @@ int gp_append(hmd_gp* g, const double* x, double y, double y_se) {
     const double e = y_se / g->s_q;
     P1.sn2 = e * e;
   }
-  hipLaunchKernelGGL(k_gp_append_row, dim3(1), dim3(1024), 0, s, g->n - 1, g->cap, g->dX, P1, g->dL, g->dtmp,
+  hipLaunchKernelGGL(k_gp_append_row, dim3(1), dim3(1024), 0, s, g->n - 1, g->ld, g->dX, P1, g->dL, g->dtmp,
                      g->dinfo);
   int info = 0;
   HMD_HIP(ctx, hipMemcpyAsync(&info, g->dinfo, sizeof(int), hipMemcpyDeviceToHost, s));
   HMD_HIP(ctx, hipStreamSynchronize(s));
   if (info != 0) return full_refit();
-  rc = solve_alpha(g, true);
+  rc = solve_alpha(g);
   if (rc != HMD_OK) return rc;
   HMD_HIP(ctx, hipStreamSynchronize(s));
   return HMD_OK;
@@ -643,7 +1093,7 @@ int gp_predict(hmd_gp* g, const double* Xs, int m, double* mean, double* var) {
     for (int k = 0; k < g->d; ++k) xs[size_t(q) * GP_MAXD + k] = Xs[size_t(q) * g->d + k];
   hipStream_t s = ctx->stream;
   HMD_HIP(ctx, hipMemcpyAsync(dXq, xs.data(), 8 * xs.size(), hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->cap, g->dX, dXq,
+  hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->ld, g->dX, dXq,
                      g->dLi, g->dalpha, kparams(g), dres);
   HMD_HIP(ctx, hipGetLastError());
   HMD_HIP(ctx, hipMemcpyAsync(res.data(), dres, 8 * res.size(), hipMemcpyDeviceToHost, s));
@@ -674,7 +1124,7 @@ int gp_predict_dev(hmd_gp* g, const double* dXs, int m, double* dmean, double* d
   hipLaunchKernelGGL(k_gp_pack, dim3((m + 255) / 256), dim3(256), 0, s, m, g->d, dXs, dXq);
   HMD_HIP(ctx, hipGetLastError());
   if (g->n > 0) {
-    hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->cap, g->dX,
+    hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->ld, g->dX,
                        dXq, g->dLi, g->dalpha, kparams(g), dres);
     HMD_HIP(ctx, hipGetLastError());
   }
@@ -693,7 +1143,7 @@ int gp_log_marginal(hmd_gp* g, double* lml) {
   }
   HMD_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t s = ctx->stream;
-  hipLaunchKernelGGL(k_gp_lml, dim3(1), dim3(256), 0, s, g->n, g->cap, g->dL, g->dy, g->dalpha, g->dout);
+  hipLaunchKernelGGL(k_gp_lml, dim3(1), dim3(256), 0, s, g->n, g->ld, g->dL, g->dy, g->dalpha, g->dout);
   double h[2];
   HMD_HIP(ctx, hipMemcpyAsync(h, g->dout, sizeof(h), hipMemcpyDeviceToHost, s));
   HMD_HIP(ctx, hipStreamSynchronize(s));
@@ -705,10 +1155,19 @@ int gp_log_marginal(hmd_gp* g, double* lml) {
 // evidence can have several local maxima (the periodic kernel's has in ell),
 // so the search first evaluates it on a grid of 17 points per chosen
 // parameter, a quarter decade apart over two decades either side of the
-// start, then refines from the best grid point by cyclic golden-section
-// searches over the logarithm of each chosen parameter, bracketed by a factor
-// 10 around the current value, each refit on the device, until a cycle gains
-// less than 1e-12 relative (at most 30 cycles).
+// start, then refines from the best grid point by cyclic line searches over
+// the logarithm of each chosen parameter, bracketed by a factor 10 around the
+// current value, until a cycle gains less than 1e-12 relative (at most 30
+// cycles).
+//
+// Refits are independent of each other, so a whole grid, or a round of up to
+// 256 points along a line, is one set of launches: a line search closes its
+// bracket by (nb + 1) / 2 per round, five rounds where golden sections took 63
+// refits in turn.  A cycle ends with a search along the way it came, which
+// crosses the ridge that sigma_f and ell share (4 cycles instead of 12).  The
+// rounds of a cycle are queued without waiting for the host.  Up to EV_LDS_N
+// points a set is one workgroup; beyond, the panel elimination runs on all
+// sets at once, as many as a workspace of kEvBytes holds.
 int gp_optimize(hmd_gp* g, int mask, double* lml) {
   if (!g || mask <= 0 || mask > 7) return HMD_EINVAL;
   hmd_ctx* ctx = g->ctx;
@@ -716,92 +1175,133 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
     ctx->err = "gp_optimize: needs data, and sigma_n only with uniform noise";
     return HMD_EINVAL;
   }
+  HMD_HIP(ctx, hipSetDevice(ctx->device));
+  hipStream_t s = ctx->stream;
+  const int n = g->n, nt = (n + TB - 1) / TB, ld = (nt + 1) * TB;
   if (mask & 4) g->hyp.sigma_n = g->sigma_n * g->s_q;  // held explicitly from here on
-  // the database and its scaling stay on the device through the search
-  // (they do not depend on sigma_f, ell or sigma_n); L^-1 is formed once
-  // at the end
-  HMD_TRY(reserve(g, g->n));
   normalise(g);
+  HMD_TRY(reserve(g, n));
   HMD_TRY(upload_db(g));
-  auto get = [&](int k) {
-    return k == 0 ? g->hyp.sigma_f : (k == 1 ? g->hyp.ell : g->hyp.sigma_n / g->s_q);
-  };
-  auto set = [&](int k, double v) {
-    if (k == 0) g->hyp.sigma_f = v;
-    else if (k == 1) g->hyp.ell = v;
-    else g->hyp.sigma_n = v * g->s_q;
-  };
-  auto eval = [&](int k, double logv, double* out) -> int {
-    set(k, std::exp(logv));
-    const int rc = refit(g, false, false);
-    if (rc == HMD_ENOTSPD) {
-      *out = -INFINITY;
-      return HMD_OK;
+  // device buffers of the search, released on every return
+  struct Work {
+    double *A = nullptr, *dinv = nullptr, *small = nullptr;
+    int* info = nullptr;
+    ~Work() {
+      for (void* p : {(void*)A, (void*)dinv, (void*)small, (void*)info})
+        if (p) (void)hipFree(p);
     }
-    if (rc != HMD_OK) return rc;
-    return gp_log_marginal(g, out);
+  } w;
+  // parameters, points, two evidence buffers and two states
+  HMD_HIP(ctx, hipMalloc(&w.small, sizeof(double) * 8 * EV_MAX + 2 * sizeof(EvState)));
+  double* const par = w.small;
+  double* const pts_dev = w.small + 3 * EV_MAX;
+  double* const lml_dev[2] = {w.small + 6 * EV_MAX, w.small + 7 * EV_MAX};
+  EvState* const st_dev = reinterpret_cast<EvState*>(w.small + 8 * EV_MAX);
+  int nb = EV_MAX;
+  Chol M{};
+  if (n > EV_LDS_N) {
+    constexpr double kEvBytes = 8.0 * 1024 * 1024 * 1024;
+    M.ld = ld;
+    M.nt = nt;
+    M.stride = size_t(ld) * nt * TB;
+    M.dstride = size_t(nt) * TB * TB;
+    nb = int(std::min(double(EV_MAX), std::max(3.0, kEvBytes / (8.0 * double(M.stride + M.dstride)))));
+    while (hipMalloc(&w.A, sizeof(double) * M.stride * nb) != hipSuccess) {
+      w.A = nullptr;
+      (void)hipGetLastError();
+      if (nb == 3) {
+        ctx->err = "gp_optimize: device allocation failed";
+        return HMD_ENOMEM;
+      }
+      nb = std::max(3, nb / 2);
+    }
+    HMD_HIP(ctx, hipMalloc(&w.dinv, sizeof(double) * M.dstride * nb));
+    HMD_HIP(ctx, hipMalloc(&w.info, sizeof(int) * nb));
+    M.A = w.A;
+    M.dinv = w.dinv;
+    M.info = w.info;
+  }
+  int flip = 0;  // states and evidences alternate between launches
+  auto line = [&](int axis, int round, int last, int first, int m, double width) {
+    return EvLine{axis, round, last, first, m, width, pts_dev, st_dev + flip, st_dev + 1 - flip, lml_dev[flip],
+                  lml_dev[1 - flip]};
   };
+  const double* const noise = g->hyp.noise_mode == 1 ? g->dnoise : nullptr;
+  // one round: its sets' evidences
+  auto evaluate = [&](const EvLine& E) {
+    if (n <= 64) {
+      hipLaunchKernelGGL((k_gp_ev_lds<16, 5, 4>), dim3(E.nb), dim3(256), 0, s, n, g->dX, g->dy, kparams(g), noise, E);
+    } else if (n <= EV_LDS_N) {
+      hipLaunchKernelGGL((k_gp_ev_lds<32, 5, 8>), dim3(E.nb), dim3(512), 0, s, n, g->dX, g->dy, kparams(g), noise, E);
+    } else {
+      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, E, par);
+      enqueue_factor<false>(g, M, E.nb, par, nullptr);
+      hipLaunchKernelGGL(k_gp_ev_sum, dim3(E.nb), dim3(256), 0, s, n, M, E.lml_out);
+    }
+    flip = 1 - flip;
+  };
+  EvState st{};
+  st.x[0] = std::log(g->hyp.sigma_f);
+  st.x[1] = std::log(g->hyp.ell);
+  st.x[2] = g->sigma_n > 0.0 ? std::log(g->sigma_n) : -INFINITY;
   int idx[3], m = 0, total = 1;
-  double c0[3], cbest[3];
   for (int k = 0; k < 3; ++k)
     if (mask & (1 << k)) {
-      idx[m] = k;
-      c0[m] = cbest[m] = std::log(get(k));
-      ++m;
+      idx[m++] = k;
       total *= 17;
     }
-  double gbest = -INFINITY;
-  for (int p = 0; p < total; ++p) {
-    int r = p;
-    for (int j = 0; j < m; ++j, r /= 17) set(idx[j], std::exp(c0[j] + std::log(10.0) * (-2.0 + 0.25 * (r % 17))));
-    const int rc = refit(g, false, false);
-    if (rc == HMD_ENOTSPD) continue;
-    if (rc != HMD_OK) return rc;
-    double f;
-    HMD_TRY(gp_log_marginal(g, &f));
-    if (f > gbest) {
-      gbest = f;
-      for (int j = 0; j < m; ++j) cbest[j] = std::log(get(idx[j]));
-    }
-  }
-  for (int j = 0; j < m; ++j) set(idx[j], std::exp(cbest[j]));
-  const double gr = 0.5 * (std::sqrt(5.0) - 1.0);
-  double best = -INFINITY;
-  HMD_TRY(eval(0, std::log(get(0)), &best));
-  for (int cycle = 0; cycle < 30; ++cycle) {
-    const double start = best;
-    for (int k = 0; k < 3; ++k) {
-      if (!(mask & (1 << k))) continue;
-      const double c0 = std::log(get(k));
-      double a = c0 - std::log(10.0), b = c0 + std::log(10.0);
-      double x1 = b - gr * (b - a), x2 = a + gr * (b - a), f1, f2;
-      HMD_TRY(eval(k, x1, &f1));
-      HMD_TRY(eval(k, x2, &f2));
-      for (int it = 0; it < 60; ++it) {
-        if (f1 >= f2) {
-          b = x2; x2 = x1; f2 = f1; x1 = b - gr * (b - a);
-          HMD_TRY(eval(k, x1, &f1));
-        } else {
-          a = x1; x1 = x2; f1 = f2; x2 = a + gr * (b - a);
-          HMD_TRY(eval(k, x2, &f2));
+  st.best = -INFINITY;
+  {
+    EvState top = st;
+    std::vector<double> pts, val(nb);
+    for (int p0 = 0; p0 < total; p0 += nb) {
+      const int c = std::min(nb, total - p0);
+      pts.assign(3 * size_t(c), 0.0);
+      for (int p = 0; p < c; ++p) {
+        double* const x = &pts[3 * size_t(p)];
+        std::copy(st.x, st.x + 3, x);
+        int r = p0 + p;
+        for (int j = 0; j < m; ++j, r /= 17) x[idx[j]] += std::log(10.0) * (-2.0 + 0.25 * (r % 17));
+      }
+      HMD_HIP(ctx, hipMemcpyAsync(pts_dev, pts.data(), 8 * pts.size(), hipMemcpyHostToDevice, s));
+      const EvLine E = line(-1, 0, 0, 0, c, 0.0);
+      evaluate(E);
+      HMD_HIP(ctx, hipGetLastError());
+      HMD_HIP(ctx, hipMemcpyAsync(val.data(), E.lml_out, 8 * size_t(c), hipMemcpyDeviceToHost, s));
+      HMD_HIP(ctx, hipStreamSynchronize(s));
+      for (int p = 0; p < c; ++p)
+        if (val[p] > top.best) {
+          top.best = val[p];
+          std::copy(&pts[3 * size_t(p)], &pts[3 * size_t(p)] + 3, top.x);
         }
-      }
-      double fc;
-      const double xc = 0.5 * (a + b);
-      HMD_TRY(eval(k, xc, &fc));
-      double fold;
-      HMD_TRY(eval(k, c0, &fold));
-      if (fc >= fold) {
-        HMD_TRY(eval(k, xc, &best));
-      } else {
-        best = fold;  // the search did not beat the start: keep it (already refit)
-      }
     }
-    if (std::fabs(best - start) <= 1e-12 * std::fabs(best)) break;
+    st = top;
   }
-  HMD_TRY(refit(g, false, true));  // at the kept values, with L^-1 for predictions
-  if (lml) *lml = best;
-  HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  flip = 0;
+  HMD_HIP(ctx, hipMemcpyAsync(st_dev, &st, sizeof(st), hipMemcpyHostToDevice, s));
+  const double width = std::log(10.0);
+  const int rounds = int(std::ceil(std::log(2.0 * width / 1e-9) / std::log(0.5 * double(nb + 1))));
+  for (int cycle = 0; cycle < 30; ++cycle) {
+    const double start = st.best;
+    for (int j = 0; j < (m > 1 ? m + 1 : m); ++j) {
+      const int axis = j < m ? idx[j] : 3;
+      for (int r = 0; r < rounds; ++r) evaluate(line(axis, r, 0, j == 0 ? 1 : 0, nb, width));
+      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, line(axis, rounds, 1, 0, nb, width), par);
+      flip = 1 - flip;
+    }
+    HMD_HIP(ctx, hipGetLastError());
+    HMD_HIP(ctx, hipMemcpyAsync(&st, st_dev + flip, sizeof(st), hipMemcpyDeviceToHost, s));
+    HMD_HIP(ctx, hipStreamSynchronize(s));
+    if (!(std::fabs(st.best - start) > 1e-12 * std::fabs(st.best))) break;
+  }
+  if (mask & 1) g->hyp.sigma_f = std::exp(st.x[0]);
+  if (mask & 2) g->hyp.ell = std::exp(st.x[1]);
+  if (mask & 4) {
+    g->hyp.sigma_n = std::exp(st.x[2]) * g->s_q;
+    g->sigma_n = g->hyp.sigma_n / g->s_q;
+  }
+  HMD_TRY(refit(g, false));  // at the kept values, with L^-1 for predictions
+  if (lml) *lml = st.best;
   return HMD_OK;
 }
 
@@ -839,9 +1339,7 @@ int gp_scales(const hmd_gp* g, double* scale, double* s_q, double* sigma_n) {
 
 void gp_free(hmd_gp* g) {
   if (!g) return;
-  for (void* p : {(void*)g->dX, (void*)g->dy, (void*)g->dL, (void*)g->dLi, (void*)g->dalpha, (void*)g->dtmp,
-                  (void*)g->dnoise, (void*)g->dq,
-                  (void*)g->dout, (void*)g->dinfo})
+  for (void* p : {(void*)g->slab, (void*)g->dq, (void*)g->dout, (void*)g->dinfo})
     if (p) (void)hipFree(p);
   delete g;
 }

@@ -42,6 +42,32 @@ def test_fit_predict_matches_oracle(ctx, n):
     assert g.log_marginal() == pytest.approx(o.log_marginal(), rel=1e-9, abs=1e-9)
 
 
+@pytest.mark.parametrize("n", [31, 32, 33, 63, 96, 97, 128, 129])
+def test_tile_edges_fit_and_evidence(ctx, n):
+    # sizes around the factorisation's tiles (32) and the evidence search's
+    # one-workgroup limits (64, 128): weights, factor and inverse against the
+    # oracle (bars of test_fit_predict_matches_oracle), and the search's
+    # maximum against the oracle's evidence at the values it returns, which
+    # no step of a percent in either parameter may exceed
+    X, y, se = data(n, 500 + n)
+    hp = dict(ranges=RANGES, noise_mode=n % 2)
+    g = B.GP(ctx, X, y, se, B.gp_hyper(**hp))
+    o = OGP(X, y, se, Hyper(**hp))
+    Xs, _, _ = data(50, 900 + n)
+    (mg, vg), (mo, vo) = g.predict(Xs), o.predict(Xs)
+    assert np.abs(mg - mo).max() <= 1e-9 * np.abs(mo).max() + 1e-12
+    assert np.abs(vg - vo).max() <= 1e-9 * o.s_q ** 2
+    best = g.optimize(("sigma_f", "ell"))
+    h = g.hyper()
+
+    def evidence(sf, ell):
+        return OGP(X, y, se, Hyper(sigma_f=sf, ell=ell, **hp)).log_marginal()
+
+    assert best == pytest.approx(evidence(h["sigma_f"], h["ell"]), rel=1e-9, abs=1e-9)
+    for a, b in ((1.01, 1.0), (0.99, 1.0), (1.0, 1.01), (1.0, 0.99)):
+        assert evidence(a * h["sigma_f"], b * h["ell"]) <= best + 1e-9 * abs(best)
+
+
 def test_append_matches_oracle_refit(ctx):
     X, y, se = data(40, 7)
     g = B.GP(ctx, X[:30], y[:30], se[:30], B.gp_hyper(ranges=RANGES))
