@@ -7,7 +7,7 @@
 //   prediction   mean = K* alpha (Eq. predMeanEq),
 //                var = sigma_f^2 - |L^-1 k*|^2 (diagonal of Eq. predVarEq), with
 //                L^-1 formed once per factorisation so that a query is a
-//                parallel product, not a sequential solve
+//                product on the matrix cores, not a sequential solve
 //   evidence     -1/2 y^T alpha - sum log L_ii - n/2 log 2 pi (Eq. evidenceEq)
 // Options: each point's own noise variance on the diagonal (heteroscedastic),
 // the periodic kernel of App. B (Eq. periodicKernel) on a single input, and
@@ -42,7 +42,9 @@ struct hmd_gp {
   double* dalpha = nullptr;  // C^-1 y
   double* dtmp = nullptr;    // cap
   double* dnoise = nullptr;  // cap: per-point noise variances (heteroscedastic)
-  double* dq = nullptr;      // query staging
+  double* dq = nullptr;      // host queries and their results
+  double* dpart = nullptr;   // sums of row groups (predictions on the matrix cores)
+  size_t part_cap = 0;
   double* dout = nullptr;    // predictions / scalars
   int* dinfo = nullptr;
   size_t q_cap = 0;
@@ -443,21 +445,12 @@ __global__ __launch_bounds__(1024) void k_gp_solve(int n, int ld, const double* 
   }
 }
 
-// Device-pointer interop: queries row-major with d columns -> the padded
-// layout of the predict kernel; results (scaled back to output units) into
-// separate mean and variance arrays.
-__global__ void k_gp_pack(int m, int d, const double* __restrict__ src, double* __restrict__ dst) {
+// Prior at m queries (empty database).
+__global__ void k_gp_prior(int m, double var0, double* __restrict__ mean, double* __restrict__ var) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
-  for (int k = 0; k < GP_MAXD; ++k) dst[size_t(q) * GP_MAXD + k] = k < d ? src[size_t(q) * d + k] : 0.0;
-}
-
-__global__ void k_gp_unpack(int m, int have_data, const double* __restrict__ res, double s_q, double sf2,
-                            double* __restrict__ mean, double* __restrict__ var) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= m) return;
-  mean[q] = have_data ? res[2 * q] * s_q : 0.0;
-  var[q] = (have_data ? res[2 * q + 1] : sf2) * s_q * s_q;
+  mean[q] = 0.0;
+  var[q] = var0;
 }
 
 // L grew by row r (its leading rows unchanged): row r of L^-1 is
@@ -483,47 +476,191 @@ __global__ __launch_bounds__(256) void k_gp_inv_append_row(int r, int ld, const 
   if (lane == 0) Li[r + size_t(j) * ld] = -t * inv_d;
 }
 
-// One query per workgroup: k* in LDS (dynamic, n doubles), mean = k* . alpha,
-// variance = sigma_f^2 - |L^-1 k*|^2, both by block reduction.
-__global__ __launch_bounds__(256) void k_gp_predict(int n, int ld, const double* __restrict__ X,
-                                                    const double* __restrict__ Xq, const double* __restrict__ Li,
-                                                    const double* __restrict__ alpha, KParams P,
-                                                    double* __restrict__ out) {
+// Query q of an m x d row-major array, padded to GP_MAXD inputs.
+struct Query {
+  double x[GP_MAXD];
+  __device__ Query(const double* Xq, int d, int q) {
+#pragma unroll
+    for (int k = 0; k < GP_MAXD; ++k) x[k] = k < d ? Xq[size_t(q) * d + k] : 0.0;
+  }
+};
+
+// One query per workgroup of 256 x PARTS threads: k* in LDS (dynamic, n
+// doubles), mean = k* . alpha, variance = sigma_f^2 - |L^-1 k*|^2 by block
+// reduction, in output units.  Thread (i, part) sums every PARTS-th column of
+// row i.  For few queries of a small database: what bounds it is the chain of
+// dependent loads of a row, so rows are split (256 points, 200 queries: 21 us
+// with one thread a row, 11 with four).
+template <int PARTS>
+__global__ __launch_bounds__(256 * PARTS) void k_gp_predict(int n, int ld, const double* __restrict__ X,
+                                                            const double* __restrict__ Xq,
+                                                            const double* __restrict__ Li,
+                                                            const double* __restrict__ alpha, KParams P, double s_q,
+                                                            double* __restrict__ mean, double* __restrict__ var) {
   extern __shared__ double ks[];
-  __shared__ double red[2][256];
-  const int q = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  __shared__ double rows[PARTS][256];
+  __shared__ double red[2][4];
+  const int q = blockIdx.x, tid = threadIdx.x, nt = 256 * PARTS, row = tid & 255, part = tid >> 8;
+  const Query x(Xq, P.d, q);
   double sm = 0.0, sv = 0.0;
   for (int i = tid; i < n; i += nt) {
-    const double k = sqexp(X + GP_MAXD * i, Xq + GP_MAXD * q, P);
+    const double k = sqexp(X + GP_MAXD * i, x.x, P);
     ks[i] = k;
-    sm += k * alpha[i];
   }
   __syncthreads();
-  for (int i = tid; i < n; i += nt) {  // row i of L^-1 k*: column-major reads are coalesced over i
-    double w0 = 0.0, w1 = 0.0;
-    int j = 0;
-    for (; j + 1 <= i; j += 2) {
-      w0 += Li[i + size_t(j) * ld] * ks[j];
-      w1 += Li[i + size_t(j + 1) * ld] * ks[j + 1];
+  for (int i0 = 0; i0 < n; i0 += 256) {
+    const int i = i0 + row;
+    double w = 0.0;
+    if (i < n) {
+      if (part == 0) sm += ks[i] * alpha[i];
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+      const double* col = Li + i;
+      int j = part;
+      for (; j + 3 * PARTS <= i; j += 4 * PARTS) {  // column-major reads are coalesced over i
+        a0 += col[size_t(j) * ld] * ks[j];
+        a1 += col[size_t(j + PARTS) * ld] * ks[j + PARTS];
+        a2 += col[size_t(j + 2 * PARTS) * ld] * ks[j + 2 * PARTS];
+        a3 += col[size_t(j + 3 * PARTS) * ld] * ks[j + 3 * PARTS];
+      }
+      for (; j <= i; j += PARTS) a0 += col[size_t(j) * ld] * ks[j];
+      w = (a0 + a1) + (a2 + a3);
     }
-    if (j == i) w0 += Li[i + size_t(j) * ld] * ks[j];
-    const double w = w0 + w1;
-    sv += w * w;
-  }
-  red[0][tid] = sm;
-  red[1][tid] = sv;
-  __syncthreads();
-  for (int o = nt / 2; o > 0; o >>= 1) {
-    if (tid < o) {
-      red[0][tid] += red[0][tid + o];
-      red[1][tid] += red[1][tid + o];
+    rows[part][row] = w;
+    __syncthreads();
+    if (part == 0) {
+#pragma unroll
+      for (int p = 1; p < PARTS; ++p) w += rows[p][row];
+      sv += w * w;
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    out[2 * q] = red[0][0];
-    out[2 * q + 1] = P.sf2 - red[1][0];
+  if (part == 0) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      sm += __shfl_xor(sm, o);
+      sv += __shfl_xor(sv, o);
+    }
+    if ((tid & 63) == 0) {
+      red[0][tid >> 6] = sm;
+      red[1][tid >> 6] = sv;
+    }
   }
+  __syncthreads();
+  if (tid == 0) {
+    mean[q] = ((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])) * s_q;
+    var[q] = (P.sf2 - ((red[1][0] + red[1][1]) + (red[1][2] + red[1][3]))) * s_q * s_q;
+  }
+}
+
+// 32 queries and 64 RB rows per workgroup: V = L^-1 K* on the FP64 matrix
+// cores, k* formed 128 points at a time in LDS, L^-1 read as the operand (16
+// rows of 4 columns a load); part[g m + q] receives the sum of V^2 over row
+// group g, mean[q] (the last group, which passes every point) k* . alpha.
+// A wavefront takes every fourth block of 16 rows, so that the triangle's
+// work is shared evenly.  What bounds it is the matrix rate and the
+// exponentials of k*, one per 256 rows and query: 20,000 queries of 1000
+// points take 0.55 ms (36 TFLOP/s, half of what a large FP64 product
+// reaches), 5.3 ms with a workgroup per query; 200 queries of 3001 points
+// 0.34 ms, 2.8 before.
+constexpr int PQ = 32, PK = 128, PQ_PITCH = 40;  // pitch: the four columns of an operand on different banks
+
+template <int RB>
+__global__ __launch_bounds__(256) void k_gp_predict_tiles(int n, int ld, const double* __restrict__ X, int m,
+                                                          const double* __restrict__ Xq,
+                                                          const double* __restrict__ Li,
+                                                          const double* __restrict__ alpha, KParams P, double s_q,
+                                                          double* __restrict__ part, double* __restrict__ mean) {
+  __shared__ double ks[PK * PQ_PITCH];
+  __shared__ double red[8][PQ];
+  const int g = int(gridDim.y) - 1 - int(blockIdx.y);  // the longest rows first
+  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, lr = l & 15, lk = l >> 4;
+  const int qi = tid & (PQ - 1), kk = tid / PQ, q = blockIdx.x * PQ + qi;
+  const bool tail = g == int(gridDim.y) - 1;
+  const Query x(Xq, P.d, min(q, m - 1));
+  const int row_g = g * 64 * RB + 16 * w;  // row block rb of this wavefront: row_g + 64 rb
+  const int kend = min(n, (g + 1) * 64 * RB);
+  f64x4 acc[RB][2];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double sm = 0.0;
+  for (int kc = 0; kc < kend; kc += PK) {
+    __syncthreads();
+    for (int i = kk; i < PK; i += 8) {
+      const int k = kc + i;
+      double v = 0.0;
+      if (k < kend) {
+        v = sqexp(X + GP_MAXD * k, x.x, P);
+        if (tail) sm += v * alpha[k];
+      }
+      ks[i * PQ_PITCH + qi] = v;
+    }
+    __syncthreads();
+    const int kn = min(PK, kend - kc);
+    for (int kb = 0; kb < kn; kb += 16) {
+      const int k0 = kc + kb;
+      double a[RB][4], b[4][2];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const int r0 = row_g + 64 * rb, r = r0 + lr;
+        if (k0 > r0 || r0 >= n) continue;  // uniform
+        const double* const src = Li + r + size_t(k0 + lk) * ld;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[rb][u] = src[size_t(4 * u) * ld];
+        if (k0 == r0 || r0 + 16 > n) {  // the diagonal, and rows past the last
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a[rb][u] = k0 + lk + 4 * u <= r && r < n ? a[rb][u] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        b[u][0] = ks[(kb + 4 * u + lk) * PQ_PITCH + lr];
+        b[u][1] = ks[(kb + 4 * u + lk) * PQ_PITCH + 16 + lr];
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const int r0 = row_g + 64 * rb;
+        if (k0 > r0 || r0 >= n) continue;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          acc[rb][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][u], b[u][0], acc[rb][0], 0, 0, 0);
+          acc[rb][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][u], b[u][1], acc[rb][1], 0, 0, 0);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    double s = 0.0;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) s += acc[rb][c][t] * acc[rb][c][t];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (lk == 0) red[w][16 * c + lr] = s;
+  }
+  __syncthreads();
+  if (tid < PQ && q < m) part[size_t(g) * m + q] = (red[0][qi] + red[1][qi]) + (red[2][qi] + red[3][qi]);
+  if (!tail) return;  // uniform
+  __syncthreads();
+  red[kk][qi] = sm;
+  __syncthreads();
+  if (tid < PQ && q < m) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += red[k][qi];
+    mean[q] = s * s_q;
+  }
+}
+
+// Variances from the row groups' sums.
+__global__ __launch_bounds__(256) void k_gp_predict_sum(int m, int groups, const double* __restrict__ part, double sf2,
+                                                        double s_q, double* __restrict__ var) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= m) return;
+  double s = 0.0;
+  for (int g = 0; g < groups; ++g) s += part[size_t(g) * m + q];
+  var[q] = (sf2 - s) * s_q * s_q;
 }
 
 // out[0] = y^T alpha, out[1] = sum log L_ii.
@@ -960,6 +1097,45 @@ int refit(hmd_gp* g, bool upload = true) {
   return HMD_OK;
 }
 
+// Queues the predictions at m device queries (row-major, d columns).  Few
+// queries of a small database: a workgroup each, the shortest chain (its work
+// grows as m n^2, 11 us at 200 x 256, where the tiles' chain of barriers and
+// exponentials alone is about 20 us).  Else the matrix cores, in row groups of
+// 256 where that fills the chip, of 64 where it does not.
+int enqueue_predict(hmd_gp* g, int m, const double* dXq, double* dmean, double* dvar, hipStream_t s) {
+  hmd_ctx* ctx = g->ctx;
+  const int n = g->n;
+  const KParams P = kparams(g);
+  if (n <= 512 && m <= 512) {
+    hipLaunchKernelGGL(k_gp_predict<4>, dim3(m), dim3(1024), sizeof(double) * size_t(n), s, n, g->ld, g->dX, dXq,
+                       g->dLi, g->dalpha, P, g->s_q, dmean, dvar);
+    HMD_HIP(ctx, hipGetLastError());
+    return HMD_OK;
+  }
+  const int qb = (m + PQ - 1) / PQ;
+  const bool wide = int64_t(qb) * ((n + 255) / 256) >= 512;
+  const int rows = wide ? 256 : 64, groups = (n + rows - 1) / rows;
+  const size_t need = size_t(groups) * size_t(m);
+  if (need > g->part_cap) {
+    HMD_HIP(ctx, hipStreamSynchronize(s));  // the old scratch may still be read
+    if (g->dpart) (void)hipFree(g->dpart);
+    g->dpart = nullptr;
+    g->part_cap = 0;
+    HMD_HIP(ctx, hipMalloc(&g->dpart, sizeof(double) * need));
+    g->part_cap = need;
+  }
+  if (wide)
+    hipLaunchKernelGGL(k_gp_predict_tiles<4>, dim3(qb, groups), dim3(256), 0, s, n, g->ld, g->dX, m, dXq, g->dLi,
+                       g->dalpha, P, g->s_q, g->dpart, dmean);
+  else
+    hipLaunchKernelGGL(k_gp_predict_tiles<1>, dim3(qb, groups), dim3(256), 0, s, n, g->ld, g->dX, m, dXq, g->dLi,
+                       g->dalpha, P, g->s_q, g->dpart, dmean);
+  hipLaunchKernelGGL(k_gp_predict_sum, dim3((m + 255) / 256), dim3(256), 0, s, m, groups, g->dpart, P.sf2, g->s_q,
+                     dvar);
+  HMD_HIP(ctx, hipGetLastError());
+  return HMD_OK;
+}
+
 }  // namespace
 }  // namespace hmd
 
@@ -1080,28 +1256,24 @@ int gp_predict(hmd_gp* g, const double* Xs, int m, double* mean, double* var) {
     return HMD_OK;
   }
   HMD_HIP(ctx, hipSetDevice(ctx->device));
-  const size_t need_q = size_t(GP_MAXD) * m;
-  if (need_q + 2 * size_t(m) > g->q_cap) {
+  // queries, means and variances
+  const size_t nq = size_t(g->d) * m, need = nq + 2 * size_t(m);
+  if (need > g->q_cap) {
     if (g->dq) (void)hipFree(g->dq);
-    g->q_cap = 2 * (need_q + 2 * size_t(m));
-    HMD_HIP(ctx, hipMalloc(&g->dq, sizeof(double) * g->q_cap));
+    g->dq = nullptr;
+    g->q_cap = 0;
+    HMD_HIP(ctx, hipMalloc(&g->dq, sizeof(double) * 2 * need));
+    g->q_cap = 2 * need;
   }
-  double* dXq = g->dq;
-  double* dres = g->dq + need_q;
-  std::vector<double> xs(need_q, 0.0), res(2 * size_t(m));
-  for (int q = 0; q < m; ++q)
-    for (int k = 0; k < g->d; ++k) xs[size_t(q) * GP_MAXD + k] = Xs[size_t(q) * g->d + k];
+  double* const dres = g->dq + nq;
+  std::vector<double> res(2 * size_t(m));
   hipStream_t s = ctx->stream;
-  HMD_HIP(ctx, hipMemcpyAsync(dXq, xs.data(), 8 * xs.size(), hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->ld, g->dX, dXq,
-                     g->dLi, g->dalpha, kparams(g), dres);
-  HMD_HIP(ctx, hipGetLastError());
+  HMD_HIP(ctx, hipMemcpyAsync(g->dq, Xs, 8 * nq, hipMemcpyHostToDevice, s));
+  HMD_TRY(enqueue_predict(g, m, g->dq, dres, dres + m, s));
   HMD_HIP(ctx, hipMemcpyAsync(res.data(), dres, 8 * res.size(), hipMemcpyDeviceToHost, s));
   HMD_HIP(ctx, hipStreamSynchronize(s));
-  for (int q = 0; q < m; ++q) {
-    mean[q] = res[2 * q] * g->s_q;
-    var[q] = res[2 * q + 1] * g->s_q * g->s_q;
-  }
+  std::copy(res.begin(), res.begin() + m, mean);
+  std::copy(res.begin() + m, res.end(), var);
   return HMD_OK;
 }
 
@@ -1111,25 +1283,9 @@ int gp_predict_dev(hmd_gp* g, const double* dXs, int m, double* dmean, double* d
   if (m == 0) return HMD_OK;
   HMD_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t s = stream ? static_cast<hipStream_t>(stream) : ctx->stream;
+  if (g->n > 0) return enqueue_predict(g, m, dXs, dmean, dvar, s);
   const double sf2 = g->hyp.sigma_f * g->hyp.sigma_f;
-  const size_t need_q = size_t(GP_MAXD) * m;
-  if (need_q + 2 * size_t(m) > g->q_cap) {
-    HMD_HIP(ctx, hipStreamSynchronize(s));  // the old scratch may still be read
-    if (g->dq) (void)hipFree(g->dq);
-    g->q_cap = 2 * (need_q + 2 * size_t(m));
-    HMD_HIP(ctx, hipMalloc(&g->dq, sizeof(double) * g->q_cap));
-  }
-  double* dXq = g->dq;
-  double* dres = g->dq + need_q;
-  hipLaunchKernelGGL(k_gp_pack, dim3((m + 255) / 256), dim3(256), 0, s, m, g->d, dXs, dXq);
-  HMD_HIP(ctx, hipGetLastError());
-  if (g->n > 0) {
-    hipLaunchKernelGGL(k_gp_predict, dim3(m), dim3(256), sizeof(double) * size_t(g->n), s, g->n, g->ld, g->dX,
-                       dXq, g->dLi, g->dalpha, kparams(g), dres);
-    HMD_HIP(ctx, hipGetLastError());
-  }
-  hipLaunchKernelGGL(k_gp_unpack, dim3((m + 255) / 256), dim3(256), 0, s, m, g->n > 0 ? 1 : 0, dres, g->s_q, sf2,
-                     dmean, dvar);
+  hipLaunchKernelGGL(k_gp_prior, dim3((m + 255) / 256), dim3(256), 0, s, m, sf2 * g->s_q * g->s_q, dmean, dvar);
   HMD_HIP(ctx, hipGetLastError());
   return HMD_OK;
 }
@@ -1339,7 +1495,7 @@ int gp_scales(const hmd_gp* g, double* scale, double* s_q, double* sigma_n) {
 
 void gp_free(hmd_gp* g) {
   if (!g) return;
-  for (void* p : {(void*)g->slab, (void*)g->dq, (void*)g->dout, (void*)g->dinfo})
+  for (void* p : {(void*)g->slab, (void*)g->dq, (void*)g->dpart, (void*)g->dout, (void*)g->dinfo})
     if (p) (void)hipFree(p);
   delete g;
 }

@@ -68,6 +68,19 @@ def test_tile_edges_fit_and_evidence(ctx, n):
         assert evidence(a * h["sigma_f"], b * h["ell"]) <= best + 1e-9 * abs(best)
 
 
+@pytest.mark.parametrize("n,m", [(512, 512), (40, 513), (513, 1), (600, 33), (1030, 100), (300, 20000)])
+def test_predict_kernels_match_oracle(ctx, n, m):
+    # both sides of the rule between a workgroup per query and the matrix
+    # cores, and of the row groups' size; odd queries and rows (bars of
+    # test_fit_predict_matches_oracle)
+    X, y, se = data(n, 40 + n)
+    g, o = B.GP(ctx, X, y, se, B.gp_hyper(ranges=RANGES)), OGP(X, y, se, Hyper(ranges=RANGES))
+    Xs, _, _ = data(m, 70 + m)
+    (mg, vg), (mo, vo) = g.predict(Xs), o.predict(Xs)
+    assert np.abs(mg - mo).max() <= 1e-9 * np.abs(mo).max() + 1e-12
+    assert np.abs(vg - vo).max() <= 1e-9 * o.s_q ** 2
+
+
 def test_append_matches_oracle_refit(ctx):
     X, y, se = data(40, 7)
     g = B.GP(ctx, X[:30], y[:30], se[:30], B.gp_hyper(ranges=RANGES))
