@@ -1313,7 +1313,7 @@ int gp_log_marginal(hmd_gp* g, double* lml) {
 // parameter, a quarter decade apart over two decades either side of the
 // start, then refines from the best grid point by cyclic line searches over
 // the logarithm of each chosen parameter, bracketed by a factor 10 around the
-// current value, until a cycle gains less than 1e-12 relative (at most 30
+// current value, until two cycles gain less than 1e-12 relative (at most 30
 // cycles).
 //
 // Refits are independent of each other, so a whole grid, or a round of up to
@@ -1437,7 +1437,8 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
   HMD_HIP(ctx, hipMemcpyAsync(st_dev, &st, sizeof(st), hipMemcpyHostToDevice, s));
   const double width = std::log(10.0);
   const int rounds = int(std::ceil(std::log(2.0 * width / 1e-9) / std::log(0.5 * double(nb + 1))));
-  for (int cycle = 0; cycle < 30; ++cycle) {
+  int settled = 0;  // cycles in a row without gain: two, since the last gains move along a flat ridge
+  for (int cycle = 0; cycle < 30 && settled < 2; ++cycle) {
     const double start = st.best;
     for (int j = 0; j < (m > 1 ? m + 1 : m); ++j) {
       const int axis = j < m ? idx[j] : 3;
@@ -1448,7 +1449,7 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
     HMD_HIP(ctx, hipGetLastError());
     HMD_HIP(ctx, hipMemcpyAsync(&st, st_dev + flip, sizeof(st), hipMemcpyDeviceToHost, s));
     HMD_HIP(ctx, hipStreamSynchronize(s));
-    if (!(std::fabs(st.best - start) > 1e-12 * std::fabs(st.best))) break;
+    settled = std::fabs(st.best - start) > 1e-12 * std::fabs(st.best) ? 0 : settled + 1;
   }
   if (mask & 1) g->hyp.sigma_f = std::exp(st.x[0]);
   if (mask & 2) g->hyp.ell = std::exp(st.x[1]);
