@@ -13,6 +13,7 @@
 // by `scale` (the MD series holds sums of B steps; scale = 1/B).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -25,104 +26,191 @@ namespace {
 
 constexpr int SER_TPB = 256;
 
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  // 256 threads: four wavefronts
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[w] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
-}
+// Estimator state of a row between batches of lags, in lags 1-3 of its
+// autocovariances (consumed by then; gamma_0 is still needed).
+constexpr int kTotal = 1, kSmallest = 2, kDone = 3;
 
 }  // namespace
 
 // out[s*4 + 0] = mean, [2] = mean of the first n/2 samples, [3] = mean of
-// the rest; [1] (the standard error) is left to the estimator kernels.
-__global__ __launch_bounds__(SER_TPB) void k_series_moments(const double* __restrict__ x, int64_t ld, int64_t n,
-                                                           double scale, double* __restrict__ out) {
-  __shared__ double red[4];
-  const int s = blockIdx.x;
+// the rest; [1] (the standard error) is left to the estimator kernels.  A
+// row is read by 16 wavefronts, four loads in flight each: latency bounds it
+// (64 rows of 20,000: 23 us with four wavefronts, one load at a time).
+constexpr int MOM_TPB = 1024;
+
+__global__ __launch_bounds__(MOM_TPB) void k_series_moments(const double* __restrict__ x, int64_t ld, int64_t n,
+                                                            double scale, double* __restrict__ out) {
+  __shared__ double red[2][MOM_TPB / 64];
+  const int s = blockIdx.x, tid = threadIdx.x;
   const double* row = x + int64_t(s) * ld;
   const int64_t half = n / 2;
-  double a = 0.0, b = 0.0;
-  for (int64_t i = threadIdx.x; i < half; i += SER_TPB) a += row[i] * scale;
-  for (int64_t i = half + threadIdx.x; i < n; i += SER_TPB) b += row[i] * scale;
-  a = block_sum(a, red);
-  b = block_sum(b, red);
-  if (threadIdx.x == 0) {
-    out[4 * s + 0] = (a + b) / double(n);
-    out[4 * s + 2] = a / double(half);
-    out[4 * s + 3] = b / double(n - half);
+  double sum[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int64_t end = h ? n : half;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int64_t i = (h ? half : 0) + tid;
+    for (; i + 3 * MOM_TPB < end; i += 4 * MOM_TPB) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[u] += row[i + u * MOM_TPB] * scale;
+    }
+    for (; i < end; i += MOM_TPB) a[0] += row[i] * scale;
+    double v = (a[0] + a[1]) + (a[2] + a[3]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((tid & 63) == 0) red[h][tid >> 6] = v;
+  }
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      sum[h] = 0.0;
+      for (int w = 0; w < MOM_TPB / 64; ++w) sum[h] += red[h][w];
+    }
+    out[4 * s + 0] = (sum[0] + sum[1]) / double(n);
+    out[4 * s + 2] = sum[0] / double(half);
+    out[4 * s + 3] = sum[1] / double(n - half);
   }
 }
 
-// gamma_t = (1/n) sum_{i < n-t} d_i d_{i+t}, d = scale x - mean, for the
-// 256 lags t0 .. t0+255 of this workgroup (grid: lag tiles x rows).  Each
-// lag sums its products in ascending i; out-of-range terms are exact zeros.
+// gamma_t = (1/n) sum_{i < n-t} d_i d_{i+t}, d = scale x - mean, on the FP64
+// matrix cores.  With the series cut into pieces of 16 samples, X[m][r] =
+// d_{16 m + r}, the products G_s = sum_m X[m][.]^T X[m + s][.] hold every lag:
+// gamma_{16 s + u} n is the sum over r of G_s[r][r + u] (r + u < 16) and of
+// G_{s+1}[r][r + u - 16].  Both operands of a 16 x 16 x 4 step are 64
+// consecutive samples, read from LDS without conflict, and one read feeds
+// 1024 products (a loop over lags made 64 of one, and the LDS bounded it at 13
+// TFLOP/s).  64 rows of 20,000 samples correlated over 1000: 2.09 ms before,
+// 0.24 ms with the batches below; what bounds a batch now is the matrix rate
+// (2,432 lags of 64 rows in 0.13 ms, 48 TFLOP/s).
+//
+// A workgroup takes 4 NS shifts s, NS per wavefront, of one row: the lags
+// 16 s0 .. 16 (s0 + 4 NS - 1) - 1, (the last shift only completes them).  NS =
+// 5 wastes a twentieth of the products; 2 wastes an eighth and gives more
+// workgroups where rows and lags are few.
+//
+// Rows that the estimator has finished with (see k_series_geyer) are skipped.
+constexpr int AC_CH = 1024;  // samples per pass
+
+template <int NS>
 __global__ __launch_bounds__(SER_TPB) void k_series_acov(const double* __restrict__ x, int64_t ld, int64_t n,
                                                         double scale, const double* __restrict__ mom,
-                                                        double* __restrict__ gam, int64_t gld) {
-  __shared__ double a[SER_TPB], b[2 * SER_TPB];
-  const int s = blockIdx.y;
+                                                        double* __restrict__ gam, int64_t gld, int tile0) {
+  using f64x4 = __attribute__((ext_vector_type(4))) double;
+  constexpr int SH = 4 * NS, LAGS = 16 * (SH - 1);
+  __shared__ double a[AC_CH], b[AC_CH + 16 * SH];
+  __shared__ double lag[16 * SH];
+  const int s = blockIdx.y, tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  double* const g = gam + int64_t(s) * gld;
+  if (tile0 > 0 && g[kDone] != 0.0) return;
+  const int64_t t0 = int64_t(tile0 + blockIdx.x) * LAGS;
   const double* row = x + int64_t(s) * ld;
-  const int64_t t0 = int64_t(blockIdx.x) * SER_TPB;
-  const int tid = threadIdx.x;
   const double mean = mom[4 * s];
-  double acc = 0.0;
-  for (int64_t i0 = 0; i0 < n - t0; i0 += SER_TPB) {
-    const int64_t ia = i0 + tid, ib = i0 + t0 + tid;
-    a[tid] = ia < n ? row[ia] * scale - mean : 0.0;
-    b[tid] = ib < n ? row[ib] * scale - mean : 0.0;
-    b[tid + SER_TPB] = ib + SER_TPB < n ? row[ib + SER_TPB] * scale - mean : 0.0;
+  f64x4 acc[NS];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) acc[k] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int64_t i0 = 0; i0 + t0 < n; i0 += AC_CH) {
     __syncthreads();
-#pragma unroll 8
-    for (int j = 0; j < SER_TPB; ++j) acc += a[j] * b[j + tid];
+#pragma unroll
+    for (int e = tid; e < AC_CH; e += SER_TPB) a[e] = i0 + e < n ? row[i0 + e] * scale - mean : 0.0;
+#pragma unroll
+    for (int e = tid; e < AC_CH + 16 * SH; e += SER_TPB) {
+      const int64_t i = i0 + t0 + e;
+      b[e] = i < n ? row[i] * scale - mean : 0.0;
+    }
+    __syncthreads();
+    for (int c = 0; c < AC_CH; c += 64) {
+      const double av = a[c + l];
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+        acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b[c + 16 * (w * NS + k) + l], acc[k], 0, 0, 0);
+    }
+  }
+  // lane l, element t holds G_s[4 t + l / 16][l % 16]: lag 16 s + r' - r
+  for (int e = tid; e < 16 * SH; e += SER_TPB) lag[e] = 0.0;
+  __syncthreads();
+#pragma unroll 1
+  for (int k = 0; k < SH; ++k) {  // shifts in turn: a fixed order of the sums
+    if (w == k / NS) {
+      double* const st = w & 1 ? b : a;  // 256 values of one shift (the samples are done with)
+#pragma unroll
+      for (int q = 0; q < NS; ++q)
+        if (q == k % NS)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) st[(4 * t + (l >> 4)) * 16 + (l & 15)] = acc[q][t];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (l < 31) {  // lag 16 k + l - 15
+        const int u = l - 15, lo = u < 0 ? -u : 0, hi = u < 0 ? 16 : 16 - u;
+        double v = 0.0;
+        for (int r = lo; r < hi; ++r) v += st[r * 16 + r + u];
+        const int t = 16 * k + u;
+        if (t >= 0) lag[t] += v;
+      }
+    }
     __syncthreads();
   }
-  const int64_t t = t0 + tid;
-  if (t < n) gam[int64_t(s) * gld + t] = acc / double(n);
+  for (int e = tid; e < LAGS; e += SER_TPB)
+    if (t0 + e < n) g[t0 + e] = lag[e] / double(n);
 }
 
 // Geyer's initial monotone sequence: Gamma_k = gamma_2k + gamma_2k+1 while
 // positive, each replaced by the smallest so far; sigma^2 = -gamma_0 +
 // 2 sum Gamma_k; SE = sqrt(sigma^2 / n).  An empty sequence, or a sigma^2
-// that is not positive, falls back to the iid value gamma_0.  One thread per
-// row; pairs are read 16 at a time ahead of the sequential scan.
-__global__ __launch_bounds__(64) void k_series_geyer(const double* __restrict__ gam, int64_t gld, int64_t n,
-                                                     int S, double* __restrict__ out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S) return;
-  const double* g = gam + int64_t(s) * gld;
-  constexpr int CH = 16;
-  const int64_t kmax = n / 2;  // pairs (2k, 2k+1) with 2k+1 < n
+// that is not positive, falls back to the iid value gamma_0.  One wavefront
+// per row, 64 pairs at a time (prefix minimum and sum across the lanes; one
+// thread a row took 390 us over 20,000 samples).
+//
+// The lags come in batches (k0 .. k1 pairs); a row whose sequence ends in one
+// is finished, and later batches of autocovariances skip it: the sequence of
+// a flux ends after a few correlation times, and the lags past it are never
+// formed.  Between batches the state stays in the row's own consumed lags.
+__global__ __launch_bounds__(64) void k_series_geyer(double* __restrict__ gam, int64_t gld, int64_t n, int64_t k0,
+                                                     int64_t k1, int last, double* __restrict__ out) {
+  const int s = blockIdx.x, l = threadIdx.x;
+  double* const g = gam + int64_t(s) * gld;
+  if (k0 > 0 && g[kDone] != 0.0) return;
   double total = 0.0, smallest = INFINITY;
-  int64_t used = 0;
-  bool stop = false;
-  for (int64_t k0 = 0; k0 < kmax && !stop; k0 += CH) {
-    double p[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int64_t k = k0 + c;
-      p[c] = k < kmax ? g[2 * k] + g[2 * k + 1] : 0.0;
-    }
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      if (!stop) {
-        if (k0 + c < kmax && p[c] > 0.0) {
-          smallest = fmin(smallest, p[c]);
-          total += smallest;
-          ++used;
-        } else {
-          stop = true;
-        }
-      }
-    }
+  if (k0 > 0) {
+    total = g[kTotal];
+    smallest = g[kSmallest];
   }
-  double var = used > 0 ? -g[0] + 2.0 * total : g[0];
-  if (!(var > 0.0)) var = g[0];
-  out[4 * s + 1] = sqrt(var / double(n));
+  bool stop = false;
+  int64_t used = k0;
+  auto pair = [&](int64_t k) { return k + l < k1 ? g[2 * (k + l)] + g[2 * (k + l) + 1] : -1.0; };
+  double next = pair(k0);
+  for (int64_t k = k0; k < k1 && !stop; k += 64) {
+    const double p = next;
+    next = pair(k + 64);
+    const unsigned long long ends = __ballot(!(p > 0.0));
+    const int c = ends ? __builtin_ctzll(ends) : 64;  // pairs of the sequence in this run
+    double m = l < c ? fmin(p, smallest) : INFINITY;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double v = __shfl_up(m, o);
+      if (l >= o) m = fmin(m, v);
+    }
+    double v = l < c ? m : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    total += v;
+    if (c > 0) smallest = __shfl(m, c - 1);
+    used += c;
+    stop = c < 64 && k + c < k1;
+  }
+  if (l != 0) return;
+  const double g0 = g[0];
+  if (stop || last) {
+    double var = used > 0 ? -g0 + 2.0 * total : g0;
+    if (!(var > 0.0)) var = g0;
+    out[4 * s + 1] = sqrt(var / double(n));
+  }
+  if (!last) {
+    g[kTotal] = total;
+    g[kSmallest] = smallest;
+    g[kDone] = stop ? 1.0 : 0.0;
+  }
 }
 
 // Block rule: nb contiguous blocks of floor(n / nb) samples (the remainder
@@ -169,14 +257,28 @@ int series_stats_check(int S, int64_t n, int64_t ld, int n_blocks, std::string& 
 
 void series_stats_enqueue(hipStream_t st, const double* d_x, int S, int64_t n, int64_t ld, double scale,
                           int n_blocks, double* d_gam, double* d_out) {
-  hipLaunchKernelGGL(k_series_moments, dim3(S), dim3(SER_TPB), 0, st, d_x, ld, n, scale, d_out);
+  hipLaunchKernelGGL(k_series_moments, dim3(S), dim3(MOM_TPB), 0, st, d_x, ld, n, scale, d_out);
   if (n_blocks >= 2) {
     hipLaunchKernelGGL(k_series_blocks, dim3(S), dim3(SER_TPB), 0, st, d_x, ld, n, scale, n_blocks, d_out);
     return;
   }
-  const unsigned lag_tiles = unsigned((n + SER_TPB - 1) / SER_TPB);
-  hipLaunchKernelGGL(k_series_acov, dim3(lag_tiles, S), dim3(SER_TPB), 0, st, d_x, ld, n, scale, d_out, d_gam, n);
-  hipLaunchKernelGGL(k_series_geyer, dim3((S + 63) / 64), dim3(64), 0, st, d_gam, n, n, S, d_out);
+  // Batches of lag tiles: enough workgroups to fill the chip, then twice as
+  // many lags each time.  Where rows are few one batch holds every lag.
+  const int64_t wide = 16 * (4 * 5 - 1), narrow = 16 * (4 * 2 - 1);
+  const bool big = int64_t(S) * ((n + wide - 1) / wide) >= 512;
+  const int64_t lags = big ? wide : narrow, tiles = (n + lags - 1) / lags, pairs = n / 2;
+  int64_t step = std::max<int64_t>(2, (512 + S - 1) / S);
+  for (int64_t t = 0; t < tiles; t += step, step = t) {
+    const int64_t c = std::min(step, tiles - t);
+    const dim3 grid{unsigned(c), unsigned(S), 1};
+    if (big)
+      hipLaunchKernelGGL(k_series_acov<5>, grid, dim3(SER_TPB), 0, st, d_x, ld, n, scale, d_out, d_gam, n, int(t));
+    else
+      hipLaunchKernelGGL(k_series_acov<2>, grid, dim3(SER_TPB), 0, st, d_x, ld, n, scale, d_out, d_gam, n, int(t));
+    const bool last = t + c == tiles;
+    hipLaunchKernelGGL(k_series_geyer, dim3(S), dim3(64), 0, st, d_gam, n, n, t * lags / 2,
+                       last ? pairs : (t + c) * lags / 2, last ? 1 : 0, d_out);
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -32,6 +32,22 @@ def _ar1(seed, phi, n):
     return 0.3 + 0.01 * x
 
 
+@pytest.mark.parametrize("S,n,rho", [(1, 112, 0.9), (1, 113, 0.9), (3, 224, 0.999), (64, 5000, 0.9995),
+                                     (600, 304, 0.99), (600, 305, 0.99), (2, 6001, 0.9999)])
+def test_lag_tiles_and_batches_match_oracle(S, n, rho):
+    # around the lag tiles of both sizes (112, 304) and over several batches of
+    # lags (long correlations: rows end in different batches); FP64 sums of n
+    # products in another order: 1e-12 of gamma_0, which a variance that is a
+    # sum of like terms keeps to 1e-9
+    ctx = hmd.Context(hmd.Params(**SMALL_L))
+    rows = np.stack([_ar1(100 + k, rho * (0.5 + 0.5 * ((k % 7) / 6)), n) for k in range(S)])
+    out = B.series_stats(ctx, rows)
+    for k in range(S):
+        m, se = ostats.geyer(rows[k])
+        assert out[k, 0] == pytest.approx(m, rel=1e-12, abs=1e-14)
+        assert out[k, 1] == pytest.approx(se, rel=1e-9)
+
+
 @pytest.mark.parametrize("n", [2, 3, 257, 1000, 20000])
 def test_series_stats_match_oracle(n):
     # four rows (iid, short and long correlation, anti-correlated) in one call;
