@@ -2,16 +2,16 @@
 // paper's GP): members of 2 -> H -> H -> 1 tanh networks, FP32 weights and
 // accumulation, trained full-batch on the mean squared error with Adam.
 //
-// Training runs every iteration of every member in one launch: one workgroup
-// per member keeps its parameters in LDS, each thread owns a fixed slice of
-// the parameters (their gradient sums and Adam moments stay in registers),
-// and the batch streams through LDS in chunks of CHUNK samples (forward,
-// back-propagation, per-parameter gradient sums).
+// Up to 256 points a member trains in one workgroup that keeps parameters,
+// moments and activations on its compute unit for hundreds of iterations; larger
+// sets are shared out over workgroups, two launches per iteration.  Either way
+// the hidden layer's products run on the FP32 matrix cores.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "engine.h"
@@ -35,189 +35,498 @@ namespace hmd {
 namespace {
 
 constexpr int ENS_TPB = 256;
+constexpr int TRAIN_TPB = 512;
 constexpr int CHUNK = 32;
 constexpr int MAXH = 64;
+constexpr int MAX_SHARES = 32;  // shared-out training: workgroups per member
+constexpr int LOCAL_N = 256;    // points a member trains on within one workgroup (LDS: 2 x 256 x 68 floats)
+constexpr int LOCAL_ITERS = 500;  // iterations per launch of that path
 
-__host__ __device__ inline int nparams(int H) { return H * H + 5 * H + 1; }
+__host__ __device__ constexpr int nparams(int H) { return H * H + 5 * H + 1; }
 
-// Which tensor a flat parameter index belongs to, and its (row, col).
-struct Slot {
-  int kind, o, i;  // kind: 0 W1, 1 b1, 2 W2, 3 b2, 4 W3, 5 b3, -1 none
-};
+using f32x4 = __attribute__((ext_vector_type(4))) float;
 
-__device__ __forceinline__ Slot decode(int p, int H) {
-  Slot s{-1, 0, 0};
-  if (p < 2 * H) s = Slot{0, p / 2, p % 2};
-  else if (p < 3 * H) s = Slot{1, p - 2 * H, 0};
-  else if (p < 3 * H + H * H) s = Slot{2, (p - 3 * H) / H, (p - 3 * H) % H};
-  else if (p < 4 * H + H * H) s = Slot{3, p - 3 * H - H * H, 0};
-  else if (p < 5 * H + H * H) s = Slot{4, p - 4 * H - H * H, 0};
-  else if (p == 5 * H + H * H) s = Slot{5, 0, 0};
-  return s;
+// One Adam step (Kingma & Ba 2015, beta = (0.9, 0.999), eps = 1e-8).
+__device__ __forceinline__ void adam(float g, float c1, float c2, float lr, float& th, float& m, float& v) {
+  m = 0.9f * m + 0.1f * g;
+  v = 0.999f * v + 0.001f * g * g;
+  th -= lr * (m * c1) / (sqrtf(v * c2) + 1e-8f);
 }
 
-// Training is split over (chunk of CHUNK points, member) workgroups so that
-// every iteration runs on many CUs: k_ens_chunk computes one chunk's forward
-// and backward pass and its share of the gradient and loss (MSE over all N
-// points: the 2/N and 1/N factors are applied here; wts, when given, holds
-// each member's bootstrap count per point); k_ens_adam sums the shares of
-// each member and takes one Adam step.
-__global__ __launch_bounds__(ENS_TPB) void k_ens_chunk(int N, int H, const float* __restrict__ Xs,
-                                                       const float* __restrict__ ys,
-                                                       const float* __restrict__ wts,
-                                                       const float* __restrict__ params, float* __restrict__ gpart,
-                                                       float* __restrict__ lpart) {
-  extern __shared__ float lds[];
-  const int P = H * H + 5 * H + 1;
-  // activation rows are padded to H + 1 floats so that lanes walking
-  // different rows at the same column hit different LDS banks
-  const int HP = H + 1;
-  float* th = lds;                   // P
-  float* x = th + P;                 // CHUNK x 2
-  float* h1 = x + 2 * CHUNK;         // CHUNK x HP
-  float* h2 = h1 + CHUNK * HP;       // CHUNK x HP
-  float* dz2 = h2 + CHUNK * HP;      // CHUNK x HP
-  float* dz1 = dz2 + CHUNK * HP;     // CHUNK x HP
-  float* dout = dz1 + CHUNK * HP;    // CHUNK
-  float* red = dout + CHUNK;         // ENS_TPB
-  float* W1 = th;
-  float* b1 = W1 + 2 * H;
-  float* W2 = b1 + H;
-  float* b2 = W2 + H * H;
-  float* W3 = b2 + H;
-  float* b3 = W3 + H;
+// v + the value of lane ^ M within 16 lanes, M one of 1, 2, 7, 15 (which span all 16).
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+  constexpr int ctrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 7 ? 0x141 : 0x140;
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
+}
 
-  const int tid = threadIdx.x, member = blockIdx.y, chunk = blockIdx.x, nchunk = gridDim.x;
-  const float* my = params + size_t(member) * P;
-  for (int p = tid; p < P; p += ENS_TPB) th[p] = my[p];
-  const int c0 = chunk * CHUNK, nc = min(CHUNK, N - c0);
-  for (int e = tid; e < 2 * nc; e += ENS_TPB) x[e] = Xs[2 * c0 + e];
-  __syncthreads();
+// Sums of V values (4, 8 or 16) over 16 lanes: lane l receives the sum of
+// value l % V.  Halving the set at each exchange takes 15 adds where V separate
+// sums take 64.
+template <int V>
+__device__ __forceinline__ float sum_split(float (&v)[V], int l) {
+  if constexpr (V < 16) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] += lane_xor<15>(v[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ((l & 8) ? v[i + 8] : v[i]) + lane_xor<15>((l & 8) ? v[i] : v[i + 8]);
+  }
+  if constexpr (V < 8) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] += lane_xor<7>(v[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = ((l & 4) ? v[i + 4] : v[i]) + lane_xor<7>((l & 4) ? v[i] : v[i + 4]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) v[i] = ((l & 2) ? v[i + 2] : v[i]) + lane_xor<2>((l & 2) ? v[i] : v[i + 2]);
+  return ((l & 1) ? v[1] : v[0]) + lane_xor<1>((l & 1) ? v[0] : v[1]);
+}
+
+// Iterations t0 + 1 .. t0 + iters of one member (a workgroup) on N <= LOCAL_N
+// points; loss_out receives the loss at the parameters before the last step.
+// With grad_out set the gradient is left there instead of being stepped along.
+//
+// Shared out over the chip, an iteration costs two launches and a trip of the
+// gradient through memory (256 points, 64 units: 44 us on the VALU; fused into
+// one launch and on the matrix cores 27 us, 15 of them the other workgroups'
+// gradients arriving), far more than its arithmetic is worth on one compute
+// unit.  Here a wavefront runs 16 points through both layers and back in
+// registers: lane (point lane % 16, g = lane / 16) holds units 16 t + 4 g + u,
+// which is how the 16 x 16 x 4 instructions leave a product transposed and
+// also a layout they take the next operand in.  Only the hidden layer's
+// gradient needs points as the contracted index; its operands pass through
+// LDS, and the wavefront that forms one of its HT x HT tiles keeps that tile's
+// parameters and moments.  19.7 us per iteration at 256 points and 64 units,
+// bound by the matrix rate (10 us) and tanh of one compute unit; it falls with
+// the points and units.
+template <int HT>
+__global__ __launch_bounds__(1024) void k_ens_local(int N, int H, const float* __restrict__ Xs,
+                                                    const float* __restrict__ ys, const float* __restrict__ wts,
+                                                    float* __restrict__ params, float* __restrict__ mom,
+                                                    float* __restrict__ vel, int t0, int iters, float lr,
+                                                    float* __restrict__ loss_out, float* __restrict__ grad_out) {
+  constexpr int HP = 16 * HT, EP = HP + 4;  // row pitch: 16 rows' 4-float reads on different banks
+  constexpr int V = HT == 3 ? 16 : 4 * HT;
+  extern __shared__ float4 lds4[];
+  float* const W2 = reinterpret_cast<float*>(lds4);  // HP rows
+  float* const small = W2 + HP * EP;                 // W1 (x, y), b1, b2, W3: HP each; b3; two bias corrections
+  float* const ha = small + 5 * HP + 4;              // first-layer activations, a row per point
+  float* const da = ha + 16 * ((N + 15) / 16) * EP;  // second-layer residuals
+  float* const part = ha;                            // per wavefront: sums for the small tensors
+  constexpr int PART = 5 * HP + 4;
+  const int P = nparams(H);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = 4 * (lane >> 4);
+  const int member = blockIdx.x, nw = (N + 15) / 16;
+  const size_t base = size_t(member) * P;
   const float invN = 1.0f / float(N);
-  for (int e = tid; e < nc * H; e += ENS_TPB) {
-    const int s = e / H, o = e % H;
-    h1[s * HP + o] = tanhf(W1[2 * o] * x[2 * s] + W1[2 * o + 1] * x[2 * s + 1] + b1[o]);
+  // this thread's parameters: four of W2 (owner wavefronts) and one of the small tensors
+  const int to = wave / HT, ti = wave % HT;
+  const bool owner = wave < HT * HT;
+  float w_th[4], w_m[4], w_v[4], s_th = 0.f, s_m = 0.f, s_v = 0.f;
+  int w_at[4], s_at = -1;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int o = 16 * to + g4 + u, i = 16 * ti + l16;
+    w_at[u] = owner && o < H && i < H ? 3 * H + o * H + i : -1;
+    const bool on = w_at[u] >= 0;
+    w_th[u] = on ? params[base + w_at[u]] : 0.f;
+    w_m[u] = on && t0 > 0 ? mom[base + w_at[u]] : 0.f;
+    w_v[u] = on && t0 > 0 ? vel[base + w_at[u]] : 0.f;
+    if (owner) W2[o * EP + i] = w_th[u];
   }
-  __syncthreads();
-  // lanes run over points (same output unit): the W2 row is a broadcast and
-  // the padded activation rows spread over the banks
-  for (int e = tid; e < nc * H; e += ENS_TPB) {
-    const int s = e % nc, o = e / nc;
-    float a = b2[o];
-    const float* w = W2 + o * H;
-    const float* hh = h1 + s * HP;
-    for (int i = 0; i < H; ++i) a += w[i] * hh[i];
-    h2[s * HP + o] = tanhf(a);
-  }
-  __syncthreads();
-  float lsum = 0.f;
-  if (tid < nc) {
-    float a = b3[0];
-    const float* hh = h2 + tid * HP;
-    for (int o = 0; o < H; ++o) a += W3[o] * hh[o];
-    // bootstrap: the point's count in this member's resample weights its
-    // squared residual (the mean still over N)
-    const float w = wts ? wts[size_t(member) * N + c0 + tid] : 1.0f;
-    const float r = a - ys[c0 + tid];
-    lsum = w * r * r;
-    dout[tid] = 2.0f * w * r * invN;
-  }
-  __syncthreads();
-  for (int e = tid; e < nc * H; e += ENS_TPB) {
-    const int s = e / H, o = e % H;
-    const float t = h2[s * HP + o];
-    dz2[s * HP + o] = dout[s] * W3[o] * (1.0f - t * t);
-  }
-  __syncthreads();
-  for (int e = tid; e < nc * H; e += ENS_TPB) {
-    const int s = e / H, i = e % H;
-    float a = 0.f;
-    const float* dz = dz2 + s * HP;
-    for (int o = 0; o < H; ++o) a += dz[o] * W2[o * H + i];
-    const float t = h1[s * HP + i];
-    dz1[s * HP + i] = a * (1.0f - t * t);
-  }
-  __syncthreads();
-  float* gout = gpart + (size_t(member) * nchunk + chunk) * P;
-  for (int p = tid; p < P; p += ENS_TPB) {
-    const Slot q = decode(p, H);
-    float a = 0.f;
-    switch (q.kind) {
-      case 0: for (int s = 0; s < nc; ++s) a += dz1[s * HP + q.o] * x[2 * s + q.i]; break;
-      case 1: for (int s = 0; s < nc; ++s) a += dz1[s * HP + q.o]; break;
-      case 2: for (int s = 0; s < nc; ++s) a += dz2[s * HP + q.o] * h1[s * HP + q.i]; break;
-      case 3: for (int s = 0; s < nc; ++s) a += dz2[s * HP + q.o]; break;
-      case 4: for (int s = 0; s < nc; ++s) a += dout[s] * h2[s * HP + q.o]; break;
-      case 5: for (int s = 0; s < nc; ++s) a += dout[s]; break;
-      default: break;
+  if (tid <= 5 * HP) {
+    const int what = tid / HP, o = tid % HP;
+    if (what == 5) s_at = 5 * H + H * H;
+    else if (o < H) s_at = what < 2 ? 2 * o + what : what == 2 ? 2 * H + o : (what - 3) * H + 3 * H + H * H + o;
+    if (s_at >= 0) {
+      s_th = params[base + s_at];
+      if (t0 > 0) {
+        s_m = mom[base + s_at];
+        s_v = vel[base + s_at];
+      }
     }
-    gout[p] = a;
+    small[tid] = s_th;
   }
-  red[tid] = lsum;
+  // this lane's point
+  const int pt = 16 * wave + l16;
+  const bool active = wave < nw, on = pt < N;
+  const float x0 = on ? Xs[2 * pt] : 0.f, x1 = on ? Xs[2 * pt + 1] : 0.f, y = on ? ys[pt] : 0.f;
+  // bootstrap: the point's count in this member's resample weights its squared
+  // residual (the mean still over N)
+  const float wt = !on ? 0.f : wts ? wts[size_t(member) * N + pt] : 1.0f;
+  double p1 = 1.0, p2 = 1.0;  // beta^t
+  if (tid == 0) {
+    p1 = pow(0.9, double(t0));
+    p2 = pow(0.999, double(t0));
+  }
+  float loss = 0.f;
   __syncthreads();
-  for (int o = ENS_TPB / 2; o > 0; o >>= 1) {
-    if (tid < o) red[tid] += red[tid + o];
+  for (int it = 0; it < iters; ++it) {
+    float sums[5] = {}, gb3 = 0.f;
+    if (active) {
+      float h1[4 * HT];
+      f32x4 z[HT];
+#pragma unroll
+      for (int t = 0; t < HT; ++t) {
+        const int i = 16 * t + g4;
+        const float4 wx = *reinterpret_cast<const float4*>(small + i);
+        const float4 wy = *reinterpret_cast<const float4*>(small + HP + i);
+        const float4 c = *reinterpret_cast<const float4*>(small + 2 * HP + i);
+        const float4 d = *reinterpret_cast<const float4*>(small + 3 * HP + i);
+        h1[4 * t] = tanhf(wx.x * x0 + wy.x * x1 + c.x);
+        h1[4 * t + 1] = tanhf(wx.y * x0 + wy.y * x1 + c.y);
+        h1[4 * t + 2] = tanhf(wx.z * x0 + wy.z * x1 + c.z);
+        h1[4 * t + 3] = tanhf(wx.w * x0 + wy.w * x1 + c.w);
+        *reinterpret_cast<float4*>(ha + pt * EP + i) = make_float4(h1[4 * t], h1[4 * t + 1], h1[4 * t + 2], h1[4 * t + 3]);
+        z[t] = f32x4{d.x, d.y, d.z, d.w};
+      }
+#pragma unroll
+      for (int t = 0; t < HT; ++t)
+#pragma unroll
+        for (int k = 0; k < HT; ++k) {
+          const f32x4 a = *reinterpret_cast<const f32x4*>(W2 + (16 * t + l16) * EP + 16 * k + g4);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], h1[4 * k + u], z[t], 0, 0, 0);
+        }
+      float out = 0.f;
+      f32x4 w3[HT];
+#pragma unroll
+      for (int t = 0; t < HT; ++t) {
+        w3[t] = *reinterpret_cast<const f32x4*>(small + 4 * HP + 16 * t + g4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          z[t][u] = tanhf(z[t][u]);
+          out += w3[t][u] * z[t][u];
+        }
+      }
+      out += __shfl_xor(out, 16);
+      out += __shfl_xor(out, 32);
+      const float r = out + small[5 * HP] - y;
+      const float dout = on ? 2.0f * wt * r * invN : 0.f;
+      loss = on ? wt * r * r : 0.f;
+      gb3 = dout;
+      gb3 += lane_xor<15>(gb3);
+      gb3 += lane_xor<7>(gb3);
+      gb3 += lane_xor<2>(gb3);
+      gb3 += lane_xor<1>(gb3);
+      float v[V];
+      auto collect = [&](auto value) {
+#pragma unroll
+        for (int q = 0; q < V; ++q) v[q] = q < 4 * HT ? value(q) : 0.f;
+        return sum_split<V>(v, l16);
+      };
+      sums[4] = collect([&](int q) { return dout * z[q / 4][q % 4]; });
+#pragma unroll
+      for (int t = 0; t < HT; ++t) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) z[t][u] = dout * w3[t][u] * (1.0f - z[t][u] * z[t][u]);
+        *reinterpret_cast<f32x4*>(da + pt * EP + 16 * t + g4) = z[t];
+      }
+      sums[3] = collect([&](int q) { return z[q / 4][q % 4]; });
+      f32x4 b[HT];
+#pragma unroll
+      for (int k = 0; k < HT; ++k) b[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < HT; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int k = 0; k < HT; ++k)
+            b[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(W2[(16 * t + g4 + u) * EP + 16 * k + l16], z[t][u], b[k], 0, 0,
+                                                        0);
+#pragma unroll
+      for (int q = 0; q < 4 * HT; ++q) h1[q] = b[q / 4][q % 4] * (1.0f - h1[q] * h1[q]);
+      sums[0] = collect([&](int q) { return h1[q] * x0; });
+      sums[1] = collect([&](int q) { return h1[q] * x1; });
+      sums[2] = collect([&](int q) { return h1[q]; });
+    }
+    if (tid == 0) {
+      p1 *= 0.9;
+      p2 *= 0.999;
+      small[5 * HP + 1] = float(1.0 / (1.0 - p1));
+      small[5 * HP + 2] = float(1.0 / (1.0 - p2));
+    }
+    __syncthreads();
+    const float a1 = small[5 * HP + 1], a2 = small[5 * HP + 2];
+    if (owner) {
+      f32x4 g = {0.f, 0.f, 0.f, 0.f};
+      const float* dp = da + g4 * EP + 16 * to + l16;
+      const float* hp = ha + g4 * EP + 16 * ti + l16;
+      for (int c = 0; c < nw; ++c, dp += 16 * EP, hp += 16 * EP) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) g = __builtin_amdgcn_mfma_f32_16x16x4f32(dp[u * EP], hp[u * EP], g, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (grad_out) {
+          if (w_at[u] >= 0) grad_out[base + w_at[u]] = g[u];
+        } else {
+          adam(w_at[u] >= 0 ? g[u] : 0.f, a1, a2, lr, w_th[u], w_m[u], w_v[u]);
+          W2[(16 * to + g4 + u) * EP + 16 * ti + l16] = w_th[u];
+        }
+      }
+    }
+    __syncthreads();
+    if (active) {
+      const int q = l16 % V, o = 16 * (q / 4) + g4 + q % 4;
+      if (l16 < V && o < HP) {
+#pragma unroll
+        for (int j = 0; j < 5; ++j) part[wave * PART + j * HP + o] = sums[j];
+      }
+      if (lane == 0) part[wave * PART + 5 * HP] = gb3;
+    }
+    __syncthreads();
+    if (s_at >= 0) {
+      float g = 0.f;
+#pragma unroll 4
+      for (int w = 0; w < nw; ++w) g += part[w * PART + tid];
+      if (grad_out) {
+        grad_out[base + s_at] = g;
+      } else {
+        adam(g, a1, a2, lr, s_th, s_m, s_v);
+        small[tid] = s_th;
+      }
+    }
     __syncthreads();
   }
-  if (tid == 0) lpart[size_t(member) * nchunk + chunk] = red[0] * invN;
+  if (!grad_out) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (w_at[u] >= 0) {
+        params[base + w_at[u]] = w_th[u];
+        mom[base + w_at[u]] = w_m[u];
+        vel[base + w_at[u]] = w_v[u];
+      }
+    if (s_at >= 0) {
+      params[base + s_at] = s_th;
+      mom[base + s_at] = s_m;
+      vel[base + s_at] = s_v;
+    }
+  }
+  if (lane < 16 && active) part[pt] = loss;
+  __syncthreads();
+  if (tid == 0) {
+    float l = 0.f;
+    for (int i = 0; i < N; ++i) l += part[i];
+    loss_out[member] = l * invN;
+  }
 }
 
-// Per member: the gradient summed over chunks, then (unless grad_out is set,
-// which receives the gradient instead) one Adam step (Kingma & Ba 2015,
-// beta = (0.9, 0.999), eps = 1e-8).  Grid: (parameter blocks, members); the
-// step number is *tbase + k + 1.  loss_out receives the loss at the
-// parameters before the step.
-__global__ __launch_bounds__(ENS_TPB) void k_ens_adam(int P, int nchunk, const float* __restrict__ gpart,
+// Forward and backward pass of (share of the points, member), CHUNK points at a
+// time, and its part of the gradient and loss (MSE over all N points: the 2/N
+// and 1/N factors are applied here; wts as above).
+//
+// Hidden units are padded to HT tiles of 16 with zero weights, points to CHUNK
+// with zero residuals.  The three products of the hidden layer (forward, back
+// to the first layer, gradient) are 16 x 16 x 4 matrix instructions from LDS,
+// a 16 x 16 tile per wavefront and turn.
+template <int HT>
+__global__ __launch_bounds__(TRAIN_TPB) void k_ens_share(int N, int H, const float* __restrict__ Xs,
+                                                         const float* __restrict__ ys,
+                                                         const float* __restrict__ wts,
+                                                         const float* __restrict__ params, float* __restrict__ gout,
+                                                         float* __restrict__ lout) {
+  constexpr int HP = 16 * HT, EP = HP + 4;  // row pitch: a matrix operand's 16 rows x 4 columns on different banks
+  constexpr int WAVES = TRAIN_TPB / 64;
+  constexpr int GT = (HT * HT + WAVES - 1) / WAVES;  // gradient tiles per wavefront
+  __shared__ float W2[HP * EP], h1[CHUNK * EP], h2[CHUNK * EP], dz1[CHUNK * EP];
+  __shared__ float W1[2 * HP], b1[HP], b2[HP], W3[HP], b3[1];
+  __shared__ float x[2 * CHUNK], dout[CHUNK], loss[CHUNK];
+  const int P = nparams(H);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr16 = lane & 15, lk = lane >> 4;
+  const int member = blockIdx.y, share = blockIdx.x, nshare = gridDim.x;
+  // units H .. HP - 1 are zeros
+  const float* const th = params + size_t(member) * P;
+#pragma unroll 4
+  for (int e = tid; e < HP * HP; e += TRAIN_TPB) {
+    const int o = e / HP, i = e % HP;
+    W2[o * EP + i] = o < H && i < H ? th[3 * H + o * H + i] : 0.f;
+  }
+  if (tid < HP) {
+    const bool on = tid < H;
+    W1[2 * tid] = on ? th[2 * tid] : 0.f;
+    W1[2 * tid + 1] = on ? th[2 * tid + 1] : 0.f;
+    b1[tid] = on ? th[2 * H + tid] : 0.f;
+    b2[tid] = on ? th[3 * H + H * H + tid] : 0.f;
+    W3[tid] = on ? th[4 * H + H * H + tid] : 0.f;
+    if (tid == 0) b3[0] = th[5 * H + H * H];
+  }
+  // tile of a product over K with operands A(row, k) = a[row * as + k * ak],
+  // B(k, col) = b[k * bk + col * bs], added to acc (element u: row 4 lk + u,
+  // column lr16)
+  auto product = [&](const float* a, int as, int ak, const float* b, int bk, int bs, int K, f32x4 acc) {
+    const float* ap = a + lr16 * as + lk * ak;
+    const float* bp = b + lk * bk + lr16 * bs;
+#pragma unroll
+    for (int q = 0; q < K; q += 4)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ap[q * ak], bp[q * bk], acc, 0, 0, 0);
+    return acc;
+  };
+  const float invN = 1.0f / float(N);
+  f32x4 gw2[GT];
+#pragma unroll
+  for (int j = 0; j < GT; ++j) gw2[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gw3 = 0.f, gsmall = 0.f, gb3 = 0.f, lsum = 0.f;
+  for (int c0 = share * CHUNK; c0 < N; c0 += nshare * CHUNK) {
+    const int nc = min(CHUNK, N - c0);
+    if (tid < 2 * CHUNK) x[tid] = tid < 2 * nc ? Xs[2 * c0 + tid] : 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int e = tid; e < CHUNK * HP; e += TRAIN_TPB) {
+      const int s = e / HP, o = e % HP;
+      h1[s * EP + o] = tanhf(W1[2 * o] * x[2 * s] + W1[2 * o + 1] * x[2 * s + 1] + b1[o]);
+    }
+    __syncthreads();
+    for (int q = wave; q < (CHUNK / 16) * HT; q += WAVES) {
+      const int tr = q / HT, tc = q % HT, o = 16 * tc + lr16;
+      const float bo = b2[o];
+      const f32x4 z = product(h1 + 16 * tr * EP, EP, 1, W2 + 16 * tc * EP, 1, EP, HP, f32x4{bo, bo, bo, bo});
+#pragma unroll
+      for (int u = 0; u < 4; ++u) h2[(16 * tr + 4 * lk + u) * EP + o] = tanhf(z[u]);
+    }
+    __syncthreads();
+    {  // output layer: 16 lanes per point
+      const int s = tid / 16, part = tid & 15;
+      float a = 0.f;
+#pragma unroll
+      for (int o = part; o < HP; o += 16) a += W3[o] * h2[s * EP + o];
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o);
+      if (part == 0) {
+        float l = 0.f, d = 0.f;
+        if (s < nc) {
+          // bootstrap: the point's count in this member's resample weights its
+          // squared residual (the mean still over N)
+          const float w = wts ? wts[size_t(member) * N + c0 + s] : 1.0f;
+          const float r = a + b3[0] - ys[c0 + s];
+          l = w * r * r;
+          d = 2.0f * w * r * invN;
+        }
+        loss[s] = l;
+        dout[s] = d;
+      }
+    }
+    __syncthreads();
+    // W3, b3 and the loss, before h2 becomes the second layer's residuals
+    if (tid < HP) {
+#pragma unroll 8
+      for (int s = 0; s < CHUNK; ++s) gw3 += dout[s] * h2[s * EP + tid];
+    } else if (wave == WAVES - 1 && lane < CHUNK) {
+      gb3 += dout[lane];
+      lsum += loss[lane];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = tid; e < CHUNK * HP; e += TRAIN_TPB) {
+      const int s = e / HP, o = e % HP;
+      const float v = h2[s * EP + o];
+      h2[s * EP + o] = dout[s] * W3[o] * (1.0f - v * v);
+    }
+    __syncthreads();
+    const float* const dz2 = h2;
+    for (int q = wave; q < (CHUNK / 16) * HT; q += WAVES) {
+      const int tr = q / HT, tc = q % HT, i = 16 * tc + lr16;
+      const f32x4 a = product(dz2 + 16 * tr * EP, EP, 1, W2 + 16 * tc, EP, 1, HP, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int s = 16 * tr + 4 * lk + u;
+        const float v = h1[s * EP + i];
+        dz1[s * EP + i] = a[u] * (1.0f - v * v);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < GT; ++j) {
+      const int q = wave + j * WAVES;
+      if (q < HT * HT)
+        gw2[j] = product(dz2 + 16 * (q / HT), 1, EP, h1 + 16 * (q % HT), EP, 1, CHUNK, gw2[j]);
+    }
+    __syncthreads();
+    // W1, b1 (from dz1) and b2 (from dz2): four sums per unit
+    if (tid < 4 * HP) {
+      const int o = tid >> 2, what = tid & 3;
+#pragma unroll 8
+      for (int s = 0; s < CHUNK; ++s) {
+        const float f = what < 2 ? x[2 * s + what] : 1.0f;
+        gsmall += (what < 3 ? dz1[s * EP + o] : dz2[s * EP + o]) * f;
+      }
+    }
+    __syncthreads();  // the next points' x and activations
+  }
+  float* const go = gout + (size_t(member) * nshare + share) * P;
+#pragma unroll
+  for (int j = 0; j < GT; ++j) {
+    const int q = wave + j * WAVES, i = 16 * (q % HT) + lr16;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int o = 16 * (q / HT) + 4 * lk + u;
+      if (o < H && i < H) go[3 * H + o * H + i] = gw2[j][u];
+    }
+  }
+  if (tid < H) go[4 * H + H * H + tid] = gw3;
+  if (tid < 4 * H) {
+    const int o = tid >> 2, what = tid & 3;
+    go[what < 2 ? 2 * o + what : (what == 2 ? 2 * H + o : 3 * H + H * H + o)] = gsmall;
+  }
+  if (wave == WAVES - 1) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      gb3 += __shfl_xor(gb3, o);
+      lsum += __shfl_xor(lsum, o);
+    }
+    if (lane == 0) {
+      go[5 * H + H * H] = gb3;
+      lout[size_t(member) * nshare + share] = lsum * invN;
+    }
+  }
+}
+
+// Per member: the gradient summed over shares and one Adam step.  Grid:
+// (parameter blocks, members); the step number is *tbase + k + 1.  loss_out
+// receives the loss at the parameters before the step.
+__global__ __launch_bounds__(ENS_TPB) void k_ens_adam(int P, int nshare, const float* __restrict__ gpart,
                                                       const float* __restrict__ lpart, float* __restrict__ params,
                                                       float* __restrict__ mom, float* __restrict__ vel,
                                                       const int* __restrict__ tbase, int k, float lr,
                                                       float* __restrict__ loss_out, float* __restrict__ grad_out) {
   const int member = blockIdx.y, p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p < P) {
-    const float* gm = gpart + size_t(member) * nchunk * P;
+    const float* gm = gpart + size_t(member) * nshare * P + p;
+    const size_t at = size_t(member) * P + p;
     float g = 0.f;
-    for (int c = 0; c < nchunk; ++c) g += gm[size_t(c) * P + p];
+#pragma unroll 8
+    for (int c = 0; c < nshare; ++c) g += gm[size_t(c) * P];
     if (grad_out) {
-      grad_out[size_t(member) * P + p] = g;
+      grad_out[at] = g;
     } else {
       const int t = *tbase + k + 1;
       const float c1 = float(1.0 / (1.0 - pow(0.9, double(t)))), c2 = float(1.0 / (1.0 - pow(0.999, double(t))));
-      float* m = mom + size_t(member) * P;
-      float* v = vel + size_t(member) * P;
-      const float mk = 0.9f * m[p] + 0.1f * g, vk = 0.999f * v[p] + 0.001f * g * g;
-      m[p] = mk;
-      v[p] = vk;
-      params[size_t(member) * P + p] -= lr * (mk * c1) / (sqrtf(vk * c2) + 1e-8f);
+      adam(g, c1, c2, lr, params[at], mom[at], vel[at]);
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     float l = 0.f;
-    for (int c = 0; c < nchunk; ++c) l += lpart[size_t(member) * nchunk + c];
+    for (int c = 0; c < nshare; ++c) l += lpart[size_t(member) * nshare + c];
     loss_out[member] = l;
   }
 }
 
 __global__ void k_ens_tick(int* tbase, int k) { *tbase += k; }
 
-// Prediction, member by member: one wavefront per (block of PQB queries,
-// member), lane o holding hidden unit o.  The member's W2 sits transposed in
-// LDS so lane o reads its column with consecutive addresses; the layer-1
-// activations of the PQB queries are shared through LDS; the output layer is
-// a wavefront sum.
-constexpr int PQB = 8;
-
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
-__global__ __launch_bounds__(64) void k_ens_member_out(int m, int H, const float* __restrict__ params,
-                                                       const double* __restrict__ Xq, double mu0, double mu1,
-                                                       double sd0, double sd1, float* __restrict__ yout) {
-  __shared__ float w2t[MAXH * MAXH];
-  __shared__ float h1[PQB][MAXH];
-  const int k = blockIdx.y, o = threadIdx.x, q0 = blockIdx.x * PQB;
+// Prediction, member by member: a wavefront keeps its member's weights in
+// registers as matrix operands and takes 16 queries at a time.  A lane forms
+// the first-layer activations it feeds to the 16 x 16 x 4 instructions (query
+// lane % 16, units 4 k + lane / 16) itself, and the output layer is a sum over
+// 16 lanes, so nothing passes through LDS.  What bounds it is the tanh of two
+// layers (128 per query and member, about 30 instructions each) and the matrix
+// rate: 50,000 queries of 5 members of 64 units took 300 us with W2 in LDS and
+// a lane per unit, and take 65 us.
+template <int HT>
+__global__ __launch_bounds__(256) void k_ens_member_out(int m, int H, const float* __restrict__ params,
+                                                        const double* __restrict__ Xq, double mu0, double mu1,
+                                                        double sd0, double sd1, float* __restrict__ yout) {
+  const int k = blockIdx.y, lane = threadIdx.x & 63, lr16 = lane & 15, lk = lane >> 4;
   const int P = nparams(H);
   const float* W1 = params + size_t(k) * P;
   const float* b1 = W1 + 2 * H;
@@ -225,33 +534,50 @@ __global__ __launch_bounds__(64) void k_ens_member_out(int m, int H, const float
   const float* b2 = W2 + H * H;
   const float* W3 = b2 + H;
   const float b3 = W3[H];
-  for (int t = o; t < H * H; t += 64) w2t[(t % H) * H + t / H] = W2[t];  // W2 row o' = output unit o'
-  const bool unit = o < H;
-  if (unit) {
-    const float w10 = W1[2 * o], w11 = W1[2 * o + 1], c1 = b1[o];
+  float w10[4 * HT], w11[4 * HT], c1[4 * HT], w2[HT][4 * HT], c2[HT], w3[HT];
 #pragma unroll
-    for (int q = 0; q < PQB; ++q) {
-      const int qq = q0 + q < m ? q0 + q : m - 1;
-      const float x0 = float((Xq[2 * qq] - mu0) / sd0), x1 = float((Xq[2 * qq + 1] - mu1) / sd1);
-      h1[q][o] = tanhf(w10 * x0 + w11 * x1 + c1);
+  for (int q = 0; q < 4 * HT; ++q) {
+    const int i = 4 * q + lk;
+    w10[q] = i < H ? W1[2 * i] : 0.f;
+    w11[q] = i < H ? W1[2 * i + 1] : 0.f;
+    c1[q] = i < H ? b1[i] : 0.f;
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      const int o = 16 * t + lr16;
+      w2[t][q] = i < H && o < H ? W2[o * H + i] : 0.f;
     }
   }
-  __syncthreads();
-  float a[PQB];
-  const float c2 = unit ? b2[o] : 0.0f;
 #pragma unroll
-  for (int q = 0; q < PQB; ++q) a[q] = c2;
-  if (unit)
-    for (int i = 0; i < H; ++i) {
-      const float w = w2t[i * H + o];
+  for (int t = 0; t < HT; ++t) {
+    const int o = 16 * t + lr16;
+    c2[t] = o < H ? b2[o] : 0.f;
+    w3[t] = o < H ? W3[o] : 0.f;
+  }
+  const int tiles = (m + 15) / 16, nw = gridDim.x * (blockDim.x / 64);
+  for (int tile = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); tile < tiles; tile += nw) {
+    const int qq = min(16 * tile + lr16, m - 1);
+    const float x0 = float((Xq[2 * qq] - mu0) / sd0), x1 = float((Xq[2 * qq + 1] - mu1) / sd1);
+    f32x4 z[HT];
 #pragma unroll
-      for (int q = 0; q < PQB; ++q) a[q] += w * h1[q][i];
+    for (int t = 0; t < HT; ++t) z[t] = f32x4{c2[t], c2[t], c2[t], c2[t]};
+#pragma unroll
+    for (int q = 0; q < 4 * HT; ++q) {
+      // (a padded unit's zero weights would make a NaN of an infinite query)
+      const float h = 4 * q + lk < H ? tanhf(w10[q] * x0 + w11[q] * x1 + c1[q]) : 0.f;
+#pragma unroll
+      for (int t = 0; t < HT; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, w2[t][q], z[t], 0, 0, 0);
     }
-  const float w3 = unit ? W3[o] : 0.0f;
+    // element u: query 4 lk + u, units 16 t + lr16
 #pragma unroll
-  for (int q = 0; q < PQB; ++q) {
-    const float v = wave_sum_f(unit ? w3 * tanhf(a[q]) : 0.0f);
-    if (o == 0 && q0 + q < m) yout[size_t(k) * m + q0 + q] = b3 + v;
+    for (int u = 0; u < 4; ++u) {
+      float v = 0.f;
+#pragma unroll
+      for (int t = 0; t < HT; ++t) v += w3[t] * tanhf(z[t][u]);
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+      const int q = 16 * tile + 4 * lk + u;
+      if (lr16 == 0 && q < m) yout[size_t(k) * m + q] = b3 + v;
+    }
   }
 }
 
@@ -273,8 +599,25 @@ __global__ __launch_bounds__(128) void k_ens_reduce(int m, int members, const fl
   std_out[q] = sqrt(var > 0.0 ? var : 0.0);
 }
 
-size_t train_lds_bytes(int H) {
-  return sizeof(float) * (size_t(nparams(H)) + 2 * CHUNK + 4 * size_t(CHUNK) * (H + 1) + CHUNK + ENS_TPB);
+// Calls f with the smallest number of 16-unit tiles that holds H units, as a type.
+template <class F>
+void with_tiles(int H, F f) {
+  if (H <= 16) f(std::integral_constant<int, 1>{});
+  else if (H <= 32) f(std::integral_constant<int, 2>{});
+  else if (H <= 48) f(std::integral_constant<int, 3>{});
+  else f(std::integral_constant<int, 4>{});
+}
+
+// Queues the members' outputs at m queries: 16 queries per wavefront and turn,
+// as many workgroups as two turns each allow up to 512 per member (with 5
+// members ten per compute unit).
+void enqueue_members(const hmd_ens* e, int m, const double* dXq, float* yout, hipStream_t s) {
+  const int H = e->cfg.hidden, tiles = (m + 15) / 16;
+  const dim3 grid{unsigned(std::min(512, (tiles + 7) / 8)), unsigned(e->cfg.members), 1};
+  with_tiles(H, [&](auto tiles) {
+    hipLaunchKernelGGL(k_ens_member_out<decltype(tiles)::value>, grid, dim3(256), 0, s, m, H, e->dparams, dXq, e->mu[0],
+                       e->mu[1], e->sd[0], e->sd[1], yout);
+  });
 }
 
 // Glorot-uniform start of one member: Philox4x32-10 keyed by the seed, word
@@ -359,56 +702,79 @@ int stage_data(hmd_ens* e, const double* X, const double* y, int n, float** dX, 
 int run_train(hmd_ens* e, int n, const float* dX, const float* dy, const float* dw, int mode, float* dgrad) {
   hmd_ctx* ctx = e->ctx;
   const hmd_ens_cfg& c = e->cfg;
-  const size_t lds = train_lds_bytes(c.hidden);
-  const int nchunk = (n + CHUNK - 1) / CHUNK, P = e->P, M = c.members;
-  float *gpart = nullptr, *lpart = nullptr, *mom = nullptr, *vel = nullptr, *dloss = nullptr;
-  int* tstep = nullptr;
-  hipError_t err = hipMalloc(&gpart, sizeof(float) * size_t(M) * nchunk * P);
-  if (err == hipSuccess) err = hipMalloc(&lpart, sizeof(float) * size_t(M) * nchunk);
-  if (err == hipSuccess) err = hipMalloc(&mom, sizeof(float) * size_t(M) * P);
-  if (err == hipSuccess) err = hipMalloc(&vel, sizeof(float) * size_t(M) * P);
-  if (err == hipSuccess) err = hipMalloc(&dloss, sizeof(float) * M);
-  if (err == hipSuccess) err = hipMalloc(&tstep, sizeof(int) * M);
-  hipStream_t s = ctx->stream;
-  if (err == hipSuccess) err = hipMemsetAsync(mom, 0, sizeof(float) * size_t(M) * P, s);
-  if (err == hipSuccess) err = hipMemsetAsync(vel, 0, sizeof(float) * size_t(M) * P, s);
-  if (err == hipSuccess) err = hipMemsetAsync(tstep, 0, sizeof(int) * M, s);
+  const int P = e->P, M = c.members;
   const int iters = mode == 1 ? 1 : c.iters;
-  const dim3 agrid((P + ENS_TPB - 1) / ENS_TPB, M);
-  auto iteration = [&](int k) {
-    hipLaunchKernelGGL(k_ens_chunk, dim3(nchunk, M), dim3(ENS_TPB), lds, s, n, c.hidden, dX, dy, dw, e->dparams,
-                       gpart, lpart);
-    hipLaunchKernelGGL(k_ens_adam, agrid, dim3(ENS_TPB), 0, s, P, nchunk, gpart, lpart, e->dparams, mom, vel,
-                       tstep, k, float(c.lr), dloss, mode == 1 ? dgrad : nullptr);
-  };
-  // iterations in captured blocks of kBlock (a graph replay per block), the
-  // remainder as direct launches; the step counter advances once per block
-  constexpr int kBlock = 100;
-  const int nblock = iters / kBlock;
-  if (err == hipSuccess && nblock > 0) {
-    hipGraph_t g = nullptr;
-    hipGraphExec_t ge = nullptr;
-    err = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
-    if (err == hipSuccess) {
-      for (int k = 0; k < kBlock; ++k) iteration(k);
-      hipLaunchKernelGGL(k_ens_tick, dim3(1), dim3(1), 0, s, tstep, kBlock);
-      err = hipStreamEndCapture(s, &g);
+  // one workgroup per member as far as its LDS holds the points: 20 us per
+  // iteration at its largest (256 points, 64 units) against 27 and more for
+  // work shared out over the chip, which gains only on sets beyond that
+  const bool local = n <= LOCAL_N;
+  const int nshare = local ? 0 : std::min((n + CHUNK - 1) / CHUNK, MAX_SHARES);
+  // one allocation: moments, gradient and loss shares, losses, step counter
+  const size_t mp = size_t(M) * P;
+  float* mom = nullptr;
+  hipError_t err = hipMalloc(&mom, sizeof(float) * (2 * mp + nshare * (mp + M) + M + 1));
+  float* const vel = mom + mp;
+  float* const gpart = vel + mp;
+  float* const lpart = gpart + nshare * mp;
+  float* const dloss = lpart + size_t(nshare) * M;
+  int* const tstep = reinterpret_cast<int*>(dloss + M);
+  hipStream_t s = ctx->stream;
+  if (local) {
+    with_tiles(c.hidden, [&](auto tiles) {
+      constexpr int HT = decltype(tiles)::value, HP = 16 * HT, EP = HP + 4;
+      const int nw = (n + 15) / 16, waves = std::max({nw, HT * HT, (5 * HP + 64) / 64});
+      // activations and residuals; the sums of the small tensors take their place
+      const size_t act = std::max(2 * size_t(16 * nw) * EP, size_t(nw) * (5 * HP + 4));
+      const size_t lds = sizeof(float) * (HP * EP + 5 * HP + 4 + act);
+      if (err == hipSuccess)
+        err = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ens_local<HT>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+      for (int t = 0; t < iters && err == hipSuccess; t += LOCAL_ITERS) {
+        hipLaunchKernelGGL(k_ens_local<HT>, dim3(M), dim3(64 * waves), lds, s, n, c.hidden, dX, dy, dw, e->dparams, mom,
+                           vel, t, std::min(LOCAL_ITERS, iters - t), float(c.lr), dloss, mode == 1 ? dgrad : nullptr);
+        err = hipGetLastError();
+      }
+    });
+  } else {
+    if (err == hipSuccess) err = hipMemsetAsync(mom, 0, sizeof(float) * 2 * mp, s);
+    if (err == hipSuccess) err = hipMemsetAsync(tstep, 0, sizeof(int), s);
+    const dim3 agrid((P + ENS_TPB - 1) / ENS_TPB, M);
+    auto iteration = [&](int k) {
+      with_tiles(c.hidden, [&](auto tiles) {
+        hipLaunchKernelGGL(k_ens_share<decltype(tiles)::value>, dim3(nshare, M), dim3(TRAIN_TPB), 0, s, n, c.hidden, dX,
+                           dy, dw, e->dparams, gpart, lpart);
+      });
+      hipLaunchKernelGGL(k_ens_adam, agrid, dim3(ENS_TPB), 0, s, P, nshare, gpart, lpart, e->dparams, mom, vel, tstep,
+                         k, float(c.lr), dloss, mode == 1 ? dgrad : nullptr);
+    };
+    // iterations in captured blocks of kBlock (a graph replay per block), the
+    // remainder as direct launches; the step counter advances once per block
+    constexpr int kBlock = 100;
+    const int nblock = iters / kBlock;
+    if (err == hipSuccess && nblock > 0) {
+      hipGraph_t g = nullptr;
+      hipGraphExec_t ge = nullptr;
+      err = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+      if (err == hipSuccess) {
+        for (int k = 0; k < kBlock; ++k) iteration(k);
+        hipLaunchKernelGGL(k_ens_tick, dim3(1), dim3(1), 0, s, tstep, kBlock);
+        err = hipStreamEndCapture(s, &g);
+      }
+      if (err == hipSuccess) err = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+      for (int r = 0; r < nblock && err == hipSuccess; ++r) err = hipGraphLaunch(ge, s);
+      if (ge) (void)hipGraphExecDestroy(ge);
+      if (g) (void)hipGraphDestroy(g);
     }
-    if (err == hipSuccess) err = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    for (int r = 0; r < nblock && err == hipSuccess; ++r) err = hipGraphLaunch(ge, s);
-    if (ge) (void)hipGraphExecDestroy(ge);
-    if (g) (void)hipGraphDestroy(g);
-  }
-  for (int k = 0; k < iters - nblock * kBlock && err == hipSuccess; ++k) {
-    iteration(k);
-    err = hipGetLastError();
+    for (int k = 0; k < iters - nblock * kBlock && err == hipSuccess; ++k) {
+      iteration(k);
+      err = hipGetLastError();
+    }
   }
   std::vector<float> loss(M, 0.f);
   if (err == hipSuccess && iters > 0)
     err = hipMemcpyAsync(loss.data(), dloss, sizeof(float) * M, hipMemcpyDeviceToHost, s);
   if (err == hipSuccess) err = hipStreamSynchronize(s);
-  for (void* p : {(void*)gpart, (void*)lpart, (void*)mom, (void*)vel, (void*)dloss, (void*)tstep})
-    if (p) (void)hipFree(p);
+  if (mom) (void)hipFree(mom);
   if (err != hipSuccess) {
     ctx->err = std::string("ens training: ") + hipGetErrorString(err);
     return HMD_EDEVICE;
@@ -514,8 +880,7 @@ int ens_predict(hmd_ens* e, const double* Xs, int m, double* mean, double* std) 
   }
   std::vector<double> res(2 * size_t(m));  // means, then standard deviations
   HMD_HIP(ctx, hipMemcpyAsync(e->dq, Xs, sizeof(double) * 2 * m, hipMemcpyHostToDevice, ctx->stream));
-  hipLaunchKernelGGL(k_ens_member_out, dim3((m + PQB - 1) / PQB, e->cfg.members), dim3(64), 0, ctx->stream, m,
-                     e->cfg.hidden, e->dparams, e->dq, e->mu[0], e->mu[1], e->sd[0], e->sd[1], e->dy);
+  enqueue_members(e, m, e->dq, e->dy, ctx->stream);
   HMD_HIP(ctx, hipGetLastError());
   hipLaunchKernelGGL(k_ens_reduce, dim3((m + 127) / 128), dim3(128), 0, ctx->stream, m, e->cfg.members, e->dy,
                      e->s_q, e->dout, e->dout + m);
@@ -548,8 +913,7 @@ int ens_predict_dev(hmd_ens* e, const double* dXs, int m, double* dmean, double*
     HMD_HIP(ctx, hipMalloc(&e->dout, sizeof(double) * 2 * cap));
     e->qcap = cap;
   }
-  hipLaunchKernelGGL(k_ens_member_out, dim3((m + PQB - 1) / PQB, e->cfg.members), dim3(64), 0, s, m,
-                     e->cfg.hidden, e->dparams, dXs, e->mu[0], e->mu[1], e->sd[0], e->sd[1], e->dy);
+  enqueue_members(e, m, dXs, e->dy, s);
   HMD_HIP(ctx, hipGetLastError());
   hipLaunchKernelGGL(k_ens_reduce, dim3((m + 127) / 128), dim3(128), 0, s, m, e->cfg.members, e->dy, e->s_q,
                      dmean, dstd);

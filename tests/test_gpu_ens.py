@@ -115,3 +115,31 @@ def test_bad_configuration_rejected(ctx):
     X, y = data(16, 6)
     with pytest.raises(B.HmdError):
         B.Ensemble(ctx, X, y, B.ens_cfg(hidden=65))
+
+
+@pytest.mark.parametrize("n,hidden,bootstrap", [(1, 49, 0), (16, 33, 0), (17, 17, 1), (255, 63, 0), (256, 48, 1),
+                                                (257, 15, 0), (320, 64, 1), (1025, 31, 0)])
+def test_tile_edges(ctx, n, hidden, bootstrap):
+    """Ends of the 16-unit and 16-point tiles, of the one-workgroup training and
+    of the shares: gradients at the start against the oracle (FP32 sums of up to
+    1025 x 64 terms: 1e-4), predictions of the untrained members (sums of 64
+    terms of unit size: 1e-5 of the output scale), then 20 steps."""
+    X, y = data(n, 7 * n + hidden)
+    cfg = B.ens_cfg(members=2, hidden=hidden, iters=1, seed=5, bootstrap=bootstrap)
+    Xs, ys = _oracle_scaled(X, y) if n > 1 else (np.zeros((1, 2)), np.sign(y))
+    for k in range(2):
+        _, g_g = B.ens_grad_init(ctx, X, y, cfg, k)
+        th = mlp.glorot_init(hidden, k, 5)
+        w = mlp.bootstrap_counts(n, k, 5) if bootstrap else None
+        _, g_o = mlp.loss_and_grad(th, Xs, ys, hidden, w)
+        assert np.linalg.norm(g_g - g_o) <= 1e-4 * np.linalg.norm(g_o)
+    if n == 1:
+        return
+    for m in (1, 15, 200):
+        Xq = data(m, m)[0]
+        e = B.Ensemble(ctx, X, y, B.ens_cfg(members=2, hidden=hidden, iters=0, seed=5))
+        o = mlp.Ensemble(X, y, members=2, hidden=hidden, iters=0, seed=5)
+        assert np.abs(e.predict(Xq)[0] - o.predict(Xq)[0]).max() <= 1e-5 * np.sqrt(np.mean(y ** 2)) * 2
+    e = B.Ensemble(ctx, X, y, B.ens_cfg(members=2, hidden=hidden, iters=20, seed=5, bootstrap=bootstrap))
+    o = mlp.Ensemble(X, y, members=2, hidden=hidden, iters=20, seed=5, bootstrap=bool(bootstrap))
+    np.testing.assert_allclose(e.losses(), o.losses, rtol=1e-3)
