@@ -199,10 +199,11 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
       HMD_V(K, 0, 1, 0, 0), HMD_V(K, 0, 1, 0, 1), HMD_V(K, 0, 1, 1, 0), HMD_V(K, 0, 1, 1, 1),           \
       HMD_V(K, 1, 0, 0, 0), HMD_V(K, 1, 0, 0, 1), HMD_V(K, 1, 0, 1, 0), HMD_V(K, 1, 0, 1, 1),           \
       HMD_V(K, 1, 1, 0, 0), HMD_V(K, 1, 1, 0, 1), HMD_V(K, 1, 1, 1, 0), HMD_V(K, 1, 1, 1, 1)
-decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr) {
-  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_tiles)};
-  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
-  return pr ? tab_pr[v & 7] : tab[v];
+decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr, bool narrow) {
+  using Fn = decltype(&k_force_tiles<0, 0, 0, 0, 0>);
+  static const Fn tab[16] = {HMD_VARIANTS(k_force_tiles)}, tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
+  static const Fn ntab[16] = {HMD_VARIANTS(k_force_narrow)}, ntab_pr[8] = {HMD_VARIANTS_PR(k_force_narrow)};
+  return narrow ? (pr ? ntab_pr[v & 7] : ntab[v]) : (pr ? tab_pr[v & 7] : tab[v]);
 }
 decltype(&k_force_list<0, 0, 0, 0, 0>) force_list_variant(int v, bool pr) {
   static const decltype(&k_force_list<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_list)};
@@ -230,7 +231,7 @@ void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, St
     const int v = ((mode * 2 + (K.energy_on ? 1 : 0)) * 2 + (b->uniform ? 1 : 0)) * 2 + (b->walls_same ? 1 : 0);
     const bool pr = mode == 1 && K.press_on;
     if (b->path == 2) {
-      hipLaunchKernelGGL(force_tiles_variant(v, pr), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
+      hipLaunchKernelGGL(force_tiles_variant(v, pr, b->narrow), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
                          b->d_tilerec, b->d_sims, b->d_pfix, b->d_list,
                          b->d_nlist, b->d_f4, state_ref(b, 0), b->acc, b->d_dstate, R, K);
     } else {
@@ -375,20 +376,18 @@ int get_graph(hmd_batch* b, int chunk, const StepConst& K, hipGraphExec_t* out) 
 int make_tiles(hmd_batch* b) {
   hmd_ctx* ctx = b->ctx;
   constexpr int kStageCap = TILE_STAGE;
+  constexpr int64_t kMinTiles = 512;
   b->stage_cap = kStageCap;
-  std::vector<int4> tiles;
-  b->tile_first.assign(b->S + 1, 0);
+  // columns per tile: the most home atoms per unit of cost, cost being
+  // the lanes of whole 256-lane passes plus tile_alpha per staged atom
+  // (a wider tile stages less halo per home atom); 2% hysteresis keeps
+  // the narrower of two near-equal choices
+  std::vector<int> cols(b->S, 1);
   for (int k = 0; k < b->S; ++k) {
-    b->tile_first[k] = int(tiles.size());
     const SimDev& D = b->sims[k];
     const HostSystem& H = b->host[k];
     const double per_col = double(D.nf) / double(D.nx * D.nz);
     const double wall_col = double(H.nw) / double(2 * D.nx * D.nz);
-    // columns per tile: the most home atoms per unit of cost, cost being
-    // the lanes of whole 256-lane passes plus tile_alpha per staged atom
-    // (a wider tile stages less halo per home atom); 2% hysteresis keeps
-    // the narrower of two near-equal choices
-    int best = 1;
     double best_use = -1.0;
     for (int nc = 1; nc <= D.nx; ++nc) {
       const double atoms = nc * per_col;
@@ -398,10 +397,33 @@ int make_tiles(hmd_batch* b) {
       const double use = atoms / (passes * TILE_THREADS + b->tile_alpha * staged);
       if (use > best_use + 0.02 * (b->tile_alpha > 0.0 ? best_use : 1.0)) {
         best_use = use;
-        best = nc;
+        cols[k] = nc;
       }
     }
-    const int ntx = (D.nx + best - 1) / best;
+  }
+  auto count = [&](int widest) {
+    int64_t n = 0;
+    for (int k = 0; k < b->S; ++k) {
+      const int nc = std::min(cols[k], widest);
+      n += int64_t(b->sims[k].nz) * ((b->sims[k].nx + nc - 1) / nc);
+    }
+    return n;
+  };
+  // fewer tiles than two per compute unit leave the chip idle: narrower ones
+  // then, down to a column each, though each stages more halo (a step of the
+  // 2,048-atom channel 37 -> 31 us with 49 tiles for 14, of the 39,189-atom
+  // one 48.8 -> 48 us with 400 for 80: a list build 54 -> 47 us, a force
+  // 13.9 -> 14.6 us; batches of nine hundred tiles gain nothing)
+  int widest = *std::max_element(cols.begin(), cols.end());
+  while (widest > 1 && count(widest) < kMinTiles) --widest;
+  std::vector<int4> tiles;
+  b->tile_first.assign(b->S + 1, 0);
+  b->narrow = true;
+  for (int k = 0; k < b->S; ++k) {
+    b->tile_first[k] = int(tiles.size());
+    const SimDev& D = b->sims[k];
+    const int nc = std::min(cols[k], widest), ntx = (D.nx + nc - 1) / nc;
+    if (double(D.nf) * nc > 0.5 * TILE_THREADS * D.nx * D.nz) b->narrow = false;
     for (int z = 0; z < D.nz; ++z)
       for (int t = 0; t < ntx; ++t) {  // columns split as evenly as possible
         const int x0 = int(int64_t(t) * D.nx / ntx), x1 = int(int64_t(t + 1) * D.nx / ntx);

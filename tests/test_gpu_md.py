@@ -128,6 +128,23 @@ def test_tiled_list_build_shapes(h, skin, cell_w, params):
     assert pe == pytest.approx(peo, rel=1e-4)
 
 
+@pytest.mark.parametrize("h,cell_w", [(4.0, 0.0), (9.0, 0.0), (15.0, 0.0), (4.0, 4.0), (8.0, 4.0), (12.0, 4.0)])
+def test_lists_shared_by_lanes(h, cell_w):
+    # columns of about 25 to 170 atoms: four, two and one lane per list, with
+    # padded (five slabs) and partial (three slabs) last groups; bounds as above
+    params = dict(Lx_nom=12.7, Lz_nom=12.7)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=0.3, cell_w=cell_w, **params))
+    g_sys, o_sys = hmd.System(ctx, h, 0.02, 9), omd.System(h, 0.02, 9, omd.Params(**params))
+    o_sys.run(60)
+    xo, vo = o_sys.get_state()
+    g_sys.set_state(xo, vo)
+    f, pe = g_sys.forces()
+    fo, peo = o_sys.forces_cells()
+    ok, info = _per_atom_ok(f, fo)
+    assert ok, info
+    assert pe == pytest.approx(peo, rel=1e-4)
+
+
 @pytest.mark.parametrize("path", [1, 2, 3])
 @pytest.mark.parametrize("h,params,steps", [(6.0, SMALL_L, 300), (4.0, SMALL_L, 100), (12.0, SMALL_L, 200),
                                             (15.0, SMALL, 200)])
