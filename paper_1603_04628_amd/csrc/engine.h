@@ -83,6 +83,8 @@ struct StepConst {
   int press_on;    // sampled steps also record the wall normal pressure
 };
 
+constexpr int kPairCounters = 32, kPairPitch = 16;
+
 // Per-system FP64 accumulators (device).
 struct Acc {
   double* vc2[2];   // sum v_c^2 after the second half-kick, by step parity
@@ -97,7 +99,8 @@ struct Acc {
   double* tbins;    // [tiles * BIN_LDS * 2] the tiled path's bins: (sum v_x, count) per tile and bin,
                     // each tile adding to its own (no atomics; summed per system when read)
   int* status;      // [S] bit 0: unstable
-  unsigned long long* pairs;  // [2] in-cutoff fluid-fluid (ordered) and wall-fluid pairs
+  unsigned long long* pairs;  // in-cutoff fluid-fluid (ordered) and wall-fluid pairs: the sums over
+                              // kPairCounters entries, kPairPitch words apart
 };
 
 enum Kern { K_INTEGRATE = 0, K_SCAN, K_SCATTER, K_REORDER, K_FORCE, K_KEYS, K_LIST, K_COUNT };

@@ -277,7 +277,7 @@ int forces_now(hmd_batch* b, bool energy) {
   const int p = int((b->done + 1) & 1);
   HMD_HIP(ctx, hipMemsetAsync(b->acc.pe[p], 0, sizeof(double) * b->S, s));
   HMD_HIP(ctx, hipMemsetAsync(b->acc.ke[p], 0, sizeof(double) * b->S, s));
-  HMD_HIP(ctx, hipMemsetAsync(b->acc.pairs, 0, 2 * sizeof(unsigned long long), s));
+  HMD_HIP(ctx, hipMemsetAsync(b->acc.pairs, 0, kPairCounters * kPairPitch * sizeof(unsigned long long), s));
   enqueue_force(b, s, 0, K, StepRef{nullptr, b->done});
   HMD_HIP(ctx, hipGetLastError());
   return HMD_OK;
@@ -616,7 +616,7 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
                               ctx->stream));
   const int64_t nacc = 6 * int64_t(n) + 2 * int64_t(n) * b->nser + 3 * int64_t(n) + 2 * b->nbins;
   if ((rc = dalloc(ctx, &b->d_accbuf, nacc)) || (rc = dalloc(ctx, &b->d_status, n)) ||
-      (rc = dalloc(ctx, &b->acc.pairs, 2)) || (rc = dalloc(ctx, &b->d_sout, 4 * int64_t(n))))
+      (rc = dalloc(ctx, &b->acc.pairs, kPairCounters * kPairPitch)) || (rc = dalloc(ctx, &b->d_sout, 4 * int64_t(n))))
     return fail(rc);
   if (b->n_sample > 0 && b->P.n_blocks == 0 && (rc = dalloc(ctx, &b->d_gam, int64_t(n) * b->nser)))
     return fail(rc);
@@ -1186,11 +1186,13 @@ int batch_neighbors(hmd_batch* b, int sim, uint32_t* counts, uint32_t* idx, int6
 int batch_pairs(hmd_batch* b, int64_t* ff, int64_t* wf) {
   hmd_ctx* ctx = b->ctx;
   HMD_TRY(forces_now(b, true));
-  unsigned long long h[2] = {0, 0};
+  unsigned long long h[kPairCounters * kPairPitch], sum[2] = {0, 0};
   HMD_HIP(ctx, hipMemcpyAsync(h, b->acc.pairs, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
   HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  if (ff) *ff = int64_t(h[0]);
-  if (wf) *wf = int64_t(h[1]);
+  for (int k = 0; k < kPairCounters * kPairPitch; ++k)
+    if (k % kPairPitch < 2) sum[k % kPairPitch] += h[k];
+  if (ff) *ff = int64_t(sum[0]);
+  if (wf) *wf = int64_t(sum[1]);
   return HMD_OK;
 }
 

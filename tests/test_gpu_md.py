@@ -145,6 +145,27 @@ def test_lists_shared_by_lanes(h, cell_w):
     assert pe == pytest.approx(peo, rel=1e-4)
 
 
+@pytest.mark.parametrize("path", PATHS)
+def test_pair_counts(path):
+    # ordered fluid pairs and wall pairs inside the cut-off, counted directly;
+    # a pair within FP32 rounding of it (1e-6 of the ~1e5 pairs) may go either way
+    ctx = hmd.Context(hmd.Params(force_path=path, skin=SKIN, **SMALL_L))
+    b = hmd.Batch(ctx, [(6.0, 0.02, 3, 0), (4.0, 0.02, 4, 0)])
+    b.run(40, graph_chunk=20)
+    ff, wf = b.pair_count()
+    want = [0, 0]
+    for k, h in enumerate((6.0, 4.0)):
+        o = omd.System(h, 0.02, 3 + k, omd.Params(**SMALL_L))
+        x, xw = b.get_state(k)[0], o.wall()
+        for q, y in enumerate((x, xw)):
+            for xi in x:
+                d = y - xi
+                for a, L in ((0, o.Lx), (2, o.Lz)):
+                    d[:, a] -= L * np.round(d[:, a] / L)
+                want[q] += int(np.sum(np.sum(d * d, axis=1) < 6.25)) - (1 if q == 0 else 0)
+    assert abs(ff - want[0]) <= 4 and abs(wf - want[1]) <= 4, (ff, wf, want)
+
+
 @pytest.mark.parametrize("path", [1, 2, 3])
 @pytest.mark.parametrize("h,params,steps", [(6.0, SMALL_L, 300), (4.0, SMALL_L, 100), (12.0, SMALL_L, 200),
                                             (15.0, SMALL, 200)])
