@@ -165,6 +165,9 @@ struct hmd_batch {
   uint32_t* d_start = nullptr;      // first slot of each cell
   uint32_t* d_ncount = nullptr;     // atoms per cell after the sort
   uint32_t* d_perm = nullptr;       // scatter target -> source slot
+  uint32_t* d_bucket = nullptr;     // pair paths: bucket_cap entries per cell, its slots of the old order
+  uint32_t bucket_cap = 0;          // 0: sorted by the separate kernels only
+  int* d_done = nullptr;            // pair paths: workgroups of each system that have filled their buckets
   float4* d_wpos4 = nullptr;        // wall atoms, column order, column-relative
   uint32_t* d_wstart = nullptr;
   uint32_t* d_wcount = nullptr;

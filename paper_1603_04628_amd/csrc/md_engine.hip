@@ -157,28 +157,37 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
     L.end();
     L.begin(K_REORDER);
     hipLaunchKernelGGL(k_reorder<0>, dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_cell_sim, b->d_key,
-                       b->d_start, b->d_ncount, b->d_perm, state_ref(b, src), state_ref(b, dst), b->d_tag[src],
+                       b->d_start, b->d_ncount, b->d_perm, 0u, state_ref(b, src), state_ref(b, dst), b->d_tag[src],
                        b->d_tag[dst], b->d_pos4, b->d_pfix, b->d_pbuild, b->d_slot_cell, nullptr, R);
     L.end();
     b->cur = dst;
     return;
   }
-  L.begin(K_KEYS);
-  hipLaunchKernelGGL(k_keys, dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim, state_ref(b, 0), b->d_key,
-                     b->d_count, b->d_rank, flag, R);
-  L.end();
-  L.begin(K_SCAN);
-  hipLaunchKernelGGL(k_scan, dim3(b->S), dim3(1024), 0, s, b->d_sims, b->d_count, b->d_start, b->d_ncount, flag,
-                     R);
-  L.end();
-  L.begin(K_SCATTER);
-  hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(tpb), 0, s, nt, b->d_key, b->d_start, b->d_rank, b->d_perm, flag,
-                     R);
-  L.end();
+  // two kernels do the sort; the four they replace run where each kernel of
+  // the step is timed on its own
+  const bool whole = b->bucket_cap > 0 && !L.spans && !L.marks;
+  if (whole) {
+    hipLaunchKernelGGL(k_sort, dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim, state_ref(b, 0), b->d_key,
+                       b->d_count, b->d_bucket, b->bucket_cap, b->d_start, b->d_ncount, b->d_done, flag, R);
+  } else {
+    L.begin(K_KEYS);
+    hipLaunchKernelGGL(k_keys, dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim, state_ref(b, 0), b->d_key,
+                       b->d_count, b->d_rank, flag, R);
+    L.end();
+    L.begin(K_SCAN);
+    hipLaunchKernelGGL(k_scan, dim3(b->S), dim3(1024), 0, s, b->d_sims, b->d_count, b->d_start, b->d_ncount, flag,
+                       R);
+    L.end();
+    L.begin(K_SCATTER);
+    hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(tpb), 0, s, nt, b->d_key, b->d_start, b->d_rank, b->d_perm, flag,
+                       R);
+    L.end();
+  }
   L.begin(K_REORDER);
   hipLaunchKernelGGL(k_reorder<1>, dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_cell_sim, b->d_key, b->d_start,
-                     b->d_ncount, b->d_perm, state_ref(b, 0), state_ref(b, 1), b->d_tag[0], b->d_tag[1],
-                     b->d_pos4, b->d_pfix, b->d_pbuild, b->d_slot_cell, flag, R);
+                     b->d_ncount, whole ? b->d_bucket : b->d_perm, whole ? b->bucket_cap : 0u, state_ref(b, 0),
+                     state_ref(b, 1), b->d_tag[0], b->d_tag[1], b->d_pos4, b->d_pfix, b->d_pbuild, b->d_slot_cell,
+                     flag, R);
   L.end();
   L.begin(K_LIST);
   launch_build(b, s, flag, R, state_ref(b, 1), state_ref(b, 0), b->d_tag[1], b->d_tag[0], 0);
@@ -583,6 +592,20 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
         (rc = dalloc(ctx, &b->d_slot_cell, b->ntot)) || (rc = dalloc(ctx, &b->d_nlist, b->ntot)) ||
         (rc = dalloc(ctx, &b->d_list, int64_t(b->list_cap) * b->list_ld)))
       return fail(rc);
+    // buckets of the sort: twice a system's mean cell and some (a fuller cell
+    // is handled, slowly); a system without atoms would be left unscanned
+    bool all = true;
+    double mean = 0.0;
+    for (const SimDev& D : b->sims) {
+      all = all && D.nf > 0;
+      mean = std::max(mean, double(D.nf) / double(D.ncell));
+    }
+    if (all) {
+      b->bucket_cap = 8u * uint32_t(std::ceil((2.0 * mean + 16.0) / 8.0));
+      if ((rc = dalloc(ctx, &b->d_bucket, b->ncell * int64_t(b->bucket_cap))) || (rc = dalloc(ctx, &b->d_done, n)))
+        return fail(rc);
+      HMD_HIP(ctx, hipMemsetAsync(b->d_done, 0, sizeof(int) * n, ctx->stream));
+    }
     // screening reads whole blocks past the end of a range
     if (b->path == 2 && (rc = dalloc(ctx, &b->d_pos4, b->ntot + b->nwall + SCREEN_PAD))) return fail(rc);
   }
@@ -733,7 +756,7 @@ void batch_free(hmd_batch* b) {
   for (auto e : b->ev) (void)hipEventDestroy(e);
   void* ptrs[] = {b->d_sims, b->d_atom_sim, b->d_cell_sim, b->d_f4, b->d_pos4, b->d_pfix, b->d_pbuild,
                   b->d_slot_cell, b->d_list, b->d_nlist, b->d_flag, b->d_key, b->d_count, b->d_rank, b->d_start,
-                  b->d_ncount, b->d_perm, b->d_wpos4, b->d_wstart, b->d_wcount, b->d_dstate, b->d_tag[0],
+                  b->d_ncount, b->d_perm, b->d_bucket, b->d_done, b->d_wpos4, b->d_wstart, b->d_wcount, b->d_dstate, b->d_tag[0],
                   b->d_tag[1], b->d_accbuf, b->d_status, b->acc.pairs, b->d_cellmap, b->d_tiles,
                   b->d_tilerec, b->d_tbins, b->d_gam, b->d_sout, b->d_stamps};
   for (void* p : ptrs)

@@ -27,15 +27,18 @@ __global__ void k_integrate(int ntot, const SimDev* sims, const uint16_t* atom_s
                             int* flag, Acc acc, const int64_t* dstate, StepRef R, StepConst K);
 __global__ void k_keys(int ntot, const SimDev* sims, const uint16_t* atom_sim, StateRef st, uint32_t* key,
                        uint32_t* count, uint32_t* rank, const int* flag, StepRef R);
+__global__ void k_sort(int ntot, const SimDev* sims, const uint16_t* atom_sim, StateRef st, uint32_t* key,
+                       uint32_t* count, uint32_t* bucket, uint32_t cap, uint32_t* start, uint32_t* ncount, int* done,
+                       const int* flag, StepRef R);
 __global__ void k_scan(const SimDev* sims, uint32_t* count, uint32_t* start, uint32_t* ncount, const int* flag,
                        StepRef R);
 __global__ void k_scatter(int ntot, const uint32_t* key, const uint32_t* start, const uint32_t* rank, uint32_t* perm,
                           const int* flag, StepRef R);
 template <int PATH>
 __global__ void k_reorder(int ntot, const SimDev* sims, const uint16_t* cell_sim, const uint32_t* key,
-                          const uint32_t* start, const uint32_t* ncount, const uint32_t* perm, StateRef src,
-                          StateRef dst, const int* tag_src, int* tag_dst, float4* pos4, int4* pfix, int4* pbuild,
-                          uint32_t* slot_cell, const int* flag, StepRef R);
+                          const uint32_t* start, const uint32_t* ncount, const uint32_t* perm, uint32_t cap,
+                          StateRef src, StateRef dst, const int* tag_src, int* tag_dst, float4* pos4, int4* pfix,
+                          int4* pbuild, uint32_t* slot_cell, const int* flag, StepRef R);
 __global__ void k_build_list(int ntot, int ld, int cap, const SimDev* sims, const uint16_t* atom_sim,
                              const uint32_t* slot_cell, const int4* pfix, const uint32_t* start,
                              const uint32_t* ncount, const uint32_t* wstart, const uint32_t* wcount, uint32_t* list,

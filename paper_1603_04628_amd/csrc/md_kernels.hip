@@ -89,7 +89,11 @@ __device__ __forceinline__ int xcd_block() {
 }
 
 __device__ __forceinline__ bool rebuild_needed(const int* flag, const StepRef& R) {
-  return flag == nullptr || flag[(step_n(R) + 1) & 1] != 0;
+  if (flag == nullptr) return true;
+  // both parities' flags and the step index are requested together: one
+  // memory latency, not two, on the steps that stop here
+  const int2 f = *reinterpret_cast<const int2*>(flag);
+  return (((step_n(R) + 1) & 1) ? f.y : f.x) != 0;
 }
 
 // Arrival rank of each lane's key inside its cell: lanes of a wave with the
@@ -121,8 +125,7 @@ __device__ __forceinline__ void rank_in_cell(bool valid, uint32_t c, uint32_t* _
 // all threads call it): the block counts its own atoms per cell in an LDS
 // table, then takes one global atomic per distinct cell -- all in parallel,
 // where the wavefront version takes one per cell in turn.
-__device__ __forceinline__ void rank_in_cell_block(bool valid, uint32_t c, uint32_t* __restrict__ count,
-                                                   uint32_t* __restrict__ rank, int i) {
+__device__ __forceinline__ uint32_t rank_in_cell_block(bool valid, uint32_t c, uint32_t* __restrict__ count) {
   constexpr uint32_t H = 256, EMPTY = 0xffffffffu;
   __shared__ uint32_t hkey[H], hcnt[H], hbase[H];
   const uint32_t tid = threadIdx.x;
@@ -141,7 +144,7 @@ __device__ __forceinline__ void rank_in_cell_block(bool valid, uint32_t c, uint3
   for (uint32_t k = tid; k < H; k += blockDim.x)
     if (hkey[k] != EMPTY) hbase[k] = atomicAdd(&count[hkey[k]], hcnt[k]);
   __syncthreads();
-  if (valid) rank[i] = hbase[h] + local;
+  return valid ? hbase[h] + local : 0u;
 }
 
 }  // namespace
@@ -234,15 +237,13 @@ __global__ __launch_bounds__(256) void k_integrate(int ntot, const SimDev* __res
   else body(sl);
 }
 
-// Pair path: cell keys of the current positions on rebuild steps.
-__global__ __launch_bounds__(256) void k_keys(int ntot, const SimDev* __restrict__ sims,
-                                              const uint16_t* __restrict__ atom_sim, StateRef st,
-                                              uint32_t* __restrict__ key, uint32_t* __restrict__ count,
-                                              uint32_t* __restrict__ rank, const int* __restrict__ flag, StepRef R) {
-  if (!rebuild_needed(flag, R)) return;
-  const int i = xcd_block() * blockDim.x + threadIdx.x;
-  const bool valid = i < ntot;
-  uint32_t c = 0;
+// Pair path: the cell of every slot and its arrival rank there, on rebuild
+// steps.
+__device__ __forceinline__ uint32_t cell_and_rank(int i, bool valid, const SimDev* __restrict__ sims,
+                                                  const uint16_t* __restrict__ atom_sim, const StateRef& st,
+                                                  uint32_t* __restrict__ key, uint32_t* __restrict__ count,
+                                                  uint32_t& c) {
+  c = 0;
   auto cell_of = [&](const int s) {
     const SimDev& D = sims[s];
     const int cx = dcell(st.x[i], D.inv_x, D.nx);
@@ -258,7 +259,103 @@ __global__ __launch_bounds__(256) void k_keys(int ntot, const SimDev* __restrict
     c = cell_of(sl);
   }
   if (valid) key[i] = c;
-  rank_in_cell_block(valid, c, count, rank, i);
+  return rank_in_cell_block(valid, c, count);
+}
+
+// Exclusive scan of a system's cell counts into slot offsets by one workgroup,
+// eight cells a thread and round; clears the counts for the next sort.  The
+// counts may have been added to by any workgroup of this launch.
+__device__ __forceinline__ void scan_system(const SimDev& D, uint32_t* __restrict__ count,
+                                            uint32_t* __restrict__ start, uint32_t* __restrict__ ncount) {
+  constexpr int U = 8;
+  __shared__ uint32_t wave_tot[256 / WAVE];
+  const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+  uint32_t carry = uint32_t(D.a0);
+  for (int base = 0; base < D.ncell; base += U * int(blockDim.x)) {
+    const int c0 = base + U * int(threadIdx.x);
+    uint32_t n[U], sum = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      n[u] = c0 + u < D.ncell
+                 ? __hip_atomic_load(&count[D.c0 + c0 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                 : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum += n[u];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const uint32_t t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
+    }
+    if (lane == WAVE - 1) wave_tot[wid] = incl;
+    __syncthreads();
+    uint32_t at = carry + incl - sum;
+    for (int w = 0; w < nw; ++w) {
+      const uint32_t t = wave_tot[w];
+      if (w < wid) at += t;
+      carry += t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c0 + u < D.ncell) {
+        start[D.c0 + c0 + u] = at;
+        ncount[D.c0 + c0 + u] = n[u];
+        count[D.c0 + c0 + u] = 0u;
+        at += n[u];
+      }
+  }
+}
+
+// Pair path, first half of the sort (rebuild steps): every slot goes into its
+// cell's bucket at its arrival rank (ranks past the bucket's capacity are left
+// to k_reorder); the workgroup that finishes a system's last slots (counted by
+// done[], no workgroup waits) scans that system's cells.  A launch inside a
+// graph costs 2.5 to 4.5 us even where it exits at once, so this one and the
+// bucket form of k_reorder do the work of k_keys, k_scan, k_scatter and
+// k_reorder.
+__global__ __launch_bounds__(256) void k_sort(int ntot, const SimDev* __restrict__ sims,
+                                              const uint16_t* __restrict__ atom_sim, StateRef st,
+                                              uint32_t* __restrict__ key, uint32_t* __restrict__ count,
+                                              uint32_t* __restrict__ bucket, uint32_t cap,
+                                              uint32_t* __restrict__ start, uint32_t* __restrict__ ncount,
+                                              int* __restrict__ done, const int* __restrict__ flag, StepRef R) {
+  if (!rebuild_needed(flag, R)) return;
+  __shared__ int last;
+  const int bd = blockDim.x, blk = xcd_block(), i = blk * bd + int(threadIdx.x);
+  const bool valid = i < ntot;
+  uint32_t c;
+  const uint32_t rk = cell_and_rank(i, valid, sims, atom_sim, st, key, count, c);
+  if (valid && rk < cap) bucket[size_t(c) * cap + rk] = uint32_t(i);
+  // systems of this workgroup's slots (every system has slots)
+  const int s0 = atom_sim[blk * bd], s1 = atom_sim[min(blk * bd + bd, ntot) - 1];
+  for (int s = s0; s <= s1; ++s) {
+    const SimDev& D = sims[s];
+    // what the scanning workgroup needs of the others are their additions to
+    // count: atomics whose results came back before this barrier, read there
+    // by atomic loads.  No device-wide fence, which writes back the whole L2
+    // (300 us a sort of 2.1 M atoms)
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&done[s], 1) == (D.a0 + D.nf - 1) / bd - D.a0 / bd;
+    __syncthreads();
+    if (!last) continue;
+    if (threadIdx.x == 0) done[s] = 0;
+    scan_system(D, count, start, ncount);
+  }
+}
+
+// Pair path: cell keys of the current positions on rebuild steps (steps whose
+// kernels are timed one by one).
+__global__ __launch_bounds__(256) void k_keys(int ntot, const SimDev* __restrict__ sims,
+                                              const uint16_t* __restrict__ atom_sim, StateRef st,
+                                              uint32_t* __restrict__ key, uint32_t* __restrict__ count,
+                                              uint32_t* __restrict__ rank, const int* __restrict__ flag, StepRef R) {
+  if (!rebuild_needed(flag, R)) return;
+  const int i = xcd_block() * blockDim.x + threadIdx.x;
+  const bool valid = i < ntot;
+  uint32_t c;
+  const uint32_t rk = cell_and_rank(i, valid, sims, atom_sim, st, key, count, c);
+  if (valid) rank[i] = rk;
 }
 
 // scan: one block per system; exclusive scan of the per-cell counts into
@@ -324,34 +421,43 @@ __global__ __launch_bounds__(256) void k_scatter(int ntot, const uint32_t* __res
 // of the previous order by cell.  Copies the FP64 state and the id.  The cell
 // path writes FP32 cell-relative positions; the pair path writes fixed-point
 // positions (also the reference for the displacement test) and the cell of
-// every new slot.
+// every new slot.  A cell's members are in perm at its slots (cap 0) or in
+// its bucket of cap entries; a cell with more members than that counts its
+// smaller slots over the keys of the whole system.
 template <int PATH>
 __global__ __launch_bounds__(256) void k_reorder(int ntot, const SimDev* __restrict__ sims,
                                                  const uint16_t* __restrict__ cell_sim,
                                                  const uint32_t* __restrict__ key, const uint32_t* __restrict__ start,
                                                  const uint32_t* __restrict__ ncount,
-                                                 const uint32_t* __restrict__ perm, StateRef src, StateRef dst,
-                                                 const int* __restrict__ tag_src, int* __restrict__ tag_dst,
-                                                 float4* __restrict__ pos4, int4* __restrict__ pfix,
-                                                 int4* __restrict__ pbuild, uint32_t* __restrict__ slot_cell,
-                                                 const int* __restrict__ flag, StepRef R) {
+                                                 const uint32_t* __restrict__ perm, uint32_t cap, StateRef src,
+                                                 StateRef dst, const int* __restrict__ tag_src,
+                                                 int* __restrict__ tag_dst, float4* __restrict__ pos4,
+                                                 int4* __restrict__ pfix, int4* __restrict__ pbuild,
+                                                 uint32_t* __restrict__ slot_cell, const int* __restrict__ flag,
+                                                 StepRef R) {
   if (!rebuild_needed(flag, R)) return;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= ntot) return;
-  const uint32_t p = perm[j];
+  const uint32_t p = cap ? uint32_t(j) : perm[j];
   const uint32_t c = key[p];
   const uint32_t st = start[c], n = ncount[c];
   // eight of the cell's entries in flight at a time (one at a time, each
   // waited for, made this loop the kernel's cost)
   uint32_t rank = 0, m = 0;
-  for (; m + 8 <= n; m += 8) {
-    uint32_t e[8];
+  if (cap && n > cap) {
+    const SimDev& D = sims[cell_sim[c]];
+    for (uint32_t q = uint32_t(D.a0); q < p; ++q) rank += key[q] == c ? 1u : 0u;
+  } else {
+    const uint32_t* const cell = perm + (cap ? size_t(c) * cap : size_t(st));
+    for (; m + 8 <= n; m += 8) {
+      uint32_t e[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) e[u] = perm[st + m + u];
+      for (int u = 0; u < 8; ++u) e[u] = cell[m + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) rank += e[u] < p ? 1u : 0u;
+      for (int u = 0; u < 8; ++u) rank += e[u] < p ? 1u : 0u;
+    }
+    for (; m < n; ++m) rank += cell[m] < p ? 1u : 0u;
   }
-  for (; m < n; ++m) rank += perm[st + m] < p ? 1u : 0u;
   const uint32_t d = st + rank;
   const double x = src.x[p], y = src.y[p], z = src.z[p];
   dst.x[d] = x; dst.y[d] = y; dst.z[d] = z;
@@ -1749,11 +1855,11 @@ HMD_INST_INTEGRATE(1, 0)
 HMD_INST_INTEGRATE(0, 1)
 HMD_INST_INTEGRATE(1, 1)
 template __global__ void k_reorder<0>(int, const SimDev*, const uint16_t*, const uint32_t*, const uint32_t*,
-                                      const uint32_t*, const uint32_t*, StateRef, StateRef, const int*, int*,
-                                      float4*, int4*, int4*, uint32_t*, const int*, StepRef);
+                                      const uint32_t*, const uint32_t*, uint32_t, StateRef, StateRef, const int*,
+                                      int*, float4*, int4*, int4*, uint32_t*, const int*, StepRef);
 template __global__ void k_reorder<1>(int, const SimDev*, const uint16_t*, const uint32_t*, const uint32_t*,
-                                      const uint32_t*, const uint32_t*, StateRef, StateRef, const int*, int*,
-                                      float4*, int4*, int4*, uint32_t*, const int*, StepRef);
+                                      const uint32_t*, const uint32_t*, uint32_t, StateRef, StateRef, const int*,
+                                      int*, float4*, int4*, int4*, uint32_t*, const int*, StepRef);
 template __global__ void k_force_cell<0>(int, const SimDev*, const uint16_t*, const float4*, const uint32_t*,
                                          const uint32_t*, const float4*, const uint32_t*, const uint32_t*, float4*,
                                          StateRef, Acc, int64_t*, StepRef, StepConst);

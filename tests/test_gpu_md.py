@@ -104,6 +104,33 @@ def test_cell_sort_is_stable(path):
             assert np.all(np.diff(rank1[sub]) > 0), (c, oc)
 
 
+@pytest.mark.parametrize("path", [1, 2])
+@pytest.mark.parametrize("n_in", [40, 56, 57, 100])
+def test_sort_of_crowded_cells(n_in, path):
+    # a cell up to, at and past its bucket (56 entries here): members complete
+    # and in their old order, every other cell too
+    ctx, g_sys, o_sys = _pair(6.0, 0.02, 9, path, **SMALL_L)
+    x, v = g_sys.get_state()
+    cell1, _, order1 = (a.astype(np.int64) for a in g_sys.cells())
+    rank1 = np.empty_like(order1)
+    rank1[order1] = np.arange(len(order1))
+    inside = np.all((x > 0.05) & (x < 2.7), axis=1)
+    x[inside] += 2.9  # out of the first cell
+    pick = np.random.default_rng(n_in).choice(len(x), n_in, replace=False)
+    grid = np.stack(np.meshgrid(*[np.arange(5) * 0.5 + 0.3] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x[pick] = grid[:n_in]
+    g_sys.set_state(x, v)
+    cell, cnt, order = (a.astype(np.int64) for a in g_sys.cells())
+    assert np.array_equal(np.bincount(cell, minlength=len(cnt)), cnt)
+    assert cnt[cell[pick[0]]] >= n_in and np.all(cell[pick] == cell[pick[0]])
+    start = np.concatenate([[0], np.cumsum(cnt)[:-1]])
+    for c in np.nonzero(cnt)[0]:  # cells are reported row by row, not in slot order: one old cell at a time
+        m = order[start[c]:start[c] + cnt[c]]
+        assert np.array_equal(np.sort(m), np.nonzero(cell == c)[0])
+        for oc in np.unique(cell1[m]):
+            assert np.all(np.diff(rank1[m[cell1[m] == oc]]) > 0), (c, oc)
+
+
 @pytest.mark.parametrize("h,skin,cell_w,params", [
     (3.0, 0.3, 0.0, SMALL_L),  # one cell between the walls: every range of a column
     (5.0, 0.25, 0.0, LARGE),   # thin and wide: columns on both sides of an origin block
