@@ -116,6 +116,13 @@ struct Launcher {
   }
 };
 
+TileBuild tile_build(hmd_batch* b, StateRef from, StateRef to, const int* tag_from, int* tag_to, int global_out) {
+  const float rl2 = float((b->P.rc + b->skin) * (b->P.rc + b->skin));
+  return {b->list_cap, b->d_tiles,  b->d_sims,  b->d_slot_cell, b->d_pfix,    b->d_pos4, b->d_start,
+          b->d_ncount, b->d_wstart, b->d_wcount, b->d_list,     b->d_nlist,   b->d_tilerec, from,
+          to,          tag_from,    tag_to,      b->d_flag + 2, rl2,          global_out || b->force_gather ? 1 : 0};
+}
+
 // Pair-list build (after a reorder into `from`: the build copies the state
 // back into `to`; from == to copies nothing).
 void launch_build(hmd_batch* b, hipStream_t s, const int* flag, StepRef R, StateRef from, StateRef to,
@@ -123,12 +130,8 @@ void launch_build(hmd_batch* b, hipStream_t s, const int* flag, StepRef R, State
   const int nt = int(b->ntot), tpb = b->tpb, nb = blocks_for(nt, tpb);
   const float rl2 = float((b->P.rc + b->skin) * (b->P.rc + b->skin));
   if (b->path == 2) {
-    hipLaunchKernelGGL(b->uniform ? k_build_tiles<1> : k_build_tiles<0>, dim3(b->ntiles), dim3(TILE_THREADS), 0,
-                       s, nt,
-                       b->list_ld, b->list_cap, b->d_tiles, b->d_sims, b->d_slot_cell, b->d_pfix, b->d_pos4,
-                       b->d_start, b->d_ncount, b->d_wstart, b->d_wcount, b->d_list, b->d_nlist,
-                       b->d_tilerec, from, to, tag_from, tag_to, b->d_flag + 2, flag, R, rl2,
-                       global_out || b->force_gather ? 1 : 0);
+    hipLaunchKernelGGL(b->uniform ? k_build_tiles<1> : k_build_tiles<0>, dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt,
+                       b->list_ld, tile_build(b, from, to, tag_from, tag_to, global_out), flag, R);
     return;
   }
   hipLaunchKernelGGL(k_build_list, dim3(nb), dim3(tpb), 0, s, nt, b->list_ld, b->list_cap, b->d_sims,
@@ -136,8 +139,9 @@ void launch_build(hmd_batch* b, hipStream_t s, const int* flag, StepRef R, State
                      b->d_list, b->d_nlist, from, to, tag_from, tag_to, b->d_flag + 2, flag, R, rl2);
 }
 
-// Counting sort of the current state by cell (flag null: unconditional).
-void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag, StepRef R) {
+// Counting sort of the current state by cell (flag null: unconditional), and
+// unless left to the caller the pair lists.
+void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag, StepRef R, bool with_list = true) {
   hipStream_t s = L.s;
   const int nt = int(b->ntot), tpb = b->tpb, nb = blocks_for(nt, tpb);
   if (b->path == 0) {
@@ -189,9 +193,11 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
                      state_ref(b, 1), b->d_tag[0], b->d_tag[1], b->d_pos4, b->d_pfix, b->d_pbuild, b->d_slot_cell,
                      flag, R);
   L.end();
-  L.begin(K_LIST);
-  launch_build(b, s, flag, R, state_ref(b, 1), state_ref(b, 0), b->d_tag[1], b->d_tag[0], 0);
-  L.end();
+  if (with_list) {
+    L.begin(K_LIST);
+    launch_build(b, s, flag, R, state_ref(b, 1), state_ref(b, 0), b->d_tag[1], b->d_tag[0], 0);
+    L.end();
+  }
 }
 
 // Pair-path force kernels by variant index ((mode 2 + energy) 2 + uniform
@@ -224,6 +230,17 @@ decltype(&k_force_list<0, 0, 0, 0, 0>) force_list_variant(int v, bool pr) {
 #undef HMD_V
 #undef HMD_VP
 
+// List and force kernels of a step by variant index ((uniform 2 + walls) 2 +
+// pressure) 2 + narrow tiles.
+decltype(&k_list_force<0, 0, 0, 0>) list_force_variant(int v) {
+  static const decltype(&k_list_force<0, 0, 0, 0>) tab[16] = {
+      &k_list_force<0, 0, 0, 0>, &k_list_force<0, 0, 0, 1>, &k_list_force<0, 0, 1, 0>, &k_list_force<0, 0, 1, 1>,
+      &k_list_force<0, 1, 0, 0>, &k_list_force<0, 1, 0, 1>, &k_list_force<0, 1, 1, 0>, &k_list_force<0, 1, 1, 1>,
+      &k_list_force<1, 0, 0, 0>, &k_list_force<1, 0, 0, 1>, &k_list_force<1, 0, 1, 0>, &k_list_force<1, 0, 1, 1>,
+      &k_list_force<1, 1, 0, 0>, &k_list_force<1, 1, 0, 1>, &k_list_force<1, 1, 1, 0>, &k_list_force<1, 1, 1, 1>};
+  return tab[v];
+}
+
 void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, StepRef R) {
   const int nt = int(b->ntot), tpb = b->tpb, nb = blocks_for(nt, tpb);
   const int src = b->cur;
@@ -251,6 +268,8 @@ void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, St
   }
 }
 
+constexpr int kResidentTiles = 1024;
+
 // One velocity-Verlet step over the whole batch.
 void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
   hipStream_t s = L.s;
@@ -265,6 +284,19 @@ void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
                        state_ref(b, 0), b->d_f4, b->d_key, b->d_count, b->d_rank, b->d_pfix, b->d_pbuild, b->d_flag,
                        b->acc, b->d_dstate, R, K);
   L.end();
+  // lists and forces in one launch where all tiles are resident at once (four
+  // per compute unit): it saves a launch of 2.5 to 4 us, but asks for the
+  // rebuild flag in every workgroup, one after another on a compute unit once
+  // there are more (39,189 atoms 1.75 -> 1.69 ms for 40 steps with results;
+  // 2.1 M atoms in 9,660 tiles 17.9 -> 18.3 ms)
+  if (b->path == 2 && b->ntiles <= kResidentTiles && !L.spans && !L.marks && !K.energy_on) {
+    enqueue_sort(b, L, K, b->d_flag, R, false);
+    const int v = (b->uniform ? 8 : 0) + (b->walls_same ? 4 : 0) + (K.press_on ? 2 : 0) + (b->narrow ? 1 : 0);
+    hipLaunchKernelGGL(list_force_variant(v), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
+                       tile_build(b, state_ref(b, 1), state_ref(b, 0), b->d_tag[1], b->d_tag[0], 0), b->d_flag, b->d_f4,
+                       state_ref(b, 0), b->acc, b->d_dstate, R, K);
+    return;
+  }
   enqueue_sort(b, L, K, b->path == 0 ? nullptr : b->d_flag, R);
   L.begin(K_FORCE);
   enqueue_force(b, s, 1, K, R);

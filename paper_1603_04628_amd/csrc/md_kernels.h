@@ -73,13 +73,27 @@ __host__ __device__ inline double cell_origin(int c, double w) {
 // 32-bit words of a tile's range table, kept in memory from one list build
 // to the next
 constexpr int TILE_REC = 49;
+// What the tiled list build takes.
+struct TileBuild {
+  int cap;
+  const int4* tiles;
+  const SimDev* sims;
+  const uint32_t* slot_cell;
+  const int4* pfix;
+  const float4* pos4;
+  const uint32_t *start, *ncount, *wstart, *wcount;
+  uint32_t *list, *nlist, *tilerec;
+  StateRef from, to;
+  const int* tag_from;
+  int *tag_to, *overflow;
+  float rl2;
+  int global_out;
+};
 template <int UNI>
-__global__ void k_build_tiles(int ntot, int ld, int cap, const int4* tiles, const SimDev* sims,
-                              const uint32_t* slot_cell, const int4* pfix, const float4* pos4, const uint32_t* start,
-                              const uint32_t* ncount, const uint32_t* wstart, const uint32_t* wcount,
-                              uint32_t* list, uint32_t* nlist, uint32_t* tilerec, StateRef from, StateRef to,
-                              const int* tag_from, int* tag_to, int* overflow, const int* flag, StepRef R,
-                              float rl2, int global_out);
+__global__ void k_build_tiles(int ntot, int ld, TileBuild A, const int* flag, StepRef R);
+template <int UNI, int WS, int PR, int SPLIT>
+__global__ void k_list_force(int ntot, int ld, TileBuild A, const int* flag, float4* f4, StateRef st, Acc acc,
+                             int64_t* dstate, StepRef R, StepConst K);
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __global__ void k_force_tiles(int ntot, int ld, const uint32_t* tilerec, const SimDev* sims, const int4* pfix,
                               const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,

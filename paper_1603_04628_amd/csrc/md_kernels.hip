@@ -1010,10 +1010,10 @@ constexpr int TILE_RUNS = 18;  // kind (fluid, lower wall, upper wall) x 3 slabs
 
 
 // List build: LDS buffers of a wavefront.
-constexpr int BUILD_ROW = 128;              // list entries of an atom gathered in LDS
-constexpr int BUILD_PITCH = BUILD_ROW + 8;  // 16-byte aligned rows on different banks
+constexpr int BUILD_ROW = 104;              // list entries of an atom gathered in LDS: 16-byte aligned rows,
+                                            // their starts on different banks
 constexpr int BUILD_PART = 128;             // candidates screened together
-constexpr int BUILD_MASKS = 9;              // hit masks of an atom group between two expansions
+constexpr int BUILD_MASKS = 7;              // hit masks of an atom group between two expansions
 constexpr int BUILD_MAX_NY = WAVE;          // cells of a column looked up by one wavefront
 
 struct TileStage {
@@ -1025,6 +1025,26 @@ struct TileStage {
   uint32_t mode;                // 0: lists of LDS indices; 1: of position indices (LDS too small)
 };
 static_assert(sizeof(TileStage) == TILE_REC * sizeof(uint32_t), "tile record layout");
+
+// LDS of a tile's workgroup: the list build's buffers, then the force's
+// staged positions.
+struct BuildLds {
+  alignas(16) uint16_t rowbuf[TILE_TPB / WAVE][16][BUILD_ROW];
+  uint32_t masks[TILE_TPB / WAVE][BUILD_MASKS][WAVE];
+  float4 blocks[TILE_TPB / WAVE][BUILD_PART];
+  // LDS index of each neighbourhood cell's first atom (<< 8) and its count,
+  // by (slab, column offset, y + 1): the candidate loop then reads no cell
+  // tables from memory
+  uint32_t ctab[TILE_CTAB];
+  int tab_ok;
+};
+struct ForceLds {
+  int lx[TILE_STAGE], ly[TILE_STAGE], lz[TILE_STAGE];
+};
+union TileLds {
+  BuildLds build;
+  ForceLds force;
+};
 
 // Column pieces of x0 - 1 .. x0 + ncol with periodic wrap (one piece covers
 // the whole row when the range would meet itself).
@@ -1224,7 +1244,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D, const float4* __restrict__ pos4,
                                             const uint32_t* ctab, int ncolx, int nyt, bool whole, float rl2,
                                             int ld, int cap, uint32_t* __restrict__ list,
-                                            uint32_t* __restrict__ nlist, uint16_t (*rowbuf)[BUILD_PITCH],
+                                            uint32_t* __restrict__ nlist, uint16_t (*rowbuf)[BUILD_ROW],
                                             uint32_t (*masks)[WAVE], float4* blk, int* __restrict__ overflow) {
   const int lane = threadIdx.x & (WAVE - 1), nwave = blockDim.x / WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), ncol = __builtin_amdgcn_readfirstlane(T.ncol);
@@ -1424,24 +1444,14 @@ __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D,
 // 255 atoms) cell by cell, one thread per atom.  Other tiles, and every tile
 // with global_out, get 32-bit position indices (the layout of k_build_list).
 template <int UNI>
-__global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(
-    int ntot, int ld, int cap, const int4* __restrict__ tiles, const SimDev* __restrict__ sims,
+__device__ __forceinline__ void build_tile(
+    BuildLds& B, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles, const SimDev* __restrict__ sims,
     const uint32_t* __restrict__ slot_cell, const int4* __restrict__ pfix, const float4* __restrict__ pos4,
     const uint32_t* __restrict__ start, const uint32_t* __restrict__ ncount, const uint32_t* __restrict__ wstart, const uint32_t* __restrict__ wcount,
     uint32_t* __restrict__ list, uint32_t* __restrict__ nlist, uint32_t* __restrict__ tilerec, StateRef from,
     StateRef to, const int* __restrict__ tag_from,
-    int* __restrict__ tag_to, int* __restrict__ overflow, const int* __restrict__ flag, StepRef R, float rl2,
-    int global_out) {
-  if (!rebuild_needed(flag, R)) return;
-  __shared__ __align__(16) uint16_t rowbuf[TILE_TPB / WAVE][16][BUILD_PITCH];
-  __shared__ uint32_t masks[TILE_TPB / WAVE][BUILD_MASKS][WAVE];
-  __shared__ float4 blocks[TILE_TPB / WAVE][BUILD_PART];
-  __shared__ TileStage T;
-  // LDS index of each neighbourhood cell's first atom (<< 8) and its count,
-  // by (slab, column offset, y + 1): the candidate loop then reads no cell
-  // tables from memory
-  __shared__ uint32_t ctab[TILE_CTAB];
-  __shared__ int tab_ok;
+    int* __restrict__ tag_to, int* __restrict__ overflow, float rl2, int global_out) {
+  uint32_t* const ctab = B.ctab;
   const int t = xcd_block();
   tile_ranges(tiles[t], ntot, sims, start, ncount, wstart, wcount, T);
   const uint32_t total = T.off[TILE_RUNS];
@@ -1456,7 +1466,7 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(
   const int ncolx = whole ? D.nx : T.ncol + 2, nyt = D.ny + 2;
   bool use_tab = local && D.ny <= BUILD_MAX_NY && 3 * ncolx * nyt <= TILE_CTAB;
   if (use_tab) {
-    if (threadIdx.x == 0) tab_ok = 1;
+    if (threadIdx.x == 0) B.tab_ok = 1;
     __syncthreads();
     for (int e = threadIdx.x; e < 3 * ncolx * nyt; e += blockDim.x) {
       const int si = e / (ncolx * nyt), xi = (e / nyt) % ncolx, jy = e % nyt - 1;
@@ -1477,11 +1487,11 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(
         cn = wcount[wc];
       }
       const int run = kind * 6 + si * 2 + piece;
-      if (cn > 255u) tab_ok = 0;
+      if (cn > 255u) B.tab_ok = 0;
       ctab[e] = ((T.off[run] + (cb - T.gb[run])) << 8) | (cn > 255u ? 255u : cn);
     }
     __syncthreads();
-    use_tab = tab_ok != 0;
+    use_tab = B.tab_ok != 0;
   }
   const float rl2u = UNI ? rl2 * D.inv_u2 : rl2;  // in fixed-point units squared with UNI
   const bool copy = from.x != to.x;  // a rebuild outside the step sequence copies nothing
@@ -1492,8 +1502,8 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(
       tag_to[i] = tag_from[i];
     }
   if (use_tab) {
-    tile_screen(T, D, pos4, ctab, ncolx, nyt, whole, rl2, ld, cap, list, nlist, rowbuf[threadIdx.x / WAVE],
-                masks[threadIdx.x / WAVE], blocks[threadIdx.x / WAVE], overflow);
+    tile_screen(T, D, pos4, ctab, ncolx, nyt, whole, rl2, ld, cap, list, nlist, B.rowbuf[threadIdx.x / WAVE],
+                B.masks[threadIdx.x / WAVE], B.blocks[threadIdx.x / WAVE], overflow);
     return;
   }
   for (uint32_t i = T.home0 + threadIdx.x; i < T.home1; i += blockDim.x) {
@@ -1589,6 +1599,22 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(
   }
 }
 
+template <int UNI>
+__device__ __forceinline__ void build_tile(BuildLds& B, TileStage& T, int ntot, int ld, const TileBuild& A) {
+  build_tile<UNI>(B, T, ntot, ld, A.cap, A.tiles, A.sims, A.slot_cell, A.pfix, A.pos4, A.start, A.ncount, A.wstart,
+                  A.wcount, A.list, A.nlist, A.tilerec, A.from, A.to, A.tag_from, A.tag_to, A.overflow, A.rl2,
+                  A.global_out);
+}
+
+template <int UNI>
+__global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(int ntot, int ld, TileBuild A,
+                                                             const int* __restrict__ flag, StepRef R) {
+  if (!rebuild_needed(flag, R)) return;
+  __shared__ BuildLds B;
+  __shared__ TileStage T;
+  build_tile<UNI>(B, T, ntot, ld, A);
+}
+
 // The value of lane ^ M within groups of four lanes.
 template <int M>
 __device__ __forceinline__ float quad_xor(float v) {
@@ -1600,12 +1626,11 @@ __device__ __forceinline__ float quad_xor(float v) {
 // half-kick and the sample of the step.
 template <int MODE, int ENERGY, int UNI, int WS, int PR, int SPLIT>
 __device__ __forceinline__ void force_tiles(
-    int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
+    ForceLds& F, TileStage& T, int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list,
     const uint32_t* __restrict__ nlist, float4* __restrict__ f4, StateRef st, Acc acc,
     int64_t* __restrict__ dstate, StepRef R, StepConst K) {
-  __shared__ int lx[TILE_STAGE], ly[TILE_STAGE], lz[TILE_STAGE];
-  __shared__ TileStage T;
+  int *const lx = F.lx, *const ly = F.ly, *const lz = F.lz;
   __shared__ unsigned long long tbin[BIN_LDS];
   const int t = xcd_block();
   const int64_t nstep = step_n(R) + 1;  // the step this launch completes
@@ -1823,14 +1848,37 @@ __global__ __launch_bounds__(TILE_TPB) void k_force_tiles(
     int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 0>(ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
+  __shared__ ForceLds F;
+  __shared__ TileStage T;
+  force_tiles<MODE, ENERGY, UNI, WS, PR, 0>(F, T, ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
 }
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __global__ __launch_bounds__(TILE_TPB) void k_force_narrow(
     int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 1>(ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
+  __shared__ ForceLds F;
+  __shared__ TileStage T;
+  force_tiles<MODE, ENERGY, UNI, WS, PR, 1>(F, T, ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
+}
+
+// A step's list build and forces in one launch, for batches whose tiles are
+// all resident: a tile's forces need its own lists only, and the separate
+// build costs a launch (2.5 to 4 us) on every step, of which one in six or
+// seven has something to build.
+template <int UNI, int WS, int PR, int SPLIT>
+__global__ __launch_bounds__(TILE_TPB, 4) void k_list_force(int ntot, int ld, TileBuild A,
+                                                            const int* __restrict__ flag, float4* __restrict__ f4,
+                                                            StateRef st, Acc acc, int64_t* __restrict__ dstate,
+                                                            StepRef R, StepConst K) {
+  __shared__ TileLds L;
+  __shared__ TileStage T;
+  if (rebuild_needed(flag, R)) {
+    build_tile<UNI>(L.build, T, ntot, ld, A);
+    __syncthreads();
+  }
+  force_tiles<1, 0, UNI, WS, PR, SPLIT>(L.force, T, ntot, ld, A.tilerec, A.sims, A.pfix, A.list, A.nlist, f4, st, acc,
+                                        dstate, R, K);
 }
 
 // One timestamp of the device's constant-rate wall clock (timed graph
@@ -1866,14 +1914,16 @@ template __global__ void k_force_cell<0>(int, const SimDev*, const uint16_t*, co
 template __global__ void k_force_cell<1>(int, const SimDev*, const uint16_t*, const float4*, const uint32_t*,
                                          const uint32_t*, const float4*, const uint32_t*, const uint32_t*, float4*,
                                          StateRef, Acc, int64_t*, StepRef, StepConst);
-template __global__ void k_build_tiles<0>(int, int, int, const int4*, const SimDev*, const uint32_t*,
-                                          const int4*, const float4*, const uint32_t*, const uint32_t*, const uint32_t*,
-                                          const uint32_t*, uint32_t*, uint32_t*, uint32_t*, StateRef, StateRef,
-                                          const int*, int*, int*, const int*, StepRef, float, int);
-template __global__ void k_build_tiles<1>(int, int, int, const int4*, const SimDev*, const uint32_t*,
-                                          const int4*, const float4*, const uint32_t*, const uint32_t*, const uint32_t*,
-                                          const uint32_t*, uint32_t*, uint32_t*, uint32_t*, StateRef, StateRef,
-                                          const int*, int*, int*, const int*, StepRef, float, int);
+template __global__ void k_build_tiles<0>(int, int, TileBuild, const int*, StepRef);
+template __global__ void k_build_tiles<1>(int, int, TileBuild, const int*, StepRef);
+#define HMD_LIST_FORCE(U, W, PR, S)                                                                       \
+  template __global__ void k_list_force<U, W, PR, S>(int, int, TileBuild, const int*, float4*, StateRef, Acc, \
+                                                     int64_t*, StepRef, StepConst);
+#define HMD_LIST_FORCE_PS(U, W) \
+  HMD_LIST_FORCE(U, W, 0, 0) HMD_LIST_FORCE(U, W, 0, 1) HMD_LIST_FORCE(U, W, 1, 0) HMD_LIST_FORCE(U, W, 1, 1)
+HMD_LIST_FORCE_PS(0, 0) HMD_LIST_FORCE_PS(0, 1) HMD_LIST_FORCE_PS(1, 0) HMD_LIST_FORCE_PS(1, 1)
+#undef HMD_LIST_FORCE_PS
+#undef HMD_LIST_FORCE
 
 #define HMD_FORCE_TILES(M, E, U, W, PR)                                                                \
   template __global__ void k_force_tiles<M, E, U, W, PR>(int, int, const uint32_t*, const SimDev*,            \

@@ -172,6 +172,31 @@ def test_lists_shared_by_lanes(h, cell_w):
     assert pe == pytest.approx(peo, rel=1e-4)
 
 
+@pytest.mark.parametrize("path", [1, 2])
+@pytest.mark.parametrize("heights,pressure", [((6.0,), 0), ((4.0, 9.0, 15.0), 0), ((4.0, 9.0), 1)])
+def test_joined_launches_match_separate_ones(heights, pressure, path):
+    # a step's sort, lists and forces in joined launches, against the separate
+    # launches of timed steps: 60 steps with several rebuilds from one state.
+    # The same FP32 pair forces up to the rounding of fused multiply-adds
+    # (1e-7), which 60 steps of 0.005 amplify to well below 1e-4
+    out = []
+    for timed in (False, True):
+        ctx = hmd.Context(hmd.Params(force_path=path, skin=SKIN, pressure=pressure, n_equil=20, **SMALL_L))
+        b = hmd.Batch(ctx, [(h, 0.02, 7, 40) for h in heights])
+        b.set_timing(timed)
+        b.run(60, graph_chunk=20 if not timed else 0)
+        out.append([b.get_state(k)[0] for k in range(len(heights))] + [b.series(k) for k in range(len(heights))])
+        if timed:
+            assert b.kernel_ms("scan")[1] == 60
+    n = len(heights)
+    for k in range(n):
+        d = out[0][k] - out[1][k]
+        L = omd.System(heights[k], 0.02, 7, omd.Params(**SMALL_L)).Lx
+        d -= L * np.round(d / L)
+        assert np.abs(d).max() <= 1e-4, k
+        np.testing.assert_allclose(out[0][n + k], out[1][n + k], rtol=0, atol=1e-4)
+
+
 @pytest.mark.parametrize("path", PATHS)
 def test_pair_counts(path):
     # ordered fluid pairs and wall pairs inside the cut-off, counted directly;
