@@ -120,7 +120,7 @@ struct hmd_batch {
   int64_t nser = 1;
   int ser_B = 1 << 30, ser_r = 0;
   double* d_gam = nullptr;   // [S * nser] autocovariances (results)
-  double* d_sout = nullptr;  // [S * 4] mean, SE, half means (results)
+  double* d_sout = nullptr;  // [S * 8] mean, SE, half means (results): of the fluxes, then of the pressures
   int path = 1;           // 0 cell path, 1 pair path
   int tpb = 256;          // threads per block of the per-slot kernels
   double skin = 0.3;
@@ -174,7 +174,11 @@ struct hmd_batch {
   int64_t* d_dstate = nullptr;      // [0] steps done at a graph's start, [3] Berendsen factor pending
   hmd::Acc acc{};
   double* d_accbuf = nullptr;
+  int64_t small_n = 0;              // its leading words that batch_results reads (Acc's per-system sums,
+                                    // d_sout, d_flag, d_status)
   int* d_status = nullptr;
+  void* h_stage = nullptr;          // pinned host memory for downloads
+  size_t stage_bytes = 0;
 
   int cur = 0;  // cell path: which state copy is current (pair path: always 0)
   int64_t done = 0;

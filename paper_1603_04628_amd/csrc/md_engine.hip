@@ -316,9 +316,8 @@ int forces_now(hmd_batch* b, bool energy) {
   hipStream_t s = ctx->stream;
   StepConst K = step_const(b, b->thermo_on, energy);
   const int p = int((b->done + 1) & 1);
-  HMD_HIP(ctx, hipMemsetAsync(b->acc.pe[p], 0, sizeof(double) * b->S, s));
-  HMD_HIP(ctx, hipMemsetAsync(b->acc.ke[p], 0, sizeof(double) * b->S, s));
-  HMD_HIP(ctx, hipMemsetAsync(b->acc.pairs, 0, kPairCounters * kPairPitch * sizeof(unsigned long long), s));
+  hipLaunchKernelGGL(k_clear_sums, dim3(1), dim3(256), 0, s, b->acc.pe[p], b->acc.ke[p], b->S, b->acc.pairs,
+                     kPairCounters * kPairPitch);
   enqueue_force(b, s, 0, K, StepRef{nullptr, b->done});
   HMD_HIP(ctx, hipGetLastError());
   return HMD_OK;
@@ -614,7 +613,6 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
       (rc = dalloc(ctx, &b->d_wpos4, b->nwall)) || (rc = dalloc(ctx, &b->d_wstart, b->nwcell)) ||
       (rc = dalloc(ctx, &b->d_wcount, b->nwcell)) || (rc = dalloc(ctx, &b->d_dstate, 4)) ||
       (rc = dalloc(ctx, &b->d_tag[0], b->ntot)) || (rc = dalloc(ctx, &b->d_tag[1], b->ntot)) ||
-      (rc = dalloc(ctx, &b->d_flag, 4)) ||
       (rc = dalloc(ctx, &b->d_stamps, kMaxStamps)))
     return fail(rc);
   if (b->path == 0) {
@@ -669,19 +667,27 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   HMD_HIP(ctx, hipMemcpyAsync(b->d_cellmap, b->cell_rank.data(), 4 * b->ncell, hipMemcpyHostToDevice, ctx->stream));
   HMD_HIP(ctx, hipMemcpyAsync(b->d_cellmap + b->ncell, cell_lin.data(), 4 * b->ncell, hipMemcpyHostToDevice,
                               ctx->stream));
-  const int64_t nacc = 6 * int64_t(n) + 2 * int64_t(n) * b->nser + 3 * int64_t(n) + 2 * b->nbins;
-  if ((rc = dalloc(ctx, &b->d_accbuf, nacc)) || (rc = dalloc(ctx, &b->d_status, n)) ||
-      (rc = dalloc(ctx, &b->acc.pairs, kPairCounters * kPairPitch)) || (rc = dalloc(ctx, &b->d_sout, 4 * int64_t(n))))
+  // per-system sums: what the results read first, in one piece (energies,
+  // temperature sums, series statistics, flags and status), then the series
+  // and the profile
+  b->small_n = 17 * int64_t(n) + (n + 5) / 2;
+  const int64_t nacc = b->small_n + 2 * int64_t(n) * b->nser + 2 * b->nbins;
+  if ((rc = dalloc(ctx, &b->d_accbuf, nacc)) ||
+      (rc = dalloc(ctx, &b->acc.pairs, kPairCounters * kPairPitch)))
     return fail(rc);
   if (b->n_sample > 0 && b->P.n_blocks == 0 && (rc = dalloc(ctx, &b->d_gam, int64_t(n) * b->nser)))
     return fail(rc);
   double* q = b->d_accbuf;
   for (int p = 0; p < 2; ++p) { b->acc.vc2[p] = q; q += n; }
-  for (int p = 0; p < 2; ++p) { b->acc.pe[p] = q; q += n; }
   for (int p = 0; p < 2; ++p) { b->acc.ke[p] = q; q += n; }
+  for (int p = 0; p < 2; ++p) { b->acc.pe[p] = q; q += n; }
+  b->acc.tsum = q; q += 3 * int64_t(n);
+  b->d_sout = q; q += 8 * int64_t(n);
+  b->d_flag = reinterpret_cast<int*>(q);
+  b->d_status = b->d_flag + 4;
+  q = b->d_accbuf + b->small_n;
   b->acc.blocks = q; q += int64_t(n) * b->nser;
   b->acc.pblocks = q; q += int64_t(n) * b->nser;
-  b->acc.tsum = q; q += 3 * int64_t(n);
   b->acc.binvx = q; q += b->nbins;
   b->acc.bincnt = q;
   b->acc.tbins = b->d_tbins;
@@ -769,9 +775,7 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   for (int a = 0; a < 6; ++a)
     if ((rc = up(b->d_state[0][a], hs[a].data(), 8 * b->ntot))) return fail(rc);
   HMD_HIP(ctx, hipMemsetAsync(b->d_accbuf, 0, sizeof(double) * nacc, s));
-  HMD_HIP(ctx, hipMemsetAsync(b->d_status, 0, sizeof(int) * n, s));
   HMD_HIP(ctx, hipMemsetAsync(b->d_count, 0, 4 * b->ncell, s));
-  HMD_HIP(ctx, hipMemsetAsync(b->d_flag, 0, 4 * sizeof(int), s));
   b->cur = 0;
   StepConst K = step_const(b, true, true);
   sort_now(b, K);
@@ -787,12 +791,13 @@ void batch_free(hmd_batch* b) {
   release_graphs(b);
   for (auto e : b->ev) (void)hipEventDestroy(e);
   void* ptrs[] = {b->d_sims, b->d_atom_sim, b->d_cell_sim, b->d_f4, b->d_pos4, b->d_pfix, b->d_pbuild,
-                  b->d_slot_cell, b->d_list, b->d_nlist, b->d_flag, b->d_key, b->d_count, b->d_rank, b->d_start,
-                  b->d_ncount, b->d_perm, b->d_bucket, b->d_done, b->d_wpos4, b->d_wstart, b->d_wcount, b->d_dstate, b->d_tag[0],
-                  b->d_tag[1], b->d_accbuf, b->d_status, b->acc.pairs, b->d_cellmap, b->d_tiles,
-                  b->d_tilerec, b->d_tbins, b->d_gam, b->d_sout, b->d_stamps};
+                  b->d_slot_cell, b->d_list, b->d_nlist, b->d_key, b->d_count, b->d_rank, b->d_start, b->d_ncount,
+                  b->d_perm, b->d_bucket, b->d_done, b->d_wpos4, b->d_wstart, b->d_wcount, b->d_dstate, b->d_tag[0],
+                  b->d_tag[1], b->d_accbuf, b->acc.pairs, b->d_cellmap, b->d_tiles,
+                  b->d_tilerec, b->d_tbins, b->d_gam, b->d_stamps};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  if (b->h_stage) (void)hipHostFree(b->h_stage);
   for (int w = 0; w < 2; ++w)
     for (int a = 0; a < 6; ++a)
       if (b->d_state[w][a]) (void)hipFree(b->d_state[w][a]);
@@ -912,6 +917,30 @@ int batch_run(hmd_batch* b, int64_t steps, int graph_chunk, bool thermostat, dou
   return HMD_OK;
 }
 
+namespace {
+
+// Pinned host memory of the batch for downloads, at least `bytes` (null: not to
+// be had; its earlier contents are dropped).  A copy into memory of the
+// caller's costs 15 to 25 us of staging each.
+void* stage(hmd_batch* b, size_t bytes) {
+  constexpr size_t kMaxStage = size_t(64) << 20;
+  if (bytes > kMaxStage) return nullptr;
+  if (bytes > b->stage_bytes) {
+    if (b->h_stage) (void)hipHostFree(b->h_stage);
+    b->stage_bytes = 0;
+    const size_t want = std::max<size_t>(bytes, 1 << 16);
+    if (hipHostMalloc(&b->h_stage, want, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      b->h_stage = nullptr;
+      return nullptr;
+    }
+    b->stage_bytes = want;
+  }
+  return b->h_stage;
+}
+
+}  // namespace
+
 int batch_results(hmd_batch* b, hmd_md_result* out) {
   hmd_ctx* ctx = b->ctx;
   HMD_HIP(ctx, hipSetDevice(ctx->device));
@@ -920,23 +949,25 @@ int batch_results(hmd_batch* b, hmd_md_result* out) {
   // the sampling window is complete once every one of its n_sample steps ran
   const bool complete = b->n_sample > 0 && b->done - b->P.n_equil >= b->n_sample;
   hipStream_t s = ctx->stream;
-  std::vector<double> sout(4 * size_t(n)), pout(4 * size_t(n), 0.0), tsum(3 * size_t(n)), pe(n);
-  if (complete && b->P.pressure) {  // the pressure series first: d_sout is reused
-    series_stats_enqueue(s, b->acc.pblocks, n, b->nser, b->nser, 1.0 / double(b->ser_B), b->P.n_blocks,
-                         b->d_gam, b->d_sout);
-    HMD_HIP(ctx, hipMemcpyAsync(pout.data(), b->d_sout, 8 * pout.size(), hipMemcpyDeviceToHost, s));
-  }
+  double* const d_pout = b->d_sout + 4 * size_t(n);
+  if (complete && b->P.pressure)
+    series_stats_enqueue(s, b->acc.pblocks, n, b->nser, b->nser, 1.0 / double(b->ser_B), b->P.n_blocks, b->d_gam,
+                         d_pout);
   if (complete)
     series_stats_enqueue(s, b->acc.blocks, n, b->nser, b->nser, 1.0 / double(b->ser_B), b->P.n_blocks, b->d_gam,
                          b->d_sout);
-  std::vector<int> status(n);
-  int flags[4] = {0, 0, 0, 0};
-  if (complete)
-    HMD_HIP(ctx, hipMemcpyAsync(sout.data(), b->d_sout, 8 * sout.size(), hipMemcpyDeviceToHost, s));
-  HMD_HIP(ctx, hipMemcpyAsync(tsum.data(), b->acc.tsum, 8 * tsum.size(), hipMemcpyDeviceToHost, s));
-  HMD_HIP(ctx, hipMemcpyAsync(pe.data(), b->acc.pe[(b->done + 1) & 1], 8 * size_t(n), hipMemcpyDeviceToHost, s));
-  HMD_HIP(ctx, hipMemcpyAsync(status.data(), b->d_status, 4 * size_t(n), hipMemcpyDeviceToHost, s));
-  HMD_HIP(ctx, hipMemcpyAsync(flags, b->d_flag, sizeof(flags), hipMemcpyDeviceToHost, s));
+  std::vector<double> pageable;
+  double* h = static_cast<double*>(stage(b, 8 * size_t(b->small_n)));
+  if (!h) {
+    pageable.resize(b->small_n);
+    h = pageable.data();
+  }
+  HMD_HIP(ctx, hipMemcpyAsync(h, b->d_accbuf, 8 * size_t(b->small_n), hipMemcpyDeviceToHost, s));
+  auto host = [&](const void* d) { return h + (static_cast<const double*>(d) - b->d_accbuf); };
+  const double *sout = host(b->d_sout), *pout = host(d_pout), *tsum = host(b->acc.tsum),
+               *pe = host(b->acc.pe[(b->done + 1) & 1]);
+  const int* const flags = reinterpret_cast<const int*>(host(b->d_flag));
+  const int* const status = flags + 4;
   HMD_HIP(ctx, hipStreamSynchronize(s));
   HMD_HIP(ctx, hipGetLastError());
   for (int k = 0; k < n; ++k) {
@@ -985,8 +1016,11 @@ int batch_series(hmd_batch* b, int sim, double* q, int64_t* n, int which) {
   if (!q) return HMD_OK;
   HMD_HIP(ctx, hipSetDevice(ctx->device));
   const double* src = which ? b->acc.pblocks : b->acc.blocks;
-  HMD_HIP(ctx, hipMemcpy(q, src + int64_t(sim) * b->nser, 8 * size_t(b->nser), hipMemcpyDeviceToHost));
-  for (int64_t k = 0; k < b->nser; ++k) q[k] /= double(b->ser_B);
+  double* h = static_cast<double*>(stage(b, 8 * size_t(b->nser)));
+  if (!h) h = q;
+  HMD_HIP(ctx, hipMemcpyAsync(h, src + int64_t(sim) * b->nser, 8 * size_t(b->nser), hipMemcpyDeviceToHost, ctx->stream));
+  HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  for (int64_t k = 0; k < b->nser; ++k) q[k] = h[k] / double(b->ser_B);
   return HMD_OK;
 }
 
@@ -1074,22 +1108,33 @@ int batch_set_all_states(hmd_batch* b, const std::vector<std::vector<double>>& x
 int batch_get_state(hmd_batch* b, int sim, double* x, double* v) {
   hmd_ctx* ctx = b->ctx;
   if (sim < 0 || sim >= b->S) return HMD_EINVAL;
-  std::vector<double> hs[6];
-  std::vector<int> tag;
-  HMD_TRY(download_state(b, hs, tag));
   const SimDev& D = b->sims[sim];
-  double lam = 1.0;
-  if (b->pending) {  // the device holds velocities before the last Berendsen factor
-    double vc2 = 0.0;
-    HMD_HIP(ctx, hipMemcpy(&vc2, b->acc.vc2[b->done & 1] + sim, sizeof(double), hipMemcpyDeviceToHost));
-    lam = std::sqrt(1.0 + (b->P.dt / b->P.tau_T) * (b->P.T0 / (vc2 * D.inv_nf) - 1.0));
+  const size_t n = size_t(D.nf), bytes = 8 * (6 * n + 1) + 4 * n;
+  std::vector<char> pageable;
+  char* h = static_cast<char*>(stage(b, bytes));
+  if (!h) {
+    pageable.resize(bytes);
+    h = pageable.data();
   }
-  for (int i = 0; i < D.nf; ++i) {
-    const int64_t g = D.a0 + i;
-    const int id = tag[g];
+  // x y z vx vy vz, the sum behind a Berendsen factor still to come, atom ids
+  double* const hs = reinterpret_cast<double*>(h);
+  int* const tag = reinterpret_cast<int*>(hs + 6 * n + 1);
+  hipStream_t s = ctx->stream;
+  for (int a = 0; a < 6; ++a)
+    if (a < 3 ? x != nullptr : v != nullptr)
+      HMD_HIP(ctx, hipMemcpyAsync(hs + a * n, b->d_state[b->cur][a] + D.a0, 8 * n, hipMemcpyDeviceToHost, s));
+  HMD_HIP(ctx, hipMemcpyAsync(tag, b->d_tag[b->cur] + D.a0, 4 * n, hipMemcpyDeviceToHost, s));
+  if (b->pending)
+    HMD_HIP(ctx, hipMemcpyAsync(hs + 6 * n, b->acc.vc2[b->done & 1] + sim, 8, hipMemcpyDeviceToHost, s));
+  HMD_HIP(ctx, hipStreamSynchronize(s));
+  // the device holds velocities before the last Berendsen factor
+  const double lam =
+      b->pending ? std::sqrt(1.0 + (b->P.dt / b->P.tau_T) * (b->P.T0 / (hs[6 * n] * D.inv_nf) - 1.0)) : 1.0;
+  for (size_t i = 0; i < n; ++i) {
+    const size_t id = size_t(tag[i]);
     for (int a = 0; a < 3; ++a) {
-      if (x) x[3 * id + a] = hs[a][g];
-      if (v) v[3 * id + a] = hs[3 + a][g] * (a == b->P.thermo_axis ? lam : 1.0);
+      if (x) x[3 * id + a] = hs[a * n + i];
+      if (v) v[3 * id + a] = hs[(3 + a) * n + i] * (a == b->P.thermo_axis ? lam : 1.0);
     }
   }
   return HMD_OK;

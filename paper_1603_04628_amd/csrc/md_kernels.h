@@ -106,5 +106,6 @@ __global__ void k_stamp(unsigned long long* slot, const int* flag, StepRef R);
 __global__ void k_set_i64(int64_t* p, int64_t v);
 __global__ void k_add_i64(int64_t* p, int64_t v);
 __global__ void k_set_i32(int* p, int v);
+__global__ void k_clear_sums(double* pe, double* ke, int n, unsigned long long* pairs, int np);
 
 }  // namespace hmd

@@ -1893,6 +1893,10 @@ __global__ void k_stamp(unsigned long long* slot, const int* flag, StepRef R) {
 __global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
 __global__ void k_add_i64(int64_t* p, int64_t v) { *p += v; }
 __global__ void k_set_i32(int* p, int v) { *p = v; }
+__global__ void k_clear_sums(double* pe, double* ke, int n, unsigned long long* pairs, int np) {
+  for (int k = threadIdx.x; k < n; k += blockDim.x) pe[k] = ke[k] = 0.0;
+  for (int k = threadIdx.x; k < np; k += blockDim.x) pairs[k] = 0ull;
+}
 
 #define HMD_INST_INTEGRATE(M, P)                                                                                  \
   template __global__ void k_integrate<M, P>(int, const SimDev*, const uint16_t*, StateRef, const float4*,         \
