@@ -149,7 +149,7 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
     if (!flag && R.base == nullptr && R.k < 0) {  // keys for a sort outside a time step
       hipLaunchKernelGGL((k_integrate<0, 0>), dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim,
                          state_ref(b, src), b->d_f4, b->d_key, b->d_count, b->d_rank, b->d_pfix, b->d_pbuild,
-                         b->d_flag, b->acc, b->d_dstate, StepRef{nullptr, 0}, K);
+                         b->d_flag, b->acc, b->d_dstate, StepRef{nullptr, 0}, K, b->S == 1);
     }
     L.begin(K_SCAN);
     hipLaunchKernelGGL(k_scan, dim3(b->S), dim3(1024), 0, s, b->d_sims, b->d_count, b->d_start, b->d_ncount,
@@ -278,11 +278,11 @@ void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
   if (b->path == 0)
     hipLaunchKernelGGL((k_integrate<1, 0>), dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim,
                        state_ref(b, b->cur), b->d_f4, b->d_key, b->d_count, b->d_rank, b->d_pfix, b->d_pbuild,
-                       b->d_flag, b->acc, b->d_dstate, R, K);
+                       b->d_flag, b->acc, b->d_dstate, R, K, b->S == 1);
   else
     hipLaunchKernelGGL((k_integrate<1, 1>), dim3(nb), dim3(tpb), 0, s, nt, b->d_sims, b->d_atom_sim,
                        state_ref(b, 0), b->d_f4, b->d_key, b->d_count, b->d_rank, b->d_pfix, b->d_pbuild, b->d_flag,
-                       b->acc, b->d_dstate, R, K);
+                       b->acc, b->d_dstate, R, K, b->S == 1);
   L.end();
   // lists and forces in one launch where all tiles are resident at once (four
   // per compute unit): it saves a launch of 2.5 to 4 us, but asks for the

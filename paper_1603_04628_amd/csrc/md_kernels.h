@@ -24,7 +24,7 @@ struct StepRef {
 template <int MODE, int PATH>
 __global__ void k_integrate(int ntot, const SimDev* sims, const uint16_t* atom_sim, StateRef st, const float4* f4,
                             uint32_t* key, uint32_t* count, uint32_t* rank, int4* pfix, const int4* pbuild,
-                            int* flag, Acc acc, const int64_t* dstate, StepRef R, StepConst K);
+                            int* flag, Acc acc, const int64_t* dstate, StepRef R, StepConst K, int one);
 __global__ void k_keys(int ntot, const SimDev* sims, const uint16_t* atom_sim, StateRef st, uint32_t* key,
                        uint32_t* count, uint32_t* rank, const int* flag, StepRef R);
 __global__ void k_sort(int ntot, const SimDev* sims, const uint16_t* atom_sim, StateRef st, uint32_t* key,

@@ -50,6 +50,29 @@ __device__ __forceinline__ T wave_sum(T v) {
   return v;
 }
 
+// FP64 sums on the DPP and scalar lane reads: the LDS exchange of __shfl_xor
+// costs about 130 cycles a step, and a tile ends with up to six sums of six
+// steps one after another (with the range table and the flags requested
+// earlier: the force of 2.1 M atoms 219 -> 210 us).  Whole wavefronts only.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <>
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0xB1>(v);   // lane ^ 1
+  v = dpp_add<0x4E>(v);   // lane ^ 2
+  v = dpp_add<0x141>(v);  // lane ^ 7
+  v = dpp_add<0x140>(v);  // lane ^ 15
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
 // True when every active lane of the wave holds the same system index.
 __device__ __forceinline__ bool wave_uniform(int s) {
   const int s0 = __shfl(s, 0);
@@ -164,7 +187,7 @@ __global__ __launch_bounds__(256) void k_integrate(int ntot, const SimDev* __res
                                                    uint32_t* __restrict__ count, uint32_t* __restrict__ rank,
                                                    int4* __restrict__ pfix, const int4* __restrict__ pbuild,
                                                    int* __restrict__ flag, Acc acc, const int64_t* __restrict__ dstate,
-                                                   StepRef R, StepConst K) {
+                                                   StepRef R, StepConst K, int one) {
   const int i = xcd_block() * blockDim.x + threadIdx.x;
   const bool valid = i < ntot;
   // The step of one atom for system s.  A wavefront whose atoms all belong
@@ -179,9 +202,10 @@ __global__ __launch_bounds__(256) void k_integrate(int ntot, const SimDev* __res
       v[0] = st.vx[i]; v[1] = st.vy[i]; v[2] = st.vz[i];
     }
     if (MODE == 1) {
-      const int64_t n = step_n(R);  // steps completed before this one
+      const double w0 = acc.vc2[0][s], w1 = acc.vc2[1][s];  // both, before the step's parity is known
+      const int64_t n = step_n(R);                          // steps completed before this one
       if (valid && dstate[3] != 0) {
-        const double Tc = ((n & 1) ? acc.vc2[1] : acc.vc2[0])[s] * D.inv_nf;
+        const double Tc = ((n & 1) ? w1 : w0) * D.inv_nf;
         const double lam = sqrt(1.0 + K.dt_tau * (K.T0 / Tc - 1.0));
         v[0] *= K.axis == 0 ? lam : 1.0;
         v[1] *= K.axis == 1 ? lam : 1.0;
@@ -232,8 +256,9 @@ __global__ __launch_bounds__(256) void k_integrate(int ntot, const SimDev* __res
     }
     rank_in_cell(valid, c, count, rank, i);
   };
-  const int sl = valid ? int(atom_sim[i]) : 0;
-  if (wave_uniform(valid ? sl : -1)) body(__builtin_amdgcn_readfirstlane(sl));
+  int sl = 0;
+  if (!one && valid) sl = int(atom_sim[i]);  // one: a single system, known without a look
+  if (one || wave_uniform(valid ? sl : -1)) body(__builtin_amdgcn_readfirstlane(sl));
   else body(sl);
 }
 
@@ -1172,11 +1197,11 @@ __device__ __forceinline__ void tile_stage(const TileStage& T, const int4* __res
   });
 }
 
-// Range table of a tile as the last list build left it (the cell ranges only
-// change when the cells are rebuilt, and every rebuild runs the list build).
-__device__ __forceinline__ void tile_load(const uint32_t* __restrict__ rec, TileStage& T) {
-  if (threadIdx.x < TILE_REC) reinterpret_cast<uint32_t*>(&T)[threadIdx.x] = rec[threadIdx.x];
-  __syncthreads();
+// This thread's word of a tile's range table as the last list build left it
+// (the cell ranges only change when the cells are rebuilt, and every rebuild
+// runs the list build).
+__device__ __forceinline__ uint32_t tile_word(const uint32_t* tilerec) {
+  return threadIdx.x < TILE_REC ? tilerec[size_t(xcd_block()) * TILE_REC + threadIdx.x] : 0u;
 }
 
 // NB blocks of 16 candidates against 16 atoms: the sign bits of r^2 - r_l^2,
@@ -1626,7 +1651,7 @@ __device__ __forceinline__ float quad_xor(float v) {
 // half-kick and the sample of the step.
 template <int MODE, int ENERGY, int UNI, int WS, int PR, int SPLIT>
 __device__ __forceinline__ void force_tiles(
-    ForceLds& F, TileStage& T, int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
+    ForceLds& F, TileStage& T, uint32_t rec, int ntot, int ld, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list,
     const uint32_t* __restrict__ nlist, float4* __restrict__ f4, StateRef st, Acc acc,
     int64_t* __restrict__ dstate, StepRef R, StepConst K) {
@@ -1636,9 +1661,11 @@ __device__ __forceinline__ void force_tiles(
   const int64_t nstep = step_n(R) + 1;  // the step this launch completes
   const bool sampled = MODE == 1 && sampled_step(nstep, K);
   const bool bins = sampled && K.bins_on;
-  if (bins)
-    for (int k = threadIdx.x; k < BIN_LDS; k += blockDim.x) tbin[k] = 0ull;
-  tile_load(tilerec + size_t(t) * TILE_REC, T);  // ends with a barrier
+  // (cleared in any case: whether the step takes bins is known one memory
+  // latency later)
+  for (int k = threadIdx.x; k < BIN_LDS; k += blockDim.x) tbin[k] = 0ull;
+  if (threadIdx.x < TILE_REC) reinterpret_cast<uint32_t*>(&T)[threadIdx.x] = rec;
+  __syncthreads();
   const bool local = T.mode == 0;
   const int s = __builtin_amdgcn_readfirstlane(T.s);  // one system per tile
   const SimDev& D = sims[s];
@@ -1850,7 +1877,8 @@ __global__ __launch_bounds__(TILE_TPB) void k_force_tiles(
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
   __shared__ ForceLds F;
   __shared__ TileStage T;
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 0>(F, T, ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
+  force_tiles<MODE, ENERGY, UNI, WS, PR, 0>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
+                                            dstate, R, K);
 }
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __global__ __launch_bounds__(TILE_TPB) void k_force_narrow(
@@ -1859,7 +1887,8 @@ __global__ __launch_bounds__(TILE_TPB) void k_force_narrow(
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
   __shared__ ForceLds F;
   __shared__ TileStage T;
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 1>(F, T, ntot, ld, tilerec, sims, pfix, list, nlist, f4, st, acc, dstate, R, K);
+  force_tiles<MODE, ENERGY, UNI, WS, PR, 1>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
+                                            dstate, R, K);
 }
 
 // A step's list build and forces in one launch, for batches whose tiles are
@@ -1873,11 +1902,13 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_list_force(int ntot, int ld, Ti
                                                             StepRef R, StepConst K) {
   __shared__ TileLds L;
   __shared__ TileStage T;
+  uint32_t rec = tile_word(A.tilerec);  // requested with the flag, read again after a build
   if (rebuild_needed(flag, R)) {
     build_tile<UNI>(L.build, T, ntot, ld, A);
     __syncthreads();
+    rec = tile_word(A.tilerec);
   }
-  force_tiles<1, 0, UNI, WS, PR, SPLIT>(L.force, T, ntot, ld, A.tilerec, A.sims, A.pfix, A.list, A.nlist, f4, st, acc,
+  force_tiles<1, 0, UNI, WS, PR, SPLIT>(L.force, T, rec, ntot, ld, A.sims, A.pfix, A.list, A.nlist, f4, st, acc,
                                         dstate, R, K);
 }
 
@@ -1901,7 +1932,7 @@ __global__ void k_clear_sums(double* pe, double* ke, int n, unsigned long long* 
 #define HMD_INST_INTEGRATE(M, P)                                                                                  \
   template __global__ void k_integrate<M, P>(int, const SimDev*, const uint16_t*, StateRef, const float4*,         \
                                              uint32_t*, uint32_t*, uint32_t*, int4*, const int4*, int*, Acc,       \
-                                             const int64_t*, StepRef, StepConst);
+                                             const int64_t*, StepRef, StepConst, int);
 HMD_INST_INTEGRATE(0, 0)
 HMD_INST_INTEGRATE(1, 0)
 HMD_INST_INTEGRATE(0, 1)
