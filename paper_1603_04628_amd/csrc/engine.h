@@ -156,7 +156,6 @@ struct hmd_batch {
   double* d_tbins = nullptr;        // tiled path: profile bins per tile (Acc::tbins)
   std::vector<int> tile_first;      // tiled path: first tile of each system (S + 1 entries)
   int ntiles = 0, stage_cap = 0;    // tiles; LDS capacity in atoms
-  bool narrow = false;              // tiles of at most half a workgroup's atoms: lists shared by lanes
   uint32_t* d_nlist = nullptr;
   int* d_flag = nullptr;            // [2] rebuild flags by step parity, list overflow, builds so far
   uint32_t* d_key = nullptr;        // global cell of each slot

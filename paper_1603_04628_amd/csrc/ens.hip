@@ -179,7 +179,8 @@ __global__ __launch_bounds__(1024) void k_ens_local(int N, int H, const float* _
         h1[4 * t + 1] = tanhf(wx.y * x0 + wy.y * x1 + c.y);
         h1[4 * t + 2] = tanhf(wx.z * x0 + wy.z * x1 + c.z);
         h1[4 * t + 3] = tanhf(wx.w * x0 + wy.w * x1 + c.w);
-        *reinterpret_cast<float4*>(ha + pt * EP + i) = make_float4(h1[4 * t], h1[4 * t + 1], h1[4 * t + 2], h1[4 * t + 3]);
+        *reinterpret_cast<float4*>(ha + pt * EP + i) =
+            make_float4(h1[4 * t], h1[4 * t + 1], h1[4 * t + 2], h1[4 * t + 3]);
         z[t] = f32x4{d.x, d.y, d.z, d.w};
       }
 #pragma unroll

@@ -214,11 +214,10 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
       HMD_V(K, 0, 1, 0, 0), HMD_V(K, 0, 1, 0, 1), HMD_V(K, 0, 1, 1, 0), HMD_V(K, 0, 1, 1, 1),           \
       HMD_V(K, 1, 0, 0, 0), HMD_V(K, 1, 0, 0, 1), HMD_V(K, 1, 0, 1, 0), HMD_V(K, 1, 0, 1, 1),           \
       HMD_V(K, 1, 1, 0, 0), HMD_V(K, 1, 1, 0, 1), HMD_V(K, 1, 1, 1, 0), HMD_V(K, 1, 1, 1, 1)
-decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr, bool narrow) {
-  using Fn = decltype(&k_force_tiles<0, 0, 0, 0, 0>);
-  static const Fn tab[16] = {HMD_VARIANTS(k_force_tiles)}, tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
-  static const Fn ntab[16] = {HMD_VARIANTS(k_force_narrow)}, ntab_pr[8] = {HMD_VARIANTS_PR(k_force_narrow)};
-  return narrow ? (pr ? ntab_pr[v & 7] : ntab[v]) : (pr ? tab_pr[v & 7] : tab[v]);
+decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr) {
+  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_tiles)};
+  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
+  return pr ? tab_pr[v & 7] : tab[v];
 }
 decltype(&k_force_list<0, 0, 0, 0, 0>) force_list_variant(int v, bool pr) {
   static const decltype(&k_force_list<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_list)};
@@ -230,14 +229,12 @@ decltype(&k_force_list<0, 0, 0, 0, 0>) force_list_variant(int v, bool pr) {
 #undef HMD_V
 #undef HMD_VP
 
-// List and force kernels of a step by variant index ((uniform 2 + walls) 2 +
-// pressure) 2 + narrow tiles.
-decltype(&k_list_force<0, 0, 0, 0>) list_force_variant(int v) {
-  static const decltype(&k_list_force<0, 0, 0, 0>) tab[16] = {
-      &k_list_force<0, 0, 0, 0>, &k_list_force<0, 0, 0, 1>, &k_list_force<0, 0, 1, 0>, &k_list_force<0, 0, 1, 1>,
-      &k_list_force<0, 1, 0, 0>, &k_list_force<0, 1, 0, 1>, &k_list_force<0, 1, 1, 0>, &k_list_force<0, 1, 1, 1>,
-      &k_list_force<1, 0, 0, 0>, &k_list_force<1, 0, 0, 1>, &k_list_force<1, 0, 1, 0>, &k_list_force<1, 0, 1, 1>,
-      &k_list_force<1, 1, 0, 0>, &k_list_force<1, 1, 0, 1>, &k_list_force<1, 1, 1, 0>, &k_list_force<1, 1, 1, 1>};
+// List and force kernels of a step by variant index (uniform 2 + walls) 2 +
+// pressure.
+decltype(&k_list_force<0, 0, 0>) list_force_variant(int v) {
+  static const decltype(&k_list_force<0, 0, 0>) tab[8] = {
+      &k_list_force<0, 0, 0>, &k_list_force<0, 0, 1>, &k_list_force<0, 1, 0>, &k_list_force<0, 1, 1>,
+      &k_list_force<1, 0, 0>, &k_list_force<1, 0, 1>, &k_list_force<1, 1, 0>, &k_list_force<1, 1, 1>};
   return tab[v];
 }
 
@@ -257,7 +254,7 @@ void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, St
     const int v = ((mode * 2 + (K.energy_on ? 1 : 0)) * 2 + (b->uniform ? 1 : 0)) * 2 + (b->walls_same ? 1 : 0);
     const bool pr = mode == 1 && K.press_on;
     if (b->path == 2) {
-      hipLaunchKernelGGL(force_tiles_variant(v, pr, b->narrow), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
+      hipLaunchKernelGGL(force_tiles_variant(v, pr), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
                          b->d_tilerec, b->d_sims, b->d_pfix, b->d_list,
                          b->d_nlist, b->d_f4, state_ref(b, 0), b->acc, b->d_dstate, R, K);
     } else {
@@ -268,7 +265,7 @@ void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, St
   }
 }
 
-constexpr int kResidentTiles = 1024;
+constexpr int kResidentTiles = 1280;
 
 // One velocity-Verlet step over the whole batch.
 void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
@@ -284,14 +281,15 @@ void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
                        state_ref(b, 0), b->d_f4, b->d_key, b->d_count, b->d_rank, b->d_pfix, b->d_pbuild, b->d_flag,
                        b->acc, b->d_dstate, R, K, b->S == 1);
   L.end();
-  // lists and forces in one launch where all tiles are resident at once (four
+  // lists and forces in one launch where all tiles are resident at once (five
   // per compute unit): it saves a launch of 2.5 to 4 us, but asks for the
   // rebuild flag in every workgroup, one after another on a compute unit once
-  // there are more (39,189 atoms 1.75 -> 1.69 ms for 40 steps with results;
-  // 2.1 M atoms in 9,660 tiles 17.9 -> 18.3 ms)
+  // there are more (39,189 atoms 1.75 -> 1.69 ms for 40 steps with results,
+  // the density sweep's 1,040 tiles 60 -> 55 us a step; 2.1 M atoms in 9,660
+  // tiles 17.9 -> 18.3 ms)
   if (b->path == 2 && b->ntiles <= kResidentTiles && !L.spans && !L.marks && !K.energy_on) {
     enqueue_sort(b, L, K, b->d_flag, R, false);
-    const int v = (b->uniform ? 8 : 0) + (b->walls_same ? 4 : 0) + (K.press_on ? 2 : 0) + (b->narrow ? 1 : 0);
+    const int v = (b->uniform ? 4 : 0) + (b->walls_same ? 2 : 0) + (K.press_on ? 1 : 0);
     hipLaunchKernelGGL(list_force_variant(v), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
                        tile_build(b, state_ref(b, 1), state_ref(b, 0), b->d_tag[1], b->d_tag[0], 0), b->d_flag, b->d_f4,
                        state_ref(b, 0), b->acc, b->d_dstate, R, K);
@@ -432,7 +430,7 @@ int make_tiles(hmd_batch* b) {
     for (int nc = 1; nc <= D.nx; ++nc) {
       const double atoms = nc * per_col;
       const double staged = 3.0 * std::min(nc + 2, D.nx) * (per_col + 2.0 * wall_col);
-      if (staged > 0.9 * kStageCap && nc > 1) break;
+      if (staged > 0.95 * kStageCap && nc > 1) break;
       const double passes = std::ceil(atoms / TILE_THREADS);
       const double use = atoms / (passes * TILE_THREADS + b->tile_alpha * staged);
       if (use > best_use + 0.02 * (b->tile_alpha > 0.0 ? best_use : 1.0)) {
@@ -458,12 +456,10 @@ int make_tiles(hmd_batch* b) {
   while (widest > 1 && count(widest) < kMinTiles) --widest;
   std::vector<int4> tiles;
   b->tile_first.assign(b->S + 1, 0);
-  b->narrow = true;
   for (int k = 0; k < b->S; ++k) {
     b->tile_first[k] = int(tiles.size());
     const SimDev& D = b->sims[k];
     const int nc = std::min(cols[k], widest), ntx = (D.nx + nc - 1) / nc;
-    if (double(D.nf) * nc > 0.5 * TILE_THREADS * D.nx * D.nz) b->narrow = false;
     for (int z = 0; z < D.nz; ++z)
       for (int t = 0; t < ntx; ++t) {  // columns split as evenly as possible
         const int x0 = int(int64_t(t) * D.nx / ntx), x1 = int(int64_t(t + 1) * D.nx / ntx);
@@ -1018,7 +1014,8 @@ int batch_series(hmd_batch* b, int sim, double* q, int64_t* n, int which) {
   const double* src = which ? b->acc.pblocks : b->acc.blocks;
   double* h = static_cast<double*>(stage(b, 8 * size_t(b->nser)));
   if (!h) h = q;
-  HMD_HIP(ctx, hipMemcpyAsync(h, src + int64_t(sim) * b->nser, 8 * size_t(b->nser), hipMemcpyDeviceToHost, ctx->stream));
+  HMD_HIP(ctx, hipMemcpyAsync(h, src + int64_t(sim) * b->nser, 8 * size_t(b->nser), hipMemcpyDeviceToHost,
+                              ctx->stream));
   HMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
   for (int64_t k = 0; k < b->nser; ++k) q[k] = h[k] / double(b->ser_B);
   return HMD_OK;

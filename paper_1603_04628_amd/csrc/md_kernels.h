@@ -54,12 +54,14 @@ __global__ void k_force_list(int ntot, int ld, const SimDev* sims, const uint16_
                              const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,
                              int64_t* dstate, StepRef R, StepConst K);
 constexpr int TILE_THREADS = 256;  // threads per tile workgroup
-// LDS capacity of a tile in atoms (x, y, z fixed point: 36 KiB, so four
-// workgroups share a compute unit's 160 KiB); a
-// compile-time size lets every LDS read carry its array offset as an immediate
-constexpr int TILE_STAGE = 3072;
+// LDS capacity of a tile in atoms (x, y, z fixed point: 28 KiB, so five
+// workgroups share a compute unit's 160 KiB: force of the 64-channel batch
+// 202 us with 3,072 atoms and four workgroups, 176 us with 2,400 and five,
+// 202 us with 2,112 and six, whose tiles stage too much halo); a compile-time
+// size lets every LDS read carry its array offset as an immediate
+constexpr int TILE_STAGE = 2400;
 // cells of a tile's neighbourhood listed in LDS by the list build
-constexpr int TILE_CTAB = 768;
+constexpr int TILE_CTAB = 512;
 // entries of the screening coordinates the tiled list build may read past
 // the last one (blocks past the end of a range)
 constexpr int SCREEN_PAD = 128;
@@ -91,17 +93,13 @@ struct TileBuild {
 };
 template <int UNI>
 __global__ void k_build_tiles(int ntot, int ld, TileBuild A, const int* flag, StepRef R);
-template <int UNI, int WS, int PR, int SPLIT>
+template <int UNI, int WS, int PR>
 __global__ void k_list_force(int ntot, int ld, TileBuild A, const int* flag, float4* f4, StateRef st, Acc acc,
                              int64_t* dstate, StepRef R, StepConst K);
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __global__ void k_force_tiles(int ntot, int ld, const uint32_t* tilerec, const SimDev* sims, const int4* pfix,
                               const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,
                               int64_t* dstate, StepRef R, StepConst K);
-template <int MODE, int ENERGY, int UNI, int WS, int PR>
-__global__ void k_force_narrow(int ntot, int ld, const uint32_t* tilerec, const SimDev* sims, const int4* pfix,
-                               const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,
-                               int64_t* dstate, StepRef R, StepConst K);
 __global__ void k_stamp(unsigned long long* slot, const int* flag, StepRef R);
 __global__ void k_set_i64(int64_t* p, int64_t v);
 __global__ void k_add_i64(int64_t* p, int64_t v);

@@ -1038,7 +1038,7 @@ constexpr int TILE_RUNS = 18;  // kind (fluid, lower wall, upper wall) x 3 slabs
 constexpr int BUILD_ROW = 104;              // list entries of an atom gathered in LDS: 16-byte aligned rows,
                                             // their starts on different banks
 constexpr int BUILD_PART = 128;             // candidates screened together
-constexpr int BUILD_MASKS = 7;              // hit masks of an atom group between two expansions
+constexpr int BUILD_MASKS = 5;              // hit masks of an atom group between two expansions
 constexpr int BUILD_MAX_NY = WAVE;          // cells of a column looked up by one wavefront
 
 struct TileStage {
@@ -1470,12 +1470,13 @@ __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D,
 // with global_out, get 32-bit position indices (the layout of k_build_list).
 template <int UNI>
 __device__ __forceinline__ void build_tile(
-    BuildLds& B, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles, const SimDev* __restrict__ sims,
-    const uint32_t* __restrict__ slot_cell, const int4* __restrict__ pfix, const float4* __restrict__ pos4,
-    const uint32_t* __restrict__ start, const uint32_t* __restrict__ ncount, const uint32_t* __restrict__ wstart, const uint32_t* __restrict__ wcount,
-    uint32_t* __restrict__ list, uint32_t* __restrict__ nlist, uint32_t* __restrict__ tilerec, StateRef from,
-    StateRef to, const int* __restrict__ tag_from,
-    int* __restrict__ tag_to, int* __restrict__ overflow, float rl2, int global_out) {
+    BuildLds& B, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles,
+    const SimDev* __restrict__ sims, const uint32_t* __restrict__ slot_cell, const int4* __restrict__ pfix,
+    const float4* __restrict__ pos4, const uint32_t* __restrict__ start, const uint32_t* __restrict__ ncount,
+    const uint32_t* __restrict__ wstart, const uint32_t* __restrict__ wcount, uint32_t* __restrict__ list,
+    uint32_t* __restrict__ nlist, uint32_t* __restrict__ tilerec, StateRef from, StateRef to,
+    const int* __restrict__ tag_from, int* __restrict__ tag_to, int* __restrict__ overflow, float rl2,
+    int global_out) {
   uint32_t* const ctab = B.ctab;
   const int t = xcd_block();
   tile_ranges(tiles[t], ntot, sims, start, ncount, wstart, wcount, T);
@@ -1632,7 +1633,7 @@ __device__ __forceinline__ void build_tile(BuildLds& B, TileStage& T, int ntot, 
 }
 
 template <int UNI>
-__global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(int ntot, int ld, TileBuild A,
+__global__ __launch_bounds__(TILE_TPB, 5) void k_build_tiles(int ntot, int ld, TileBuild A,
                                                              const int* __restrict__ flag, StepRef R) {
   if (!rebuild_needed(flag, R)) return;
   __shared__ BuildLds B;
@@ -1640,16 +1641,17 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_build_tiles(int ntot, int ld, T
   build_tile<UNI>(B, T, ntot, ld, A);
 }
 
-// The value of lane ^ M within groups of four lanes.
+// The value of lane ^ M, M one of 1, 2, 7.
 template <int M>
-__device__ __forceinline__ float quad_xor(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), M == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+__device__ __forceinline__ float lane_xor(float v) {
+  constexpr int ctrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : 0x141;
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
 }
 
 // Forces of a tile's atoms from their lists, neighbour positions read from
 // LDS (or gathered, for a tile built with 32-bit indices), then the second
 // half-kick and the sample of the step.
-template <int MODE, int ENERGY, int UNI, int WS, int PR, int SPLIT>
+template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __device__ __forceinline__ void force_tiles(
     ForceLds& F, TileStage& T, uint32_t rec, int ntot, int ld, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list,
@@ -1671,12 +1673,16 @@ __device__ __forceinline__ void force_tiles(
   const SimDev& D = sims[s];
   const double bin_c1 = D.inv_bin / D.fix_y, bin_c0 = D.y_lo * D.inv_bin;  // fixed-point y -> bins
   const uint32_t n_home = T.home1 - T.home0;
-  // SPLIT: a tile of at most half (a quarter) of the workgroup's atoms gives each two
-  // (four) adjacent lanes, which take its list groups in turn: narrow tiles
-  // are those of small batches, whose force time is the latency of one list
-  // (12.2 -> 8.8 us for 2,048 atoms, with the narrower tiles themselves)
-  const uint32_t sh = !SPLIT ? 0u : n_home <= TILE_TPB / 4 ? 2u : n_home <= TILE_TPB / 2 ? 1u : 0u, ways = 1u << sh;
-  const uint32_t part = threadIdx.x & (ways - 1u), own = threadIdx.x >> sh, pass = blockDim.x >> sh;
+  // A pass takes as many atoms as the workgroup has threads; where half of
+  // that or less is left, two, four or eight adjacent lanes take an atom's
+  // list groups in turn (eight groups are always there).  A second pass for
+  // the few atoms by which a tile exceeds the workgroup, and the tiles of
+  // small batches, then cost a fraction of a list's length (tiles of just
+  // under 256 atoms on average: density sweep 41 -> 36 us; 2,048 atoms in 49
+  // tiles 12.2 -> 8.8 us).
+  auto shift_of = [](uint32_t left) {
+    return left > TILE_TPB / 2 ? 0u : left > TILE_TPB / 4 ? 1u : left > TILE_TPB / 8 ? 2u : 3u;
+  };
   // a pass's own positions, velocities, list lengths and first list groups
   // are requested one step ahead: the first pass's during the staging, the
   // next pass's during this one's arithmetic
@@ -1684,8 +1690,8 @@ __device__ __forceinline__ void force_tiles(
   uint32_t n_nx = 0;
   uint4 g_nx = make_uint4(0u, 0u, 0u, 0u);
   double3 v_nx = make_double3(0.0, 0.0, 0.0);
-  auto fetch = [&](uint32_t base) {
-    const uint32_t i = T.home0 + base + own;
+  auto fetch = [&](uint32_t base, uint32_t sh) {
+    const uint32_t own = threadIdx.x >> sh, part = threadIdx.x & ((1u << sh) - 1u), i = T.home0 + base + own;
     if (base + own < n_home) {
       me_nx = pfix[i];
       n_nx = nlist[i];
@@ -1693,7 +1699,8 @@ __device__ __forceinline__ void force_tiles(
       if (MODE == 1) v_nx = make_double3(st.vx[i], st.vy[i], st.vz[i]);
     }
   };
-  fetch(0);
+  uint32_t sh_nx = shift_of(n_home);
+  fetch(0, sh_nx);
   if (local) {
     if (threadIdx.x == 0) {  // the padding slot: half a box from the slab's centre in z
       const uint32_t pad = T.off[TILE_RUNS];
@@ -1708,14 +1715,18 @@ __device__ __forceinline__ void force_tiles(
 #pragma unroll
   for (int q = 0; q < 8; ++q) sums.v[q] = 0.0;
   uint32_t nff = 0, nwf = 0;
-  for (uint32_t base = 0; base < n_home; base += pass) {
+  for (uint32_t base = 0; base < n_home; base += TILE_TPB) {
+    const uint32_t sh = sh_nx, ways = 1u << sh, part = threadIdx.x & (ways - 1u), own = threadIdx.x >> sh;
     const uint32_t i = T.home0 + base + own;
     const bool valid = base + own < n_home;
     const int4 me = me_nx;
     const uint32_t n = n_nx;
     const uint4 g0 = g_nx;
     const double3 v = v_nx;
-    if (base + pass < n_home) fetch(base + pass);
+    if (base + TILE_TPB < n_home) {
+      sh_nx = shift_of(n_home - base - TILE_TPB);
+      fetch(base + TILE_TPB, sh_nx);
+    }
     float fx = 0.f, fy = 0.f, fz = 0.f, pe = 0.f, pw = 0.f;
     if (valid) {
       const uint4* grp = reinterpret_cast<const uint4*>(list) + i;
@@ -1742,22 +1753,27 @@ __device__ __forceinline__ void force_tiles(
         // group g of slot i at byte (g ld + i) 16: a 32-bit offset from the
         // list base (the list is below 4 GiB), no 64-bit address arithmetic
         const char* const list_b = reinterpret_cast<const char*>(list);
-        for (uint32_t g = part; g < full; g += ways) {
-          const uint32_t gn = g + ways < ngrp ? g + ways : g;
-          const uint4 jn = *reinterpret_cast<const uint4*>(list_b + ((__umul24(gn, uint32_t(ld)) + i) << 4));
-          const uint32_t w[4] = {jj.x, jj.y, jj.z, jj.w};
-          read_two(0, w[0]);
+        auto groups = [&](uint32_t first, auto step) {
+          for (uint32_t g = first; g < full; g += step) {
+            const uint32_t gn = g + step < ngrp ? g + step : g;
+            const uint4 jn = *reinterpret_cast<const uint4*>(list_b + ((__umul24(gn, uint32_t(ld)) + i) << 4));
+            const uint32_t w[4] = {jj.x, jj.y, jj.z, jj.w};
+            read_two(0, w[0]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int b = e & 1;
-            if (e < 3) read_two(1 - b, w[e + 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            pair(w[e] & 0xffffu, px[b][0], py[b][0], pz[b][0]);
-            pair(w[e] >> 16, px[b][1], py[b][1], pz[b][1]);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 4; ++e) {
+              const int b = e & 1;
+              if (e < 3) read_two(1 - b, w[e + 1]);
+              __builtin_amdgcn_sched_barrier(0);
+              pair(w[e] & 0xffffu, px[b][0], py[b][0], pz[b][0]);
+              pair(w[e] >> 16, px[b][1], py[b][1], pz[b][1]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            jj = jn;
           }
-          jj = jn;
-        }
+        };
+        // (a loop of its own for whole lists: a run-time stride costs it a tenth)
+        if (sh == 0u) groups(0u, std::integral_constant<uint32_t, 1u>{});
+        else groups(part, ways);
         if (rest && (full & (ways - 1u)) == part) {  // jj holds the partial last group
           const uint32_t w[4] = {jj.x, jj.y, jj.z, jj.w};
 #pragma unroll
@@ -1786,10 +1802,11 @@ __device__ __forceinline__ void force_tiles(
         }
       }
     }
-    if (SPLIT && sh) {  // the lanes of an atom: neighbours within groups of two or four
+    if (sh) {  // the lanes of an atom: neighbours within groups of two, four or eight
       auto total = [&](float& x) {
-        x += quad_xor<1>(x);
-        if (sh == 2u) x += quad_xor<2>(x);
+        x += lane_xor<1>(x);
+        if (sh >= 2u) x += lane_xor<2>(x);
+        if (sh == 3u) x += lane_xor<7>(x);
       };
       total(fx); total(fy); total(fz);
       if (ENERGY) total(pe);
@@ -1867,36 +1884,22 @@ __device__ __forceinline__ void force_tiles(
   }
 }
 
-// Two kernels, so that one lane per atom keeps its own loop (a run-time stride
-// for shared lists cost it up to a tenth of its time); the host takes the
-// narrow one where every tile's share of a system is half a workgroup or less.
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
-__global__ __launch_bounds__(TILE_TPB) void k_force_tiles(
+__global__ __launch_bounds__(TILE_TPB, ENERGY ? 4 : 5) void k_force_tiles(
     int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
   __shared__ ForceLds F;
   __shared__ TileStage T;
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 0>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
-                                            dstate, R, K);
+  force_tiles<MODE, ENERGY, UNI, WS, PR>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
+                                         dstate, R, K);
 }
-template <int MODE, int ENERGY, int UNI, int WS, int PR>
-__global__ __launch_bounds__(TILE_TPB) void k_force_narrow(
-    int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
-    const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
-    float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
-  __shared__ ForceLds F;
-  __shared__ TileStage T;
-  force_tiles<MODE, ENERGY, UNI, WS, PR, 1>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
-                                            dstate, R, K);
-}
-
 // A step's list build and forces in one launch, for batches whose tiles are
 // all resident: a tile's forces need its own lists only, and the separate
 // build costs a launch (2.5 to 4 us) on every step, of which one in six or
 // seven has something to build.
-template <int UNI, int WS, int PR, int SPLIT>
-__global__ __launch_bounds__(TILE_TPB, 4) void k_list_force(int ntot, int ld, TileBuild A,
+template <int UNI, int WS, int PR>
+__global__ __launch_bounds__(TILE_TPB, 5) void k_list_force(int ntot, int ld, TileBuild A,
                                                             const int* __restrict__ flag, float4* __restrict__ f4,
                                                             StateRef st, Acc acc, int64_t* __restrict__ dstate,
                                                             StepRef R, StepConst K) {
@@ -1908,7 +1911,7 @@ __global__ __launch_bounds__(TILE_TPB, 4) void k_list_force(int ntot, int ld, Ti
     __syncthreads();
     rec = tile_word(A.tilerec);
   }
-  force_tiles<1, 0, UNI, WS, PR, SPLIT>(L.force, T, rec, ntot, ld, A.sims, A.pfix, A.list, A.nlist, f4, st, acc,
+  force_tiles<1, 0, UNI, WS, PR>(L.force, T, rec, ntot, ld, A.sims, A.pfix, A.list, A.nlist, f4, st, acc,
                                         dstate, R, K);
 }
 
@@ -1951,24 +1954,18 @@ template __global__ void k_force_cell<1>(int, const SimDev*, const uint16_t*, co
                                          StateRef, Acc, int64_t*, StepRef, StepConst);
 template __global__ void k_build_tiles<0>(int, int, TileBuild, const int*, StepRef);
 template __global__ void k_build_tiles<1>(int, int, TileBuild, const int*, StepRef);
-#define HMD_LIST_FORCE(U, W, PR, S)                                                                       \
-  template __global__ void k_list_force<U, W, PR, S>(int, int, TileBuild, const int*, float4*, StateRef, Acc, \
-                                                     int64_t*, StepRef, StepConst);
-#define HMD_LIST_FORCE_PS(U, W) \
-  HMD_LIST_FORCE(U, W, 0, 0) HMD_LIST_FORCE(U, W, 0, 1) HMD_LIST_FORCE(U, W, 1, 0) HMD_LIST_FORCE(U, W, 1, 1)
-HMD_LIST_FORCE_PS(0, 0) HMD_LIST_FORCE_PS(0, 1) HMD_LIST_FORCE_PS(1, 0) HMD_LIST_FORCE_PS(1, 1)
-#undef HMD_LIST_FORCE_PS
+#define HMD_LIST_FORCE(U, W, PR)                                                                          \
+  template __global__ void k_list_force<U, W, PR>(int, int, TileBuild, const int*, float4*, StateRef, Acc,    \
+                                                  int64_t*, StepRef, StepConst);
+HMD_LIST_FORCE(0, 0, 0) HMD_LIST_FORCE(0, 0, 1) HMD_LIST_FORCE(0, 1, 0) HMD_LIST_FORCE(0, 1, 1)
+HMD_LIST_FORCE(1, 0, 0) HMD_LIST_FORCE(1, 0, 1) HMD_LIST_FORCE(1, 1, 0) HMD_LIST_FORCE(1, 1, 1)
 #undef HMD_LIST_FORCE
 
 #define HMD_FORCE_TILES(M, E, U, W, PR)                                                                \
   template __global__ void k_force_tiles<M, E, U, W, PR>(int, int, const uint32_t*, const SimDev*,            \
                                                          const int4*, const uint32_t*,                         \
                                                          const uint32_t*, float4*, StateRef, Acc, int64_t*,    \
-                                                         StepRef, StepConst);                                  \
-  template __global__ void k_force_narrow<M, E, U, W, PR>(int, int, const uint32_t*, const SimDev*,           \
-                                                          const int4*, const uint32_t*,                        \
-                                                          const uint32_t*, float4*, StateRef, Acc, int64_t*,   \
-                                                          StepRef, StepConst);
+                                                         StepRef, StepConst);
 #define HMD_FORCE_LIST(M, E, U, W, PR)                                                                 \
   template __global__ void k_force_list<M, E, U, W, PR>(int, int, const SimDev*, const uint16_t*, const int4*, \
                                                         const uint32_t*, const uint32_t*, float4*, StateRef, Acc, \

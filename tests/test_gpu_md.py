@@ -155,10 +155,12 @@ def test_tiled_list_build_shapes(h, skin, cell_w, params):
     assert pe == pytest.approx(peo, rel=1e-4)
 
 
-@pytest.mark.parametrize("h,cell_w", [(4.0, 0.0), (9.0, 0.0), (15.0, 0.0), (4.0, 4.0), (8.0, 4.0), (12.0, 4.0)])
+@pytest.mark.parametrize("h,cell_w", [(4.0, 0.0), (9.0, 0.0), (15.0, 0.0), (4.0, 4.0), (8.0, 4.0), (12.0, 4.0),
+                                      (19.0, 4.0), (21.0, 4.0), (24.0, 4.0)])
 def test_lists_shared_by_lanes(h, cell_w):
-    # columns of about 25 to 170 atoms: four, two and one lane per list, with
-    # padded (five slabs) and partial (three slabs) last groups; bounds as above
+    # columns of about 25 to 170 atoms (eight to one lanes per list) and 260 to
+    # 340 (a second pass of few), with padded (four slabs) and partial (three
+    # slabs) last groups; bounds as above
     params = dict(Lx_nom=12.7, Lz_nom=12.7)
     ctx = hmd.Context(hmd.Params(force_path=2, skin=0.3, cell_w=cell_w, **params))
     g_sys, o_sys = hmd.System(ctx, h, 0.02, 9), omd.System(h, 0.02, 9, omd.Params(**params))
