@@ -1312,14 +1312,14 @@ int gp_log_marginal(hmd_gp* g, double* lml) {
 // so the search first evaluates it on a grid of 17 points per chosen
 // parameter, a quarter decade apart over two decades either side of the
 // start, then refines from the best grid point by cyclic line searches over
-// the logarithm of each chosen parameter, bracketed by a factor 10 around the
-// current value, until two cycles gain less than 1e-12 relative (at most 30
-// cycles).
+// the logarithm of each chosen parameter, bracketed at first by a factor 10
+// around the current value and then by 16 times the last cycle's move, until
+// two cycles at the finest bracket gain less than 1e-12 relative.
 //
 // Refits are independent of each other, so a whole grid, or a round of up to
 // 256 points along a line, is one set of launches: a line search closes its
-// bracket by (nb + 1) / 2 per round, five rounds where golden sections took 63
-// refits in turn.  A cycle ends with a search along the way it came, which
+// bracket by (nb + 1) / 2 per round, two rounds where golden sections took 63
+// refits in turn (five rounds with the bracket kept at a factor 10).  A cycle ends with a search along the way it came, which
 // crosses the ridge that sigma_f and ell share (4 cycles instead of 12).  The
 // rounds of a cycle are queued without waiting for the host.  Up to EV_LDS_N
 // points a set is one workgroup; beyond, the panel elimination runs on all
@@ -1435,21 +1435,30 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
   }
   flip = 0;
   HMD_HIP(ctx, hipMemcpyAsync(st_dev, &st, sizeof(st), hipMemcpyHostToDevice, s));
-  const double width = std::log(10.0);
-  const int rounds = int(std::ceil(std::log(2.0 * width / 1e-9) / std::log(0.5 * double(nb + 1))));
+  const double widest = std::log(10.0), finest = 4e-6;
+  // rounds of nb sets that close a bracket by kClose (two of 256)
+  constexpr double kClose = 128.5 * 128.5;
+  const int rounds = int(std::ceil(std::log(kClose) / std::log(0.5 * double(nb + 1)) - 1e-9));
+  double width = widest;
   int settled = 0;  // cycles in a row without gain: two, since the last gains move along a flat ridge
-  for (int cycle = 0; cycle < 30 && settled < 2; ++cycle) {
-    const double start = st.best;
+  for (int cycle = 0; cycle < 75 && settled < 2; ++cycle) {
+    const EvState before = st;
     for (int j = 0; j < (m > 1 ? m + 1 : m); ++j) {
-      const int axis = j < m ? idx[j] : 3;
-      for (int r = 0; r < rounds; ++r) evaluate(line(axis, r, 0, j == 0 ? 1 : 0, nb, width));
-      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, line(axis, rounds, 1, 0, nb, width), par);
+      // the direction of the cycle may lead further than its parts
+      const int axis = j < m ? idx[j] : 3, nr = axis < 3 ? rounds : rounds + (rounds + 1) / 2;
+      const double w = axis < 3 ? width : std::min(widest, 128.0 * width);
+      for (int r = 0; r < nr; ++r) evaluate(line(axis, r, 0, j == 0 ? 1 : 0, nb, w));
+      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, line(axis, nr, 1, 0, nb, w), par);
       flip = 1 - flip;
     }
     HMD_HIP(ctx, hipGetLastError());
     HMD_HIP(ctx, hipMemcpyAsync(&st, st_dev + flip, sizeof(st), hipMemcpyDeviceToHost, s));
     HMD_HIP(ctx, hipStreamSynchronize(s));
-    settled = std::fabs(st.best - start) > 1e-12 * std::fabs(st.best) ? 0 : settled + 1;
+    double move = 0.0;
+    for (int k = 0; k < m; ++k) move = std::max(move, std::fabs(st.x[idx[k]] - before.x[idx[k]]));
+    const bool gain = std::fabs(st.best - before.best) > 1e-12 * std::fabs(st.best);
+    settled = gain || width > finest ? 0 : settled + 1;
+    width = std::min(widest, std::max(finest, gain ? 16.0 * move : width / 64.0));
   }
   if (mask & 1) g->hyp.sigma_f = std::exp(st.x[0]);
   if (mask & 2) g->hyp.ell = std::exp(st.x[1]);
