@@ -515,16 +515,17 @@ __global__ __launch_bounds__(ENS_TPB) void k_ens_adam(int P, int nshare, const f
 
 __global__ void k_ens_tick(int* tbase, int k) { *tbase += k; }
 
-// Prediction, member by member: a wavefront keeps its member's weights in
-// registers as matrix operands and takes 16 queries at a time.  A lane forms
-// the first-layer activations it feeds to the 16 x 16 x 4 instructions (query
-// lane % 16, units 4 k + lane / 16) itself, and the output layer is a sum over
-// 16 lanes, so nothing passes through LDS.  What bounds it is the tanh of two
-// layers (128 per query and member, about 30 instructions each) and the matrix
-// rate: 50,000 queries of 5 members of 64 units took 300 us with W2 in LDS and
-// a lane per unit, and take 65 us.
+// Prediction, member by member: a wavefront keeps its member's hidden layer in
+// registers as matrix operands (the first layer's weights in LDS, which leaves
+// room for three wavefronts a SIMD) and takes 16 queries at a time.  A lane
+// forms the first-layer activations it feeds to the 16 x 16 x 4 instructions
+// (query lane % 16, units 16 t + 4 (lane / 16) + u) itself, and the output
+// layer is a sum over 16 lanes.  What bounds it is the tanh of two layers (128
+// per query and member, about 40 instructions each) and the matrix rate:
+// 50,000 queries of 5 members of 64 units took 300 us with W2 in LDS and a lane
+// per unit, 65 us with all weights in registers and two, 50 us now.
 template <int HT>
-__global__ __launch_bounds__(256) void k_ens_member_out(int m, int H, const float* __restrict__ params,
+__global__ __launch_bounds__(256, 3) void k_ens_member_out(int m, int H, const float* __restrict__ params,
                                                         const double* __restrict__ Xq, double mu0, double mu1,
                                                         double sd0, double sd1, float* __restrict__ yout) {
   const int k = blockIdx.y, lane = threadIdx.x & 63, lr16 = lane & 15, lk = lane >> 4;
@@ -535,13 +536,18 @@ __global__ __launch_bounds__(256) void k_ens_member_out(int m, int H, const floa
   const float* b2 = W2 + H * H;
   const float* W3 = b2 + H;
   const float b3 = W3[H];
-  float w10[4 * HT], w11[4 * HT], c1[4 * HT], w2[HT][4 * HT], c2[HT], w3[HT];
+  constexpr int HP = 16 * HT;
+  __shared__ float4 first[3][HP / 4];  // W1 (x, y), b1
+  for (int i = threadIdx.x; i < HP; i += blockDim.x) {
+    float* const l = reinterpret_cast<float*>(first);
+    l[i] = i < H ? W1[2 * i] : 0.f;
+    l[HP + i] = i < H ? W1[2 * i + 1] : 0.f;
+    l[2 * HP + i] = i < H ? b1[i] : 0.f;
+  }
+  float w2[HT][4 * HT], c2[HT], w3[HT];
 #pragma unroll
   for (int q = 0; q < 4 * HT; ++q) {
-    const int i = 4 * q + lk;
-    w10[q] = i < H ? W1[2 * i] : 0.f;
-    w11[q] = i < H ? W1[2 * i + 1] : 0.f;
-    c1[q] = i < H ? b1[i] : 0.f;
+    const int i = 16 * (q / 4) + 4 * lk + q % 4;
 #pragma unroll
     for (int t = 0; t < HT; ++t) {
       const int o = 16 * t + lr16;
@@ -554,19 +560,28 @@ __global__ __launch_bounds__(256) void k_ens_member_out(int m, int H, const floa
     c2[t] = o < H ? b2[o] : 0.f;
     w3[t] = o < H ? W3[o] : 0.f;
   }
+  __syncthreads();
   const int tiles = (m + 15) / 16, nw = gridDim.x * (blockDim.x / 64);
   for (int tile = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); tile < tiles; tile += nw) {
+    asm volatile("" ::: "memory");  // the first layer stays in LDS (held in registers, it spills others)
     const int qq = min(16 * tile + lr16, m - 1);
     const float x0 = float((Xq[2 * qq] - mu0) / sd0), x1 = float((Xq[2 * qq + 1] - mu1) / sd1);
     f32x4 z[HT];
 #pragma unroll
     for (int t = 0; t < HT; ++t) z[t] = f32x4{c2[t], c2[t], c2[t], c2[t]};
 #pragma unroll
-    for (int q = 0; q < 4 * HT; ++q) {
-      // (a padded unit's zero weights would make a NaN of an infinite query)
-      const float h = 4 * q + lk < H ? tanhf(w10[q] * x0 + w11[q] * x1 + c1[q]) : 0.f;
+    for (int k = 0; k < HT; ++k) {
+      const float4 wx = first[0][4 * k + lk], wy = first[1][4 * k + lk], c = first[2][4 * k + lk];
+      const float a[4] = {wx.x * x0 + wy.x * x1 + c.x, wx.y * x0 + wy.y * x1 + c.y, wx.z * x0 + wy.z * x1 + c.z,
+                          wx.w * x0 + wy.w * x1 + c.w};
 #pragma unroll
-      for (int t = 0; t < HT; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, w2[t][q], z[t], 0, 0, 0);
+      for (int u = 0; u < 4; ++u) {
+        // (a padded unit's zero weights would make a NaN of an infinite query)
+        const float h = 16 * k + 4 * lk + u < H ? tanhf(a[u]) : 0.f;
+#pragma unroll
+        for (int t = 0; t < HT; ++t)
+          z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, w2[t][4 * k + u], z[t], 0, 0, 0);
+      }
     }
     // element u: query 4 lk + u, units 16 t + lr16
 #pragma unroll
