@@ -1238,7 +1238,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // |a|^2 - 2 a.b + (|b|^2 - r_l^2) = r^2 - r_l^2 for 256 pairs, and the sign
 // bits of its four results per lane are the hits (lane 16 q + j: atom j,
 // candidates of quarter q).  The candidates of a block are 256 contiguous
-// bytes of pos4, read from the caches: nothing is staged per tile, and four
+// bytes of pos4, read from the caches: nothing is staged per tile, and five
 // workgroups share a compute unit.
 //
 // Origins: y is taken from mid-channel, x and z from the centre of the cell's
@@ -1258,9 +1258,11 @@ __device__ __forceinline__ void wave_lds_fence() {
 //
 // Measured (64-channel batch, 2.1 M atoms, skin 0.35, one rebuild in six
 // steps): 119 us per step against 147 us for the same kernel testing pair by
-// pair on one lane per atom; 62 against 80 us per rebuild of the 39,189-atom
-// channel.  What bounds it now is the instructions per range and per hit
-// (1,620 vector instructions per 16 atoms, of which the pair tests are 220).
+// pair on one lane per atom, 100 to 113 us with today's narrower tiles; 43
+// against 80 us per rebuild of the 39,189-atom channel.  What bounds it is the
+// instructions per range and per hit (each part run twice: the pair tests 28
+// us of the 113, the expansion of the hits 35, list and state writes 3; the
+// rest sets up ranges).
 //
 // Rounding: with R^2 bounding |a|^2 and |b|^2, ten roundings of terms below
 // 2 R^2 leave r^2 within 1.2e-6 R^2 of exact, so screening at
@@ -1650,7 +1652,9 @@ __device__ __forceinline__ float lane_xor(float v) {
 
 // Forces of a tile's atoms from their lists, neighbour positions read from
 // LDS (or gathered, for a tile built with 32-bit indices), then the second
-// half-kick and the sample of the step.
+// half-kick and the sample of the step.  Bound by VALU issue (23 instructions
+// per list entry) with LDS gathers beside it: 210 us per step of 2.1 M atoms
+// before tiles left room for five workgroups, 176 us since.
 template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __device__ __forceinline__ void force_tiles(
     ForceLds& F, TileStage& T, uint32_t rec, int ntot, int ld, const SimDev* __restrict__ sims,
