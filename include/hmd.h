@@ -78,7 +78,7 @@ typedef struct {
      * capacity (for tests; reported as path 2); -1: the library's tuned
      * choice.  cell_w: minimum cell width (0: rc, or rc + skin for the pair
      * lists).  tile_alpha (tiled path): each system's tiles take the column
-     * count that minimises (padded lanes + tile_alpha x staged atoms) per
+     * count that minimises (lanes + (tile_alpha + 1/4) x staged atoms) per
      * home atom; 0 = fill the lanes, larger values favour wider tiles that
      * stage less halo per atom.  graph_chunk: steps per captured graph of
      * the whole-run calls (even; 0 = 100).  force_path -1 applies what

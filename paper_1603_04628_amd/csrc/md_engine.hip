@@ -416,10 +416,14 @@ int make_tiles(hmd_batch* b) {
   constexpr int kStageCap = TILE_STAGE;
   constexpr int64_t kMinTiles = 512;
   b->stage_cap = kStageCap;
-  // columns per tile: the most home atoms per unit of cost, cost being
-  // the lanes of whole 256-lane passes plus tile_alpha per staged atom
-  // (a wider tile stages less halo per home atom); 2% hysteresis keeps
-  // the narrower of two near-equal choices
+  // columns per tile: the most home atoms per unit of cost, cost being the
+  // lanes of whole 256-lane passes and of a last one (half, a quarter or an
+  // eighth of that where its lists are shared by lanes) plus tile_alpha + 1/4
+  // per staged atom (a wider tile stages less halo per home atom); 2%
+  // hysteresis keeps the narrower of two near-equal choices.  Without the
+  // quarter, and with every pass counted whole: 64-channel batch, force 180
+  // -> 173 us and list build 117 -> 108 us per step (1/2 and 3/4 as good);
+  // density sweep 54 -> 51 us
   std::vector<int> cols(b->S, 1);
   for (int k = 0; k < b->S; ++k) {
     const SimDev& D = b->sims[k];
@@ -431,9 +435,10 @@ int make_tiles(hmd_batch* b) {
       const double atoms = nc * per_col;
       const double staged = 3.0 * std::min(nc + 2, D.nx) * (per_col + 2.0 * wall_col);
       if (staged > 0.95 * kStageCap && nc > 1) break;
-      const double passes = std::ceil(atoms / TILE_THREADS);
-      const double use = atoms / (passes * TILE_THREADS + b->tile_alpha * staged);
-      if (use > best_use + 0.02 * (b->tile_alpha > 0.0 ? best_use : 1.0)) {
+      const double left = std::fmod(atoms, double(TILE_THREADS));
+      const double last = left > 128.0 ? 256.0 : left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : left > 0.0 ? 32.0 : 0.0;
+      const double use = atoms / (atoms - left + last + (b->tile_alpha + 0.25) * staged);
+      if (use > 1.02 * best_use) {
         best_use = use;
         cols[k] = nc;
       }
