@@ -120,7 +120,7 @@ TileBuild tile_build(hmd_batch* b, StateRef from, StateRef to, const int* tag_fr
   const float rl2 = float((b->P.rc + b->skin) * (b->P.rc + b->skin));
   return {b->list_cap, b->d_tiles,  b->d_sims,  b->d_slot_cell, b->d_pfix,    b->d_pos4, b->d_start,
           b->d_ncount, b->d_wstart, b->d_wcount, b->d_list,     b->d_nlist,   b->d_tilerec, from,
-          to,          tag_from,    tag_to,      b->d_flag + 2, rl2,          global_out || b->force_gather ? 1 : 0};
+          to,          tag_from,    tag_to,      b->d_flag + 2, rl2,          global_out || b->force_gather ? 0 : b->stage_cap};
 }
 
 // Pair-list build (after a reorder into `from`: the build copies the state
@@ -214,10 +214,11 @@ void enqueue_sort(hmd_batch* b, Launcher& L, const StepConst& K, const int* flag
       HMD_V(K, 0, 1, 0, 0), HMD_V(K, 0, 1, 0, 1), HMD_V(K, 0, 1, 1, 0), HMD_V(K, 0, 1, 1, 1),           \
       HMD_V(K, 1, 0, 0, 0), HMD_V(K, 1, 0, 0, 1), HMD_V(K, 1, 0, 1, 0), HMD_V(K, 1, 0, 1, 1),           \
       HMD_V(K, 1, 1, 0, 0), HMD_V(K, 1, 1, 0, 1), HMD_V(K, 1, 1, 1, 0), HMD_V(K, 1, 1, 1, 1)
-decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr) {
-  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_tiles)};
-  static const decltype(&k_force_tiles<0, 0, 0, 0, 0>) tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
-  return pr ? tab_pr[v & 7] : tab[v];
+decltype(&k_force_tiles<0, 0, 0, 0, 0>) force_tiles_variant(int v, bool pr, bool tall) {
+  using Fn = decltype(&k_force_tiles<0, 0, 0, 0, 0>);
+  static const Fn tab[16] = {HMD_VARIANTS(k_force_tiles)}, tab_pr[8] = {HMD_VARIANTS_PR(k_force_tiles)};
+  static const Fn ttab[16] = {HMD_VARIANTS(k_force_tall)}, ttab_pr[8] = {HMD_VARIANTS_PR(k_force_tall)};
+  return tall ? (pr ? ttab_pr[v & 7] : ttab[v]) : (pr ? tab_pr[v & 7] : tab[v]);
 }
 decltype(&k_force_list<0, 0, 0, 0, 0>) force_list_variant(int v, bool pr) {
   static const decltype(&k_force_list<0, 0, 0, 0, 0>) tab[16] = {HMD_VARIANTS(k_force_list)};
@@ -254,8 +255,8 @@ void enqueue_force(hmd_batch* b, hipStream_t s, int mode, const StepConst& K, St
     const int v = ((mode * 2 + (K.energy_on ? 1 : 0)) * 2 + (b->uniform ? 1 : 0)) * 2 + (b->walls_same ? 1 : 0);
     const bool pr = mode == 1 && K.press_on;
     if (b->path == 2) {
-      hipLaunchKernelGGL(force_tiles_variant(v, pr), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
-                         b->d_tilerec, b->d_sims, b->d_pfix, b->d_list,
+      hipLaunchKernelGGL(force_tiles_variant(v, pr, b->stage_cap > TILE_STAGE), dim3(b->ntiles), dim3(TILE_THREADS), 0,
+                         s, nt, b->list_ld, b->d_tilerec, b->d_sims, b->d_pfix, b->d_list,
                          b->d_nlist, b->d_f4, state_ref(b, 0), b->acc, b->d_dstate, R, K);
     } else {
       hipLaunchKernelGGL(force_list_variant(v, pr), dim3(nb), dim3(tpb), 0, s, nt, b->list_ld, b->d_sims,
@@ -287,7 +288,8 @@ void enqueue_step(hmd_batch* b, Launcher& L, const StepConst& K, StepRef R) {
   // there are more (39,189 atoms 1.75 -> 1.69 ms for 40 steps with results,
   // the density sweep's 1,040 tiles 60 -> 55 us a step; 2.1 M atoms in 9,660
   // tiles 17.9 -> 18.3 ms)
-  if (b->path == 2 && b->ntiles <= kResidentTiles && !L.spans && !L.marks && !K.energy_on) {
+  if (b->path == 2 && b->ntiles <= kResidentTiles && b->stage_cap == TILE_STAGE && !L.spans && !L.marks &&
+      !K.energy_on) {
     enqueue_sort(b, L, K, b->d_flag, R, false);
     const int v = (b->uniform ? 4 : 0) + (b->walls_same ? 2 : 0) + (K.press_on ? 1 : 0);
     hipLaunchKernelGGL(list_force_variant(v), dim3(b->ntiles), dim3(TILE_THREADS), 0, s, nt, b->list_ld,
@@ -413,9 +415,16 @@ int get_graph(hmd_batch* b, int chunk, const StepConst& K, hipGraphExec_t* out) 
 // staged neighbourhood fits the LDS capacity.
 int make_tiles(hmd_batch* b) {
   hmd_ctx* ctx = b->ctx;
-  constexpr int kStageCap = TILE_STAGE;
   constexpr int64_t kMinTiles = 512;
-  b->stage_cap = kStageCap;
+  b->stage_cap = TILE_STAGE;
+  auto staged_atoms = [&](int k, int nc) {
+    const SimDev& D = b->sims[k];
+    return 3.0 * std::min(nc + 2, D.nx) *
+           (double(D.nf) / double(D.nx * D.nz) + double(b->host[k].nw) / double(D.nx * D.nz));
+  };
+  // a channel whose narrowest tiles need more asks for the larger capacity
+  for (int k = 0; k < b->S; ++k)
+    if (staged_atoms(k, 1) > 0.95 * TILE_STAGE) b->stage_cap = TILE_STAGE_TALL;
   // columns per tile: the most home atoms per unit of cost, cost being the
   // lanes of whole 256-lane passes and of a last one (half, a quarter or an
   // eighth of that where its lists are shared by lanes) plus tile_alpha + 1/4
@@ -427,14 +436,12 @@ int make_tiles(hmd_batch* b) {
   std::vector<int> cols(b->S, 1);
   for (int k = 0; k < b->S; ++k) {
     const SimDev& D = b->sims[k];
-    const HostSystem& H = b->host[k];
     const double per_col = double(D.nf) / double(D.nx * D.nz);
-    const double wall_col = double(H.nw) / double(2 * D.nx * D.nz);
     double best_use = -1.0;
     for (int nc = 1; nc <= D.nx; ++nc) {
       const double atoms = nc * per_col;
-      const double staged = 3.0 * std::min(nc + 2, D.nx) * (per_col + 2.0 * wall_col);
-      if (staged > 0.95 * kStageCap && nc > 1) break;
+      const double staged = staged_atoms(k, nc);
+      if (staged > 0.95 * b->stage_cap && nc > 1) break;
       const double left = std::fmod(atoms, double(TILE_THREADS));
       const double last = left > 128.0 ? 256.0 : left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : left > 0.0 ? 32.0 : 0.0;
       const double use = atoms / (atoms - left + last + (b->tile_alpha + 0.25) * staged);

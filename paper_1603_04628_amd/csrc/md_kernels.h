@@ -60,6 +60,7 @@ constexpr int TILE_THREADS = 256;  // threads per tile workgroup
 // 202 us with 2,112 and six, whose tiles stage too much halo); a compile-time
 // size lets every LDS read carry its array offset as an immediate
 constexpr int TILE_STAGE = 2400;
+constexpr int TILE_STAGE_TALL = 3072;  // k_force_tall
 // cells of a tile's neighbourhood listed in LDS by the list build
 constexpr int TILE_CTAB = 512;
 // entries of the screening coordinates the tiled list build may read past
@@ -89,7 +90,7 @@ struct TileBuild {
   const int* tag_from;
   int *tag_to, *overflow;
   float rl2;
-  int global_out;
+  int stage;  // LDS capacity of the force kernels in atoms; 0: position indices everywhere
 };
 template <int UNI>
 __global__ void k_build_tiles(int ntot, int ld, TileBuild A, const int* flag, StepRef R);
@@ -100,6 +101,10 @@ template <int MODE, int ENERGY, int UNI, int WS, int PR>
 __global__ void k_force_tiles(int ntot, int ld, const uint32_t* tilerec, const SimDev* sims, const int4* pfix,
                               const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,
                               int64_t* dstate, StepRef R, StepConst K);
+template <int MODE, int ENERGY, int UNI, int WS, int PR>
+__global__ void k_force_tall(int ntot, int ld, const uint32_t* tilerec, const SimDev* sims, const int4* pfix,
+                             const uint32_t* list, const uint32_t* nlist, float4* f4, StateRef st, Acc acc,
+                             int64_t* dstate, StepRef R, StepConst K);
 __global__ void k_stamp(unsigned long long* slot, const int* flag, StepRef R);
 __global__ void k_set_i64(int64_t* p, int64_t v);
 __global__ void k_add_i64(int64_t* p, int64_t v);

@@ -1063,12 +1063,13 @@ struct BuildLds {
   uint32_t ctab[TILE_CTAB];
   int tab_ok;
 };
+template <int STAGE>
 struct ForceLds {
-  int lx[TILE_STAGE], ly[TILE_STAGE], lz[TILE_STAGE];
+  int lx[STAGE], ly[STAGE], lz[STAGE];
 };
 union TileLds {
   BuildLds build;
-  ForceLds force;
+  ForceLds<TILE_STAGE> force;
 };
 
 // Column pieces of x0 - 1 .. x0 + ncol with periodic wrap (one piece covers
@@ -1469,7 +1470,7 @@ __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D,
 // matrix cores where the cell table holds the neighbourhood, else (columns of
 // more than BUILD_MAX_NY cells, more cells than the table, cells of more than
 // 255 atoms) cell by cell, one thread per atom.  Other tiles, and every tile
-// with global_out, get 32-bit position indices (the layout of k_build_list).
+// with stage 0, get 32-bit position indices (the layout of k_build_list).
 template <int UNI>
 __device__ __forceinline__ void build_tile(
     BuildLds& B, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles,
@@ -1478,13 +1479,13 @@ __device__ __forceinline__ void build_tile(
     const uint32_t* __restrict__ wstart, const uint32_t* __restrict__ wcount, uint32_t* __restrict__ list,
     uint32_t* __restrict__ nlist, uint32_t* __restrict__ tilerec, StateRef from, StateRef to,
     const int* __restrict__ tag_from, int* __restrict__ tag_to, int* __restrict__ overflow, float rl2,
-    int global_out) {
+    int stage) {
   uint32_t* const ctab = B.ctab;
   const int t = xcd_block();
   tile_ranges(tiles[t], ntot, sims, start, ncount, wstart, wcount, T);
   const uint32_t total = T.off[TILE_RUNS];
   // one LDS slot beyond the staged atoms holds the padding entry's position
-  const bool local = !global_out && total < uint32_t(TILE_STAGE);
+  const bool local = total < uint32_t(stage);
   if (threadIdx.x < TILE_REC)  // range table and mode, for the force kernels until the next rebuild
     tilerec[size_t(t) * TILE_REC + threadIdx.x] =
         threadIdx.x == TILE_REC - 1 ? (local ? 0u : 1u) : reinterpret_cast<const uint32_t*>(&T)[threadIdx.x];
@@ -1631,7 +1632,7 @@ template <int UNI>
 __device__ __forceinline__ void build_tile(BuildLds& B, TileStage& T, int ntot, int ld, const TileBuild& A) {
   build_tile<UNI>(B, T, ntot, ld, A.cap, A.tiles, A.sims, A.slot_cell, A.pfix, A.pos4, A.start, A.ncount, A.wstart,
                   A.wcount, A.list, A.nlist, A.tilerec, A.from, A.to, A.tag_from, A.tag_to, A.overflow, A.rl2,
-                  A.global_out);
+                  A.stage);
 }
 
 template <int UNI>
@@ -1655,9 +1656,9 @@ __device__ __forceinline__ float lane_xor(float v) {
 // half-kick and the sample of the step.  Bound by VALU issue (23 instructions
 // per list entry) with LDS gathers beside it: 210 us per step of 2.1 M atoms
 // before tiles left room for five workgroups, 176 us since.
-template <int MODE, int ENERGY, int UNI, int WS, int PR>
+template <int MODE, int ENERGY, int UNI, int WS, int PR, class Lds>
 __device__ __forceinline__ void force_tiles(
-    ForceLds& F, TileStage& T, uint32_t rec, int ntot, int ld, const SimDev* __restrict__ sims,
+    Lds& F, TileStage& T, uint32_t rec, int ntot, int ld, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list,
     const uint32_t* __restrict__ nlist, float4* __restrict__ f4, StateRef st, Acc acc,
     int64_t* __restrict__ dstate, StepRef R, StepConst K) {
@@ -1893,7 +1894,21 @@ __global__ __launch_bounds__(TILE_TPB, ENERGY ? 4 : 5) void k_force_tiles(
     int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
     const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
     float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
-  __shared__ ForceLds F;
+  __shared__ ForceLds<TILE_STAGE> F;
+  __shared__ TileStage T;
+  force_tiles<MODE, ENERGY, UNI, WS, PR>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
+                                         dstate, R, K);
+}
+// The same for channels of which a column and its neighbours already exceed
+// TILE_STAGE (33 to 44 sigma of liquid at density 0.8): four workgroups per
+// compute unit, against gathers from memory (one channel of 36 or 40 sigma in
+// the large box: 39 and 43 us per step).
+template <int MODE, int ENERGY, int UNI, int WS, int PR>
+__global__ __launch_bounds__(TILE_TPB, 4) void k_force_tall(
+    int ntot, int ld, const uint32_t* __restrict__ tilerec, const SimDev* __restrict__ sims,
+    const int4* __restrict__ pfix, const uint32_t* __restrict__ list, const uint32_t* __restrict__ nlist,
+    float4* __restrict__ f4, StateRef st, Acc acc, int64_t* __restrict__ dstate, StepRef R, StepConst K) {
+  __shared__ ForceLds<TILE_STAGE_TALL> F;
   __shared__ TileStage T;
   force_tiles<MODE, ENERGY, UNI, WS, PR>(F, T, tile_word(tilerec), ntot, ld, sims, pfix, list, nlist, f4, st, acc,
                                          dstate, R, K);
@@ -1969,7 +1984,11 @@ HMD_LIST_FORCE(1, 0, 0) HMD_LIST_FORCE(1, 0, 1) HMD_LIST_FORCE(1, 1, 0) HMD_LIST
   template __global__ void k_force_tiles<M, E, U, W, PR>(int, int, const uint32_t*, const SimDev*,            \
                                                          const int4*, const uint32_t*,                         \
                                                          const uint32_t*, float4*, StateRef, Acc, int64_t*,    \
-                                                         StepRef, StepConst);
+                                                         StepRef, StepConst);                                  \
+  template __global__ void k_force_tall<M, E, U, W, PR>(int, int, const uint32_t*, const SimDev*,             \
+                                                        const int4*, const uint32_t*,                          \
+                                                        const uint32_t*, float4*, StateRef, Acc, int64_t*,     \
+                                                        StepRef, StepConst);
 #define HMD_FORCE_LIST(M, E, U, W, PR)                                                                 \
   template __global__ void k_force_list<M, E, U, W, PR>(int, int, const SimDev*, const uint16_t*, const int4*, \
                                                         const uint32_t*, const uint32_t*, float4*, StateRef, Acc, \

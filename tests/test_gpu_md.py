@@ -155,6 +155,28 @@ def test_tiled_list_build_shapes(h, skin, cell_w, params):
     assert pe == pytest.approx(peo, rel=1e-4)
 
 
+@pytest.mark.parametrize("h", [24.0, 26.0, 30.0, 36.0])
+def test_tall_channels(h):
+    # columns whose neighbourhoods hold about 2,300, 2,470, 2,770 and 3,200
+    # atoms: either LDS capacity and beyond both; bounds as above
+    params = dict(Lx_nom=12.7, Lz_nom=12.7)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=0.3, **params))
+    g_sys, o_sys = hmd.System(ctx, h, 0.02, 9), omd.System(h, 0.02, 9, omd.Params(**params))
+    o_sys.run(40)
+    xo, vo = o_sys.get_state()
+    g_sys.set_state(xo, vo)
+    f, pe = g_sys.forces()
+    fo, peo = o_sys.forces_cells()
+    ok, info = _per_atom_ok(f, fo)
+    assert ok, info
+    assert pe == pytest.approx(peo, rel=1e-4)
+    o_sys.run(20)
+    g_sys.run(20)
+    d = g_sys.get_state()[0] - o_sys.get_state()[0]
+    d -= o_sys.Lx * np.round(d / o_sys.Lx) * np.array([1, 0, 1])
+    assert np.abs(d).max() <= 1e-3
+
+
 @pytest.mark.parametrize("h,cell_w", [(4.0, 0.0), (9.0, 0.0), (15.0, 0.0), (4.0, 4.0), (8.0, 4.0), (12.0, 4.0),
                                       (19.0, 4.0), (21.0, 4.0), (24.0, 4.0)])
 def test_lists_shared_by_lanes(h, cell_w):
