@@ -375,10 +375,9 @@ int gp_log_marginal(hmd_gp* gp, double* lml);
  * maxima: a grid of 17 points per chosen parameter, a quarter decade apart
  * over two decades either side of the current values, picks the start of
  * cyclic line searches over the logarithm of each chosen parameter (bracket:
- * a factor 10 either side of the current value at first, then 16 times the
- * last cycle's move; with several parameters a cycle ends with a search along
- * the way it came), until two cycles in a row at the finest bracket gain less
- * than 1e-12 relative.  The evidences of a grid or of a round of a line
+ * a factor 10 either side of the current value at first, then 32 times the
+ * last cycle's move), until a cycle gains less than 1e-12 relative (at most 30
+ * cycles).  The evidences of a grid or of a round of a line
  * search are evaluated together on the device; beyond 128 points that takes
  * a workspace of up to 8 GiB for the call (less where it cannot be had).
  * The GP is left fitted at the optimum; *lml (nullable) receives the maximum.

@@ -696,20 +696,18 @@ constexpr int EV_MAX = 256;   // sets of a launch: one per compute unit
 constexpr int EV_LDS_N = 128; // points whose covariance one workgroup keeps in LDS
 
 // State of the search on the device: logarithms of sigma_f, ell and sigma_n
-// (scaled) now and at the start of the cycle, the evidence now, and the
-// direction and bracket of the current line search.
+// (scaled), the evidence there, and the bracket of the current line search.
 struct EvState {
-  double x[3], x0[3], best, dir[3], lo, hi;
+  double x[3], best, lo, hi;
 };
 
-// One round of a line search.  axis: parameter 0-2, 3 the direction the cycle
-// has taken so far (scaled to its largest component), -1 no line: set t is
+// One round of a line search.  axis: parameter 0-2, -1 no line: set t is
 // pts[t].  Round 0 opens the bracket at the current point +- width; a later
 // round closes it around the best of the nb sets of the round before (between
 // its neighbours); the last one takes that best where it beats the point the
 // search started from.  Every wavefront that calls it computes the same.
 struct EvLine {
-  int axis, round, last, first_of_cycle, nb;
+  int axis, round, last, nb;
   double width;
   const double* pts;
   const EvState* in;
@@ -721,16 +719,6 @@ struct EvLine {
 __device__ __forceinline__ EvState ev_step(const EvLine& E) {
   EvState S = *E.in;
   if (E.round == 0) {
-    double big = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (E.first_of_cycle) S.x0[k] = S.x[k];
-      const double move = S.x[k] > -INFINITY ? S.x[k] - S.x0[k] : 0.0;
-      S.dir[k] = E.axis == 3 ? move : (E.axis == k ? 1.0 : 0.0);
-      big = fmax(big, fabs(S.dir[k]));
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) S.dir[k] = big > 0.0 ? S.dir[k] / big : 0.0;
     S.lo = -E.width;
     S.hi = E.width;
     return S;
@@ -758,7 +746,7 @@ __device__ __forceinline__ EvState ev_step(const EvLine& E) {
   if (E.last) {
     if (f >= S.best) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) S.x[k] += S.dir[k] != 0.0 ? c * S.dir[k] : 0.0;
+      for (int k = 0; k < 3; ++k) S.x[k] += k == E.axis ? c : 0.0;
       S.best = f;
     }
   } else {
@@ -778,7 +766,7 @@ __device__ __forceinline__ void ev_set(const EvLine& E, int t, bool keep, double
     const EvState S = ev_step(E);
     if (keep) *E.out = S;
     const double c = S.lo + double(t + 1) * ((S.hi - S.lo) / double(E.nb + 1));
-    for (int k = 0; k < 3; ++k) x[k] = S.x[k] + (S.dir[k] != 0.0 ? c * S.dir[k] : 0.0);
+    for (int k = 0; k < 3; ++k) x[k] = S.x[k] + (k == E.axis ? c : 0.0);
   }
   sf2 = exp(2.0 * x[0]);
   i2l2 = 0.5 * exp(-2.0 * x[1]);
@@ -1313,17 +1301,18 @@ int gp_log_marginal(hmd_gp* g, double* lml) {
 // parameter, a quarter decade apart over two decades either side of the
 // start, then refines from the best grid point by cyclic line searches over
 // the logarithm of each chosen parameter, bracketed at first by a factor 10
-// around the current value and then by 16 times the last cycle's move, until
-// two cycles at the finest bracket gain less than 1e-12 relative.
+// around the current value and then by 32 times the last cycle's move, until
+// a cycle gains less than 1e-12 relative (at most 30 cycles).
 //
 // Refits are independent of each other, so a whole grid, or a round of up to
 // 256 points along a line, is one set of launches: a line search closes its
-// bracket by (nb + 1) / 2 per round, two rounds where golden sections took 63
-// refits in turn (five rounds with the bracket kept at a factor 10).  A cycle ends with a search along the way it came, which
-// crosses the ridge that sigma_f and ell share (4 cycles instead of 12).  The
-// rounds of a cycle are queued without waiting for the host.  Up to EV_LDS_N
-// points a set is one workgroup; beyond, the panel elimination runs on all
-// sets at once, as many as a workspace of kEvBytes holds.
+// bracket by (nb + 1) / 2 per round, three to five rounds where golden sections
+// took 63 refits in turn.  (Searching along the way a cycle came as well
+// converges in a third of the rounds, but where the cycles end at their limit
+// on a flat ridge it ends elsewhere, by up to 1e-3 in sigma_f.)  The rounds of a
+// cycle are queued without waiting for the host.  Up to EV_LDS_N points a set
+// is one workgroup; beyond, the panel elimination runs on all sets at once, as
+// many as a workspace of kEvBytes holds.
 int gp_optimize(hmd_gp* g, int mask, double* lml) {
   if (!g || mask <= 0 || mask > 7) return HMD_EINVAL;
   hmd_ctx* ctx = g->ctx;
@@ -1378,8 +1367,8 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
     M.info = w.info;
   }
   int flip = 0;  // states and evidences alternate between launches
-  auto line = [&](int axis, int round, int last, int first, int m, double width) {
-    return EvLine{axis, round, last, first, m, width, pts_dev, st_dev + flip, st_dev + 1 - flip, lml_dev[flip],
+  auto line = [&](int axis, int round, int last, int m, double width) {
+    return EvLine{axis, round, last, m, width, pts_dev, st_dev + flip, st_dev + 1 - flip, lml_dev[flip],
                   lml_dev[1 - flip]};
   };
   const double* const noise = g->hyp.noise_mode == 1 ? g->dnoise : nullptr;
@@ -1420,7 +1409,7 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
         for (int j = 0; j < m; ++j, r /= 17) x[idx[j]] += std::log(10.0) * (-2.0 + 0.25 * (r % 17));
       }
       HMD_HIP(ctx, hipMemcpyAsync(pts_dev, pts.data(), 8 * pts.size(), hipMemcpyHostToDevice, s));
-      const EvLine E = line(-1, 0, 0, 0, c, 0.0);
+      const EvLine E = line(-1, 0, 0, c, 0.0);
       evaluate(E);
       HMD_HIP(ctx, hipGetLastError());
       HMD_HIP(ctx, hipMemcpyAsync(val.data(), E.lml_out, 8 * size_t(c), hipMemcpyDeviceToHost, s));
@@ -1435,30 +1424,24 @@ int gp_optimize(hmd_gp* g, int mask, double* lml) {
   }
   flip = 0;
   HMD_HIP(ctx, hipMemcpyAsync(st_dev, &st, sizeof(st), hipMemcpyHostToDevice, s));
-  const double widest = std::log(10.0), finest = 4e-6;
-  // rounds of nb sets that close a bracket by kClose (two of 256)
-  constexpr double kClose = 128.5 * 128.5;
-  const int rounds = int(std::ceil(std::log(kClose) / std::log(0.5 * double(nb + 1)) - 1e-9));
+  const double widest = std::log(10.0);
   double width = widest;
-  int settled = 0;  // cycles in a row without gain: two, since the last gains move along a flat ridge
-  for (int cycle = 0; cycle < 75 && settled < 2; ++cycle) {
+  for (int cycle = 0; cycle < 30; ++cycle) {
     const EvState before = st;
-    for (int j = 0; j < (m > 1 ? m + 1 : m); ++j) {
-      // the direction of the cycle may lead further than its parts
-      const int axis = j < m ? idx[j] : 3, nr = axis < 3 ? rounds : rounds + (rounds + 1) / 2;
-      const double w = axis < 3 ? width : std::min(widest, 128.0 * width);
-      for (int r = 0; r < nr; ++r) evaluate(line(axis, r, 0, j == 0 ? 1 : 0, nb, w));
-      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, line(axis, nr, 1, 0, nb, w), par);
+    // rounds that close the bracket below 1e-9
+    const int rounds = std::max(1, int(std::ceil(std::log(2.0 * width / 1e-9) / std::log(0.5 * double(nb + 1)))));
+    for (int j = 0; j < m; ++j) {
+      for (int r = 0; r < rounds; ++r) evaluate(line(idx[j], r, 0, nb, width));
+      hipLaunchKernelGGL(k_gp_ev_line, dim3(1), dim3(EV_MAX), 0, s, line(idx[j], rounds, 1, nb, width), par);
       flip = 1 - flip;
     }
     HMD_HIP(ctx, hipGetLastError());
     HMD_HIP(ctx, hipMemcpyAsync(&st, st_dev + flip, sizeof(st), hipMemcpyDeviceToHost, s));
     HMD_HIP(ctx, hipStreamSynchronize(s));
+    if (std::fabs(st.best - before.best) <= 1e-12 * std::fabs(st.best)) break;
     double move = 0.0;
     for (int k = 0; k < m; ++k) move = std::max(move, std::fabs(st.x[idx[k]] - before.x[idx[k]]));
-    const bool gain = std::fabs(st.best - before.best) > 1e-12 * std::fabs(st.best);
-    settled = gain || width > finest ? 0 : settled + 1;
-    width = std::min(widest, std::max(finest, gain ? 16.0 * move : width / 64.0));
+    width = std::min(widest, std::max(1e-6, 32.0 * move));
   }
   if (mask & 1) g->hyp.sigma_f = std::exp(st.x[0]);
   if (mask & 2) g->hyp.ell = std::exp(st.x[1]);
