@@ -257,7 +257,7 @@ struct Chol {
   double* A;        // L (in place of C), tile rows up to the y row
   double* W;        // L^-1 (INV), same layout
   double* dinv;     // inverses of the diagonal tiles, TB x TB each
-  int* info;        // 0, or k + 1 for the first pivot k that is not positive
+  int* info;        // 0, or k + 1 for the first pivot k that is not positive (see panel_failed)
   int ld, nt;       // leading dimension, column tiles
   size_t stride, dstride;
 };
@@ -289,7 +289,8 @@ __device__ void finish_diag(const Chol& M, int z, int p, bool inv_out, double* t
     V[e] = ui;
     if (inv_out) Wd[r + size_t(c) * M.ld] = ui;
   }
-  if (threadIdx.x == 0 && bad >= 0) M.info[z] = p * TB + bad + 1;
+  if (threadIdx.x == 0 && bad >= 0)
+    __hip_atomic_store(M.info + z, p * TB + bad + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Covariance tiles (i >= j) of every problem, padded with the identity, the
@@ -337,6 +338,13 @@ __global__ __launch_bounds__(256, 4) void k_gp_cov(int n, const double* __restri
   }
 }
 
+// Whether a diagonal tile up to that of panel p has failed.  Those were
+// factored by earlier launches.  The launch that eliminates panel p may itself
+// set info, for panel p + 1, while others of its workgroups ask: a failure
+// there counts from the next launch on, so that all of them, and every thread
+// of a workgroup, decide alike whichever value they read.
+__device__ __forceinline__ bool panel_failed(int info, int p) { return info != 0 && (info - 1) / TB <= p; }
+
 // Elimination of panel p (see above); launched for p = 0 .. nt with the tiles
 // (i, j), i >= max(p - 1, 0), j <= min(i, nt - 1), numbered row by row.  The
 // last launch only replaces panel nt - 1's tiles.  Without INV (the evidence
@@ -346,7 +354,7 @@ template <bool INV>
 __global__ __launch_bounds__(256, 4) void k_gp_panel(int p, Chol M, double* __restrict__ alpha) {
   __shared__ double f[TILE_EL], g[TILE_EL], v[TILE_EL];
   const int z = blockIdx.y;
-  if (M.info[z] != 0) return;
+  const int info = __hip_atomic_load(M.info + z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int i0 = INV ? max(p - 1, 0) : p, first = i0 * (i0 + 1) / 2;
   const int b = int(blockIdx.x) + first;
   int i = int((sqrt(8.0 * double(b) + 1.0) - 1.0) * 0.5);
@@ -354,6 +362,7 @@ __global__ __launch_bounds__(256, 4) void k_gp_panel(int p, Chol M, double* __re
   while (i * (i + 1) / 2 > b) --i;
   const int j = b - i * (i + 1) / 2, nt = M.nt;
   if (j >= nt || i > nt) return;
+  if (panel_failed(info, p)) return;  // (asked for first: its way is as long as the tile numbers')
   const size_t ld = M.ld;
   double* const A = M.A + z * M.stride;
   double* const W = M.W + z * M.stride;

@@ -124,6 +124,35 @@ def test_duplicate_points_without_noise_are_not_spd(ctx):
     assert e.value.code == B.HMD_ENOTSPD
 
 
+@pytest.mark.parametrize("bad", [0, 5, 31, 32, 63, 64, 100, 198, 199])
+def test_failing_pivot_is_named_in_every_panel(ctx, bad):
+    # a NaN input makes its own pivot the first that is not positive, in the
+    # first, an inner and the last panel of 32; the launches after it stop,
+    # and a fit after that is whole
+    X, y, se = data(200, 3)
+    hp = B.gp_hyper(scale_mode=1, ranges=RANGES)
+    whole = B.GP(ctx, X, y, se, hp).log_marginal()
+    Xb = X.copy()
+    Xb[bad, 0] = np.nan
+    with pytest.raises(B.HmdError, match=rf"pivot {bad}\b") as e:
+        B.GP(ctx, Xb, y, se, hp)
+    assert e.value.code == B.HMD_ENOTSPD
+    assert B.GP(ctx, X, y, se, hp).log_marginal() == whole
+
+
+@pytest.mark.parametrize("n", [100, 129, 200])
+def test_evidence_search_past_sets_that_are_not_spd(ctx, n):
+    # without noise the long length scales of the grid are singular, the short
+    # ones are not: white outputs have their maximum among the latter
+    X, _, _ = data(n, 40 + n)
+    y = np.random.default_rng(n).standard_normal(n)
+    g = B.GP(ctx, X, y, None, B.gp_hyper(ell=0.02, sigma_n=0.0, ranges=RANGES))
+    start = g.log_marginal()
+    best = g.optimize(("ell",))
+    assert np.isfinite(best) and best >= start
+    assert g.log_marginal() == pytest.approx(best, rel=1e-10)
+
+
 def test_database_size_limit(ctx):
     X = np.column_stack([np.linspace(4, 20, 6145), np.full(6145, 0.01)])
     with pytest.raises(B.HmdError) as e:
