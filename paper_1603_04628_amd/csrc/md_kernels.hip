@@ -1551,11 +1551,9 @@ __device__ __forceinline__ void build_tile(
     // gather in a register group (g0..g3, shifted down one entry per hit, the
     // newest on top) that goes out as one 16-byte store when it holds eight:
     // the lanes of a wave then write whole, adjacent groups instead of one
-    // scattered 16-bit store per hit.  Byte offsets are 32-bit (the list is
-    // below 4 GiB); the group index is clamped to cap / 8, a spill group in
-    // the half of the capacity that 16-bit entries leave unused (an
-    // overflowing list is reported below and never used).
-    char* const list_b = reinterpret_cast<char*>(list);
+    // scattered 16-bit store per hit.  The group index is clamped to cap / 8,
+    // a spill group in the half of the capacity that 16-bit entries leave
+    // unused (an overflowing list is reported below and never used).
     uint32_t g0 = 0, g1 = 0, g2 = 0, g3 = 0;
     auto push16 = [&](uint32_t k) {
       g0 = __builtin_amdgcn_alignbit(g1, g0, 16);
@@ -1565,7 +1563,7 @@ __device__ __forceinline__ void build_tile(
     };
     auto store_group = [&](uint32_t g) {
       g = min(g, uint32_t(cap) >> 3);
-      *reinterpret_cast<uint4*>(list_b + ((__umul24(g, uint32_t(ld)) + i) << 4)) = make_uint4(g0, g1, g2, g3);
+      reinterpret_cast<uint4*>(list)[size_t(g) * uint32_t(ld) + i] = make_uint4(g0, g1, g2, g3);
     };
     auto put16 = [&](bool hit, uint32_t k) {
       if (hit) {
@@ -1755,13 +1753,15 @@ __device__ __forceinline__ void force_tiles(
           px[b][0] = lx[k0]; py[b][0] = ly[k0]; pz[b][0] = lz[k0];
           px[b][1] = lx[k1]; py[b][1] = ly[k1]; pz[b][1] = lz[k1];
         };
-        // group g of slot i at byte (g ld + i) 16: a 32-bit offset from the
-        // list base (the list is below 4 GiB), no 64-bit address arithmetic
-        const char* const list_b = reinterpret_cast<const char*>(list);
+        // group g of slot i is entry g ld + i of the list in 16-byte groups: a
+        // pointer that walks it, since the list passes 4 GiB in batches of
+        // ten million atoms
         auto groups = [&](uint32_t first, auto step) {
+          const uint4* at = grp + size_t(first) * uint32_t(ld);
+          const size_t hop = size_t(uint32_t(ld)) * step;
           for (uint32_t g = first; g < full; g += step) {
-            const uint32_t gn = g + step < ngrp ? g + step : g;
-            const uint4 jn = *reinterpret_cast<const uint4*>(list_b + ((__umul24(gn, uint32_t(ld)) + i) << 4));
+            at += g + step < ngrp ? hop : 0;
+            const uint4 jn = *at;
             const uint32_t w[4] = {jj.x, jj.y, jj.z, jj.w};
             read_two(0, w[0]);
 #pragma unroll

@@ -221,6 +221,27 @@ def test_joined_launches_match_separate_ones(heights, pressure, path):
         np.testing.assert_allclose(out[0][n + k], out[1][n + k], rtol=0, atol=1e-4)
 
 
+def test_lists_past_2_to_the_24_slots():
+    # 16.8 M atoms: list groups lie beyond 4 GiB and a slot count beyond 24
+    # bits.  The last channel's forces after 20 steps against the oracle's, bar
+    # of test_forces_match_oracle_paper_scale_channel
+    n = 429
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, **LARGE))
+    b = hmd.Batch(ctx, [(15.0, 0.02, 4, 0)] * n)
+    print("created", b.atoms, flush=True)
+    assert b.atoms > 2 ** 24
+    b.run(20, graph_chunk=0)
+    assert b.config()["path"] == 2
+    x, v = b.get_state(n - 1)
+    f, _ = b.forces(n - 1)
+    o = omd.System(15.0, 0.02, 4, omd.Params(**LARGE))
+    o.set_state(x, v)
+    fo, _ = o.forces_cells()
+    assert _rel_rms(f, fo) <= 1e-5
+    ok, info = _per_atom_ok(f, fo)
+    assert ok, info
+
+
 @pytest.mark.parametrize("path", PATHS)
 def test_pair_counts(path):
     # ordered fluid pairs and wall pairs inside the cut-off, counted directly;
