@@ -630,16 +630,31 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
         (rc = dalloc(ctx, &b->d_slot_cell, b->ntot)) || (rc = dalloc(ctx, &b->d_nlist, b->ntot)) ||
         (rc = dalloc(ctx, &b->d_list, int64_t(b->list_cap) * b->list_ld)))
       return fail(rc);
-    // buckets of the sort: twice a system's mean cell and some (a fuller cell
-    // is handled, slowly); a system without atoms would be left unscanned
+    // Buckets of the sort (a fuller cell is handled, slowly): room for twice a
+    // system's mean cell and some, and for a cell of condensed fluid at 1.25
+    // per sigma^3 (a droplet of 5,878 atoms in cells 4 sigma wide, pair lists:
+    // 55 us a step, 109 where its cells overran the first of the two).  Bounded
+    // by the size of the pair lists: very dilute systems keep the first, or
+    // the separate kernels.  Those also sort where a system has no atoms (nobody
+    // would scan it).
     bool all = true;
-    double mean = 0.0;
+    double mean = 0.0, dense = 0.0;
     for (const SimDev& D : b->sims) {
       all = all && D.nf > 0;
       mean = std::max(mean, double(D.nf) / double(D.ncell));
+      dense = std::max(dense, 1.25 * D.wx * D.wy * D.wz);
     }
     if (all) {
-      b->bucket_cap = 8u * uint32_t(std::ceil((2.0 * mean + 16.0) / 8.0));
+      const double room = double(b->list_cap) * double(b->list_ld) / double(b->ncell);
+      for (double atoms : {std::max(2.0 * mean, dense), 2.0 * mean}) {
+        const double cap = 8.0 * std::ceil((atoms + 16.0) / 8.0);
+        if (cap <= room) {
+          b->bucket_cap = uint32_t(cap);
+          break;
+        }
+      }
+    }
+    if (b->bucket_cap) {
       if ((rc = dalloc(ctx, &b->d_bucket, b->ncell * int64_t(b->bucket_cap))) || (rc = dalloc(ctx, &b->d_done, n)))
         return fail(rc);
       HMD_HIP(ctx, hipMemsetAsync(b->d_done, 0, sizeof(int) * n, ctx->stream));

@@ -131,6 +131,36 @@ def test_sort_of_crowded_cells(n_in, path):
             assert np.all(np.diff(rank1[m[cell1[m] == oc]]) > 0), (c, oc)
 
 
+@pytest.mark.parametrize("path", [1, 2])
+@pytest.mark.parametrize("n_fluid,n_in", [(200, 32), (200, 33), (200, 55), (200, 56), (200, 57), (200, 90), (0, 72),
+                                          (0, 73)])
+def test_sort_of_cells_at_their_bucket(n_fluid, n_in, path):
+    # 30 sigma^3 cells: buckets of 56 entries in a vapour of 6 atoms per cell
+    # (room for condensed fluid; twice the mean and some would be 32), of 72 in
+    # the liquid.  A cell up to, at and past them: members complete and in
+    # their old order, every other cell too
+    ctx, g_sys, o_sys = _pair(6.0, 0.02, 9, path, n_fluid=n_fluid, **SMALL_L)
+    x, v = g_sys.get_state()
+    cell1, _, order1 = (a.astype(np.int64) for a in g_sys.cells())
+    rank1 = np.empty_like(order1)
+    rank1[order1] = np.arange(len(order1))
+    corner = np.all(x < np.array([o_sys.Lx / 4, 3.0, o_sys.Lz / 4]) + 1e-6, axis=1)
+    x[corner, 0] += 0.3 * o_sys.Lx
+    pick = np.random.default_rng(n_in).choice(len(x), n_in, replace=False)
+    grid = np.stack(np.meshgrid(*[np.arange(5) * 0.5 + 0.3] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x[pick] = grid[:n_in]
+    g_sys.set_state(x, v)
+    cell, cnt, order = (a.astype(np.int64) for a in g_sys.cells())
+    assert np.array_equal(np.bincount(cell, minlength=len(cnt)), cnt)
+    assert cnt[cell[pick[0]]] == n_in and np.all(cell[pick] == cell[pick[0]])
+    start = np.concatenate([[0], np.cumsum(cnt)[:-1]])
+    for c in np.nonzero(cnt)[0]:
+        m = order[start[c]:start[c] + cnt[c]]
+        assert np.array_equal(np.sort(m), np.nonzero(cell == c)[0])
+        for oc in np.unique(cell1[m]):
+            assert np.all(np.diff(rank1[m[cell1[m] == oc]]) > 0), (c, oc)
+
+
 @pytest.mark.parametrize("h,skin,cell_w,params", [
     (3.0, 0.3, 0.0, SMALL_L),  # one cell between the walls: every range of a column
     (5.0, 0.25, 0.0, LARGE),   # thin and wide: columns on both sides of an origin block
