@@ -75,6 +75,25 @@ def test_cell_membership_bit_exact(h, params, steps, path):
 
 
 @pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("h", [14.3, 17.0, 29.0, 100.0])
+def test_sort_of_many_cells(h, path):
+    # 2,000 to 14,000 cells of a dilute channel: the scan of a system's cells in
+    # one round of 2,048, in two with a part left, in several; slots in cell
+    # order, every cell complete
+    params = dict(rho=0.05, **LARGE)
+    ctx, g_sys, o_sys = _pair(h, 0.02, 5, path, **params)
+    o_sys.run(100)
+    xo, vo = o_sys.get_state()
+    g_sys.set_state(xo, vo)
+    (cell_g, cnt_g, order_g), (cell_o, cnt_o, _) = g_sys.cells(), o_sys.cells()
+    assert np.array_equal(cell_g.astype(np.int64), cell_o.astype(np.int64))
+    assert np.array_equal(cnt_g.astype(np.int64), cnt_o.astype(np.int64))
+    by_cell = cell_o.astype(np.int64)[order_g.astype(np.int64)]
+    assert np.all(np.diff(by_cell) >= 0)
+    assert np.array_equal(np.sort(order_g.astype(np.int64)), np.arange(o_sys.n_fluid))
+
+
+@pytest.mark.parametrize("path", PATHS)
 def test_cell_sort_is_stable(path):
     # the counting sort keeps the previous slot order inside every cell:
     # sorting an already sorted state changes nothing, and after the atoms
