@@ -425,9 +425,18 @@ int make_tiles(hmd_batch* b) {
   // a channel whose narrowest tiles need more asks for the larger capacity
   for (int k = 0; k < b->S; ++k)
     if (staged_atoms(k, 1) > 0.95 * TILE_STAGE) b->stage_cap = TILE_STAGE_TALL;
+  // Whether the list build's cell table holds a tile's neighbourhood.  Tall
+  // dilute channels keep to that width where it leaves two columns (four
+  // channels of 150 sigma at density 0.05: 42 us a step with two columns, 54
+  // with three and lists built cell by cell; of 200 sigma, where it leaves
+  // one: 60 with one column, 53 with three).
+  auto tabled = [&](int k, int nc) {
+    return 3 * std::min(nc + 2, b->sims[k].nx) * (b->sims[k].ny + 2) <= TILE_CTAB;
+  };
   // columns per tile: the most home atoms per unit of cost, cost being the
   // lanes of whole 256-lane passes and of a last one (half, a quarter or an
-  // eighth of that where its lists are shared by lanes) plus tile_alpha + 1/4
+  // eighth of that where its lists are shared by lanes; the whole where they
+  // are built by one thread per atom) plus tile_alpha + 1/4
   // per staged atom (a wider tile stages less halo per home atom); 2%
   // hysteresis keeps the narrower of two near-equal choices.  Without the
   // quarter, and with every pass counted whole: 64-channel batch, force 180
@@ -442,8 +451,10 @@ int make_tiles(hmd_batch* b) {
       const double atoms = nc * per_col;
       const double staged = staged_atoms(k, nc);
       if (staged > 0.95 * b->stage_cap && nc > 1) break;
+      if (nc > 2 && !tabled(k, nc) && tabled(k, 2)) break;
       const double left = std::fmod(atoms, double(TILE_THREADS));
-      const double last = left > 128.0 ? 256.0 : left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : left > 0.0 ? 32.0 : 0.0;
+      double last = left > 0.0 ? 256.0 : 0.0;
+      if (tabled(k, nc) && left > 0.0 && left <= 128.0) last = left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : 32.0;
       const double use = atoms / (atoms - left + last + (b->tile_alpha + 0.25) * staged);
       if (use > 1.02 * best_use) {
         best_use = use;

@@ -61,8 +61,10 @@ constexpr int TILE_THREADS = 256;  // threads per tile workgroup
 // size lets every LDS read carry its array offset as an immediate
 constexpr int TILE_STAGE = 2400;
 constexpr int TILE_STAGE_TALL = 3072;  // k_force_tall
-// cells of a tile's neighbourhood listed in LDS by the list build
-constexpr int TILE_CTAB = 512;
+// cells of a tile's neighbourhood listed in LDS by the list build: columns of
+// up to 83 cells (236 sigma at 2.85 each) in the narrowest tiles; more entries
+// would leave too little LDS for five workgroups per compute unit
+constexpr int TILE_CTAB = 768;
 // entries of the screening coordinates the tiled list build may read past
 // the last one (blocks past the end of a range)
 constexpr int SCREEN_PAD = 128;

@@ -1053,7 +1053,7 @@ constexpr int BUILD_ROW = 104;              // list entries of an atom gathered 
                                             // their starts on different banks
 constexpr int BUILD_PART = 128;             // candidates screened together
 constexpr int BUILD_MASKS = 5;              // hit masks of an atom group between two expansions
-constexpr int BUILD_MAX_NY = WAVE;          // cells of a column looked up by one wavefront
+constexpr int BUILD_MAX_NY = 2 * WAVE;      // cells of a column looked up by one wavefront, two a lane
 
 struct TileStage {
   uint32_t gb[TILE_RUNS];       // first entry of each range in the position array
@@ -1328,12 +1328,17 @@ __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D,
     const uint32_t slot0 = __builtin_amdgcn_readlane(run_src, 13);
     const int ng = int(hi - lo + 15u) >> 4;
     const uint32_t cell_lo = lane < ny ? own[lane] >> 8 : 0xffffffffu;
+    const uint32_t cell_hi = lane + WAVE < ny ? own[lane + WAVE] >> 8 : 0xffffffffu;
     for (int g = (wave + nwave - first % nwave) % nwave; g < ng; g += nwave) {
       const uint32_t l0 = lo + 16u * g, n = min(16u, hi - l0);
       const uint32_t me = l0 + min(uint32_t(j), n - 1u), i = slot0 + me;
       const float4 b4 = pos4[i];
       // cells of the first and last atom of the group
-      const int ya = __popcll(__ballot(cell_lo <= l0)) - 1, yb = __popcll(__ballot(cell_lo <= l0 + n - 1u)) - 1;
+      int ya = __popcll(__ballot(cell_lo <= l0)) - 1, yb = __popcll(__ballot(cell_lo <= l0 + n - 1u)) - 1;
+      if (ny > WAVE) {
+        ya += __popcll(__ballot(cell_hi <= l0));
+        yb += __popcll(__ballot(cell_hi <= l0 + n - 1u));
+      }
       const bool all_y = ya <= 1 && yb >= ny - 2;
       const bool join = joined && (seg != 1 || all_y);
       const int ia = seg == 0 ? 0 : (seg == 1 ? max(ya, 1) : ny + 1), ib = seg == 1 ? min(yb + 2, ny) : ia;
@@ -1481,19 +1486,24 @@ __device__ __forceinline__ void tile_screen(const TileStage& T, const SimDev& D,
 // Verlet lists of a tile's atoms (rebuild steps only).  Also completes the
 // reorder (state copy back) for the tile's slots.  Tiles whose neighbourhood
 // fits the force kernels' LDS get 16-bit lists of LDS indices: screened on the
-// matrix cores where the cell table holds the neighbourhood, else (columns of
-// more than BUILD_MAX_NY cells, more cells than the table, cells of more than
-// 255 atoms) cell by cell, one thread per atom.  Other tiles, and every tile
-// with stage 0, get 32-bit position indices (the layout of k_build_list).
+// matrix cores where the cell table holds the neighbourhood, else (more cells
+// than the table, cells of more than 255 atoms) cell by cell, one thread per
+// atom, from positions staged in LDS (from memory in the tiles of tall channels
+// that exceed TILE_STAGE).  Other tiles, and every tile with stage 0, get
+// 32-bit position indices (the layout of k_build_list).
+//
+// Four channels of 500 sigma at density 0.02 (177 cells across): 85 us a rebuild
+// by one thread per atom from LDS, 134 from memory.
 template <int UNI>
 __device__ __forceinline__ void build_tile(
-    BuildLds& B, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles,
+    TileLds& L, TileStage& T, int ntot, int ld, int cap, const int4* __restrict__ tiles,
     const SimDev* __restrict__ sims, const uint32_t* __restrict__ slot_cell, const int4* __restrict__ pfix,
     const float4* __restrict__ pos4, const uint32_t* __restrict__ start, const uint32_t* __restrict__ ncount,
     const uint32_t* __restrict__ wstart, const uint32_t* __restrict__ wcount, uint32_t* __restrict__ list,
     uint32_t* __restrict__ nlist, uint32_t* __restrict__ tilerec, StateRef from, StateRef to,
     const int* __restrict__ tag_from, int* __restrict__ tag_to, int* __restrict__ overflow, float rl2,
     int stage) {
+  BuildLds& B = L.build;
   uint32_t* const ctab = B.ctab;
   const int t = xcd_block();
   tile_ranges(tiles[t], ntot, sims, start, ncount, wstart, wcount, T);
@@ -1548,6 +1558,12 @@ __device__ __forceinline__ void build_tile(
     tile_screen(T, D, pos4, ctab, ncolx, nyt, whole, rl2, ld, cap, list, nlist, B.rowbuf[threadIdx.x / WAVE],
                 B.masks[threadIdx.x / WAVE], B.blocks[threadIdx.x / WAVE], overflow);
     return;
+  }
+  const bool staged = local && total <= uint32_t(TILE_STAGE);
+  int *const lx = L.force.lx, *const ly = L.force.ly, *const lz = L.force.lz;
+  if (staged) {
+    __syncthreads();  // the table's place is reused
+    tile_stage(T, pfix, lx, ly, lz);
   }
   for (uint32_t i = T.home0 + threadIdx.x; i < T.home1; i += blockDim.x) {
     const int4 me = pfix[i];
@@ -1613,7 +1629,20 @@ __device__ __forceinline__ void build_tile(
           const int run = kind * 6 + (dz + 1) * 2 + piece;
           const uint32_t base = T.off[run] + (cb - T.gb[run]);
           const uint32_t self = i - cb;  // candidate index of the atom itself (if in this cell)
-          for (uint32_t m = 0; m < cn; ++m) {
+          uint32_t m = 0;
+          if (staged) {  // four candidates per pass: their LDS reads are in flight together
+            for (; m + 4 <= cn; m += 4) {
+              float r2[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const uint32_t k = base + m + u;
+                r2[u] = sep2(lx[k], ly[k], lz[k]);
+              }
+#pragma unroll
+              for (int u = 0; u < 4; ++u) put16(r2[u] < rl2u && m + u != self, base + m + u);
+            }
+          }
+          for (; m < cn; ++m) {
             const int4 o = pfix[cb + m];
             const bool hit = sep2(o.x, o.y, o.z) < rl2u && m != self;
             if (local) put16(hit, base + m);
@@ -1641,8 +1670,8 @@ __device__ __forceinline__ void build_tile(
 }
 
 template <int UNI>
-__device__ __forceinline__ void build_tile(BuildLds& B, TileStage& T, int ntot, int ld, const TileBuild& A) {
-  build_tile<UNI>(B, T, ntot, ld, A.cap, A.tiles, A.sims, A.slot_cell, A.pfix, A.pos4, A.start, A.ncount, A.wstart,
+__device__ __forceinline__ void build_tile(TileLds& L, TileStage& T, int ntot, int ld, const TileBuild& A) {
+  build_tile<UNI>(L, T, ntot, ld, A.cap, A.tiles, A.sims, A.slot_cell, A.pfix, A.pos4, A.start, A.ncount, A.wstart,
                   A.wcount, A.list, A.nlist, A.tilerec, A.from, A.to, A.tag_from, A.tag_to, A.overflow, A.rl2,
                   A.stage);
 }
@@ -1651,9 +1680,9 @@ template <int UNI>
 __global__ __launch_bounds__(TILE_TPB, 5) void k_build_tiles(int ntot, int ld, TileBuild A,
                                                              const int* __restrict__ flag, StepRef R) {
   if (!rebuild_needed(flag, R)) return;
-  __shared__ BuildLds B;
+  __shared__ TileLds L;
   __shared__ TileStage T;
-  build_tile<UNI>(B, T, ntot, ld, A);
+  build_tile<UNI>(L, T, ntot, ld, A);
 }
 
 // The value of lane ^ M, M one of 1, 2, 7.
@@ -1940,7 +1969,7 @@ __global__ __launch_bounds__(TILE_TPB, 5) void k_list_force(int ntot, int ld, Ti
   __shared__ TileStage T;
   uint32_t rec = tile_word(A.tilerec);  // requested with the flag, read again after a build
   if (rebuild_needed(flag, R)) {
-    build_tile<UNI>(L.build, T, ntot, ld, A);
+    build_tile<UNI>(L, T, ntot, ld, A);
     __syncthreads();
     rec = tile_word(A.tilerec);
   }

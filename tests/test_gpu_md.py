@@ -270,6 +270,91 @@ def test_joined_launches_match_separate_ones(heights, pressure, path):
         np.testing.assert_allclose(out[0][n + k], out[1][n + k], rtol=0, atol=1e-4)
 
 
+def _tile_shapes(b, o, x):
+    """Per tile of a one-channel batch (or of equal channels), from the host's
+    geometry: staged atoms, home atoms, entries of the longest run of three
+    columns' fluid; and cells of a tile's neighbourhood."""
+    nx, ny, nz = o.ncell
+    ntx = b.tuning()["tiles"] // (nz * b.n)
+    L = np.array([o.Lx, o.Lz])
+
+    def columns(p):
+        c = np.minimum((p[:, [0, 2]] / L * [nx, nz]).astype(int), [nx - 1, nz - 1])
+        return np.bincount(c[:, 1] * nx + c[:, 0], minlength=nx * nz).reshape(nz, nx)
+
+    fluid, both = columns(x), columns(np.vstack([x, o.wall()]))
+    staged, home = [], []
+    for z in range(nz):
+        zs = sorted({(z - 1) % nz, z, (z + 1) % nz})
+        for t in range(ntx):
+            x0, x1 = t * nx // ntx, (t + 1) * nx // ntx
+            xs = sorted({c % nx for c in range(x0 - 1, x1 + 1)})
+            staged.append(both[np.ix_(zs, xs)].sum())
+            home.append(fluid[z, x0:x1].sum())
+    runs = fluid + np.roll(fluid, 1, 1) + np.roll(fluid, -1, 1)
+    cells = 3 * min(-(-nx // ntx) + 2, nx) * (ny + 2)
+    return dict(staged=max(staged), home=(min(home), max(home)), run=runs.max(), cells=cells, ny=ny)
+
+
+def _forces_of_one(b, k, h, seed, params, cell_w=0.0):
+    """Forces of channel k of a batch and its state against the oracle; returns
+    the oracle's system and the state."""
+    x, v = b.get_state(k)
+    f, pe = b.forces(k)
+    o = omd.System(h, 0.02, seed, omd.Params(cell_w=max(2.5 + SKIN, cell_w), **params))
+    o.set_state(x, v)
+    fo, peo = o.forces_cells()
+    ok, info = _per_atom_ok(f, fo)
+    assert ok, info
+    assert pe == pytest.approx(peo, rel=1e-4)
+    return o, x
+
+
+@pytest.mark.parametrize("h,n_fluid,ny,table,stage", [
+    (179.0, 2000, 63, True, 0),      # cells across: one lane each in the lookup
+    (179.4, 2000, 64, True, 0),
+    (182.1, 2000, 65, True, 0),      # two
+    (233.0, 2000, 83, True, 0),      # the last the table holds
+    (236.0, 2000, 84, False, 0),     # cell by cell, staged in LDS
+    (300.0, 2000, 107, False, 0),
+    (300.0, 3500, 107, False, 1)])   # past TILE_STAGE: cell by cell, from memory
+def test_list_build_of_dilute_tall_channels(h, n_fluid, ny, table, stage):
+    # forces from the lists as in test_tiled_list_build_shapes; the tile's
+    # neighbourhood fits the force kernels' LDS, which side of the cell table it
+    # lies on is asserted from the geometry
+    params = dict(Lx_nom=12.7, Lz_nom=12.7, n_fluid=n_fluid)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, **params))
+    b = hmd.Batch(ctx, [(h, 0.02, 8, 0)])
+    b.run(60, graph_chunk=20)
+    o, x = _forces_of_one(b, 0, h, 8, params)
+    s = _tile_shapes(b, o, x)
+    assert s["ny"] == ny and (s["cells"] <= 768) == table, s
+    assert (2400 < s["staged"] < 3072) if stage else s["staged"] < 2400, s
+
+
+@pytest.mark.parametrize("n_in", [255, 256, 290])
+def test_list_build_of_a_crowded_cell(n_in):
+    # a cell of up to 255 atoms is in the table's range, more are not: its
+    # neighbours' tiles build cell by cell, within the LDS capacity
+    params = dict(n_fluid=500, wall_layers=1, Lx_nom=workloads.BOX_SMALL, Lz_nom=workloads.BOX_SMALL)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, cell_w=6.0, **params))
+    b = hmd.Batch(ctx, [(13.0, 0.02, 8, 0)])
+    x, v = b.get_state(0)
+    o = omd.System(13.0, 0.02, 8, omd.Params(cell_w=6.0, **params))
+    grid = np.stack(np.meshgrid(*[np.arange(7) * 0.95 + 0.45] * 3, indexing="ij"), -1).reshape(-1, 3)
+    grid[:, 1] += 0.5
+    grid = grid[np.all(grid < np.array([o.Lx / 3, 6.5, o.Lz / 3]), axis=1)][:n_in]
+    rest = x[(x[:, 0] > 8.0) & (x[:, 0] < o.Lx - 0.6)][:500 - n_in]
+    xs = np.vstack([grid, rest])
+    assert xs.shape == x.shape
+    b.set_state(0, xs, v)
+    o, x = _forces_of_one(b, 0, 13.0, 8, params, cell_w=6.0)
+    cell, cnt, _ = o.cells()
+    assert cnt.max() == n_in
+    s = _tile_shapes(b, o, x)
+    assert s["staged"] < 2400 and s["cells"] <= 768, s
+
+
 def test_lists_past_2_to_the_24_slots():
     # 16.8 M atoms: list groups lie beyond 4 GiB and a slot count beyond 24
     # bits.  The last channel's forces after 20 steps against the oracle's, bar
