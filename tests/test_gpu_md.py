@@ -355,6 +355,27 @@ def test_list_build_of_a_crowded_cell(n_in):
     assert s["staged"] < 2400 and s["cells"] <= 768, s
 
 
+@pytest.mark.parametrize("n,h,cell_w,params,home,run,stage", [
+    (6, 10.0, 0.0, LARGE, 257, 129, 2400),                          # second passes of up to 32 atoms
+    (1, 34.0, 0.0, dict(Lx_nom=12.7, Lz_nom=12.7, wall_layers=1), 257, 129, 3072),
+    (1, 37.2, 0.0, dict(Lx_nom=12.7, Lz_nom=12.7, wall_layers=1), 289, 129, 3072),  # of up to 64
+    (1, 39.5, 0.0, dict(Lx_nom=12.7, Lz_nom=12.7, wall_layers=1), 321, 129, 3072),  # of up to 128
+    (1, 8.0, 0.0, LARGE, 1, 129, 2400),                             # fluid ranges of two parts
+    (1, 8.0, 4.0, LARGE, 1, 257, 2400)])                            # of three
+def test_lds_tiles_of_many_atoms(n, h, cell_w, params, home, run, stage):
+    # lists of LDS indices: tiles of more atoms than the workgroup has threads,
+    # candidate ranges longer than the part screened at once.  That the tiles
+    # keep within the LDS capacity and reach these branches is asserted from
+    # the geometry
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, cell_w=cell_w, **params))
+    b = hmd.Batch(ctx, [(h, 0.02, 8, 0)] * n)
+    b.run(60, graph_chunk=20)
+    o, x = _forces_of_one(b, n - 1, h, 8, params, cell_w)
+    s = _tile_shapes(b, o, x)
+    assert s["home"][1] >= home and s["run"] >= run and s["staged"] < stage, s
+    print(s)
+
+
 def test_lists_past_2_to_the_24_slots():
     # 16.8 M atoms: list groups lie beyond 4 GiB and a slot count beyond 24
     # bits.  The last channel's forces after 20 steps against the oracle's, bar
