@@ -422,9 +422,14 @@ int make_tiles(hmd_batch* b) {
     return 3.0 * std::min(nc + 2, D.nx) *
            (double(D.nf) / double(D.nx * D.nz) + double(b->host[k].nw) / double(D.nx * D.nz));
   };
-  // a channel whose narrowest tiles need more asks for the larger capacity
-  for (int k = 0; k < b->S; ++k)
-    if (staged_atoms(k, 1) > 0.95 * TILE_STAGE) b->stage_cap = TILE_STAGE_TALL;
+  // a channel whose narrowest tiles fit only the larger capacity asks for it
+  // on behalf of the batch (32 channels of 10 sigma and one of 36: 168 us a
+  // step, 272 with the one gathering from memory; alone 38 and 64), one that
+  // exceeds both does not (8 of 10 sigma and one of 50: 144 us, 157 with it)
+  for (int k = 0; k < b->S; ++k) {
+    const double staged = staged_atoms(k, 1);
+    if (staged > 0.95 * TILE_STAGE && staged < TILE_STAGE_TALL) b->stage_cap = TILE_STAGE_TALL;
+  }
   // Whether the list build's cell table holds a tile's neighbourhood.  Tall
   // dilute channels keep to that width where it leaves two columns (four
   // channels of 150 sigma at density 0.05: 42 us a step with two columns, 54

@@ -376,6 +376,18 @@ def test_lds_tiles_of_many_atoms(n, h, cell_w, params, home, run, stage):
     print(s)
 
 
+@pytest.mark.parametrize("heights", [(6.0, 30.0), (6.0, 36.0), (6.0, 30.0, 36.0)])
+def test_tall_channels_among_others(heights):
+    # one capacity per batch: the larger for neighbourhoods of 2,770 atoms, the
+    # smaller where 3,200 exceed both and gather from memory
+    params = dict(Lx_nom=12.7, Lz_nom=12.7)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, **params))
+    b = hmd.Batch(ctx, [(h, 0.02, 9, 0) for h in heights])
+    b.run(60, graph_chunk=20)
+    for k, h in enumerate(heights):
+        _forces_of_one(b, k, h, 9, params)
+
+
 def test_lists_past_2_to_the_24_slots():
     # 16.8 M atoms: list groups lie beyond 4 GiB and a slot count beyond 24
     # bits.  The last channel's forces after 20 steps against the oracle's, bar
