@@ -33,11 +33,14 @@ constexpr int kTotal = 1, kSmallest = 2, kDone = 3;
 }  // namespace
 
 // out[s*4 + 0] = mean, [2] = mean of the first n/2 samples, [3] = mean of
-// the rest; [1] (the standard error) is left to the estimator kernels.  A
+// the rest; [1] (the standard error) is left to the estimator kernels.  A long
 // row is read by 16 wavefronts, four loads in flight each: latency bounds it
-// (64 rows of 20,000: 23 us with four wavefronts, one load at a time).
-constexpr int MOM_TPB = 1024;
+// (64 rows of 20,000: 23 us with four wavefronts, one load at a time).  Rows
+// of fewer than four samples a thread take four wavefronts (65,535 rows of 16
+// with the block rule: 126 us, 345 with sixteen).
+constexpr int MOM_LONG = 4096;
 
+template <int MOM_TPB>
 __global__ __launch_bounds__(MOM_TPB) void k_series_moments(const double* __restrict__ x, int64_t ld, int64_t n,
                                                             double scale, double* __restrict__ out) {
   __shared__ double red[2][MOM_TPB / 64];
@@ -71,6 +74,80 @@ __global__ __launch_bounds__(MOM_TPB) void k_series_moments(const double* __rest
     out[4 * s + 2] = sum[0] / double(half);
     out[4 * s + 3] = sum[1] / double(n - half);
   }
+}
+
+// Everything of a short row by one wavefront: moments, then Geyer's estimator
+// (see k_series_geyer) over 64 lags at a time, a lag per lane, each summed in
+// ascending i from LDS, until the sequence ends.  The matrix form below works
+// in pieces of 1024 samples and 304 lags, which rows of a few hundred samples
+// leave empty (65,535 rows of 16: 56 us, 2,020 in matrix form).  What bounds it
+// is the chain of a row's products and the LDS, two reads per product: for few
+// rows it is the better one up to about 256 samples (64 random walks of 200:
+// 13 against 18 us, of 384: 26 against 19), for many up to 512 (512 walks of
+// 384: 27 against 40 us; 20,000 of 384: 195 against 1,180).
+constexpr int SHORT_N = 512;
+
+bool short_rows(int S, int64_t n) { return n <= std::min(256 + S / 4, SHORT_N); }
+
+__global__ __launch_bounds__(SER_TPB) void k_series_short(const double* __restrict__ x, int64_t ld, int n,
+                                                         double scale, int S, double* __restrict__ out) {
+  __shared__ double lds[SER_TPB / 64][SHORT_N + 64];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6, s = blockIdx.x * (SER_TPB / 64) + w;
+  if (s >= S) return;  // whole wavefronts
+  double* const d = lds[w];
+  const double* const row = x + int64_t(s) * ld;
+  const int half = n / 2;
+  double a = 0.0, b = 0.0;
+  for (int i = l; i < n; i += 64) {
+    const double v = row[i] * scale;
+    d[i] = v;
+    if (i < half) a += v;
+    else b += v;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o);
+    b += __shfl_xor(b, o);
+  }
+  const double mean = (a + b) / double(n);
+  for (int i = l; i < n; i += 64) d[i] -= mean;  // the lane's own
+  d[n + l] = 0.0;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  double total = 0.0, smallest = INFINITY, g0 = 0.0;
+  bool any = false, stop = false;
+  for (int t0 = 0; t0 < n && !stop; t0 += 64) {
+    double g = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < n - t0; ++i) g += d[i] * d[i + t0 + l];
+    g /= double(n);
+    if (t0 == 0) g0 = __shfl(g, 0);
+    const double p = g + __shfl_down(g, 1);  // even lanes: a pair
+    const bool even = (l & 1) == 0;
+    const unsigned long long ends = __ballot(even && !(t0 + l + 1 < n && p > 0.0));
+    const int c = ends ? __builtin_ctzll(ends) : 64;  // lanes of the sequence in this run
+    stop = c < 64;
+    any = any || c > 0;
+    double m = even && l < c ? fmin(p, smallest) : INFINITY;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double v = __shfl_up(m, o);
+      if (l >= o) m = fmin(m, v);
+    }
+    double v = even && l < c ? m : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    total += v;
+    if (c > 0) smallest = __shfl(m, c - 1);
+  }
+  if (l != 0) return;
+  double var = any ? -g0 + 2.0 * total : g0;
+  if (!(var > 0.0)) var = g0;
+  out[4 * s + 0] = mean;
+  out[4 * s + 1] = sqrt(var / double(n));
+  out[4 * s + 2] = a / double(half);
+  out[4 * s + 3] = b / double(n - half);
 }
 
 // gamma_t = (1/n) sum_{i < n-t} d_i d_{i+t}, d = scale x - mean, on the FP64
@@ -257,7 +334,16 @@ int series_stats_check(int S, int64_t n, int64_t ld, int n_blocks, std::string& 
 
 void series_stats_enqueue(hipStream_t st, const double* d_x, int S, int64_t n, int64_t ld, double scale,
                           int n_blocks, double* d_gam, double* d_out) {
-  hipLaunchKernelGGL(k_series_moments, dim3(S), dim3(MOM_TPB), 0, st, d_x, ld, n, scale, d_out);
+  if (n_blocks == 0 && short_rows(S, n)) {
+    constexpr int rows = SER_TPB / 64;
+    hipLaunchKernelGGL(k_series_short, dim3((S + rows - 1) / rows), dim3(SER_TPB), 0, st, d_x, ld, int(n), scale, S,
+                       d_out);
+    return;
+  }
+  if (n >= MOM_LONG)
+    hipLaunchKernelGGL(k_series_moments<1024>, dim3(S), dim3(1024), 0, st, d_x, ld, n, scale, d_out);
+  else
+    hipLaunchKernelGGL(k_series_moments<256>, dim3(S), dim3(256), 0, st, d_x, ld, n, scale, d_out);
   if (n_blocks >= 2) {
     hipLaunchKernelGGL(k_series_blocks, dim3(S), dim3(SER_TPB), 0, st, d_x, ld, n, scale, n_blocks, d_out);
     return;
@@ -269,7 +355,10 @@ void series_stats_enqueue(hipStream_t st, const double* d_x, int S, int64_t n, i
   const int64_t lags = big ? wide : narrow, tiles = (n + lags - 1) / lags, pairs = n / 2;
   int64_t step = std::max<int64_t>(2, (512 + S - 1) / S);
   for (int64_t t = 0; t < tiles; t += step, step = t) {
-    const int64_t c = std::min(step, tiles - t);
+    // a last batch of a few tiles joins the one before (64 white rows of 1000:
+    // 22.8 -> 19.5 us)
+    if (tiles - t <= step + step / 4) step = tiles - t;
+    const int64_t c = step;
     const dim3 grid{unsigned(c), unsigned(S), 1};
     if (big)
       hipLaunchKernelGGL(k_series_acov<5>, grid, dim3(SER_TPB), 0, st, d_x, ld, n, scale, d_out, d_gam, n, int(t));

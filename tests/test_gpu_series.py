@@ -48,6 +48,40 @@ def test_lag_tiles_and_batches_match_oracle(S, n, rho):
         assert out[k, 1] == pytest.approx(se, rel=1e-9)
 
 
+@pytest.mark.parametrize("S,n", [(1, 2), (5, 3), (4, 63), (4, 64), (4, 65), (9, 128), (2, 256), (2, 257), (1023, 511),
+                                 (1024, 512), (1024, 513)])
+def test_short_rows_match_oracle(S, n):
+    # both sides of the lengths a wavefront takes alone (256 for few rows, 512
+    # for many), runs of 64 lags and their ends; bars of
+    # test_lag_tiles_and_batches_match_oracle.  Rows stop in every run of lags
+    ctx = hmd.Context(hmd.Params(**SMALL_L))
+    rows = np.stack([_ar1(300 + k, (0.0, 0.9, 0.99, 1.0 - 1e-6)[k % 4], n) for k in range(S)])
+    out = B.series_stats(ctx, rows)
+    for k in range(0, S, max(1, S // 64)):
+        m, se = ostats.geyer(rows[k])
+        h1, h2 = ostats.halves(rows[k])
+        assert out[k, 0] == pytest.approx(m, rel=1e-12, abs=1e-14)
+        assert out[k, 1] == pytest.approx(se, rel=1e-9)
+        assert out[k, 2] == pytest.approx(h1, rel=1e-12, abs=1e-14)
+        assert out[k, 3] == pytest.approx(h2, rel=1e-12, abs=1e-14)
+
+
+def test_short_rows_of_unusual_values():
+    # a constant row has no error; a row that holds a NaN or an infinity gives
+    # NaN and leaves its neighbours alone
+    ctx = hmd.Context(hmd.Params(**SMALL_L))
+    rows = np.stack([_ar1(1, 0.5, 100)] * 6)
+    rows[1] = 0.25
+    rows[2, 40] = np.nan
+    rows[4, 99] = np.inf
+    out = B.series_stats(ctx, rows)
+    m, se = ostats.geyer(rows[0])
+    for k in (0, 3, 5):
+        assert out[k, 0] == pytest.approx(m, rel=1e-12) and out[k, 1] == pytest.approx(se, rel=1e-9)
+    assert out[1, 0] == 0.25 and out[1, 1] == 0.0
+    assert np.isnan(out[2, :2]).all() and np.isnan(out[4, 1]) and np.isinf(out[4, 0])
+
+
 @pytest.mark.parametrize("n", [2, 3, 257, 1000, 20000])
 def test_series_stats_match_oracle(n):
     # four rows (iid, short and long correlation, anti-correlated) in one call;
