@@ -624,12 +624,16 @@ void with_tiles(int H, F f) {
   else f(std::integral_constant<int, 4>{});
 }
 
-// Queues the members' outputs at m queries: 16 queries per wavefront and turn,
-// as many workgroups as two turns each allow up to 512 per member (with 5
-// members ten per compute unit).
+// Queues the members' outputs at m queries: 16 queries per wavefront and turn.
+// One turn each up to a workgroup per compute unit (5 members of 64 units, 200
+// to 3,000 queries: 16 us, 20 with two turns), then two, up to 512 workgroups
+// per member, which share the loads of the hidden layer (5,000 queries: 20 us,
+// 23 with one).
 void enqueue_members(const hmd_ens* e, int m, const double* dXq, float* yout, hipStream_t s) {
-  const int H = e->cfg.hidden, tiles = (m + 15) / 16;
-  const dim3 grid{unsigned(std::min(512, (tiles + 7) / 8)), unsigned(e->cfg.members), 1};
+  constexpr int kUnits = 256;
+  const int H = e->cfg.hidden, tiles = (m + 15) / 16, one = (tiles + 3) / 4;
+  const int blocks = one * e->cfg.members <= kUnits ? one : std::min(512, (tiles + 7) / 8);
+  const dim3 grid{unsigned(blocks), unsigned(e->cfg.members), 1};
   with_tiles(H, [&](auto tiles) {
     hipLaunchKernelGGL(k_ens_member_out<decltype(tiles)::value>, grid, dim3(256), 0, s, m, H, e->dparams, dXq, e->mu[0],
                        e->mu[1], e->sd[0], e->sd[1], yout);

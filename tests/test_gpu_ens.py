@@ -143,3 +143,18 @@ def test_tile_edges(ctx, n, hidden, bootstrap):
     e = B.Ensemble(ctx, X, y, B.ens_cfg(members=2, hidden=hidden, iters=20, seed=5, bootstrap=bootstrap))
     o = mlp.Ensemble(X, y, members=2, hidden=hidden, iters=20, seed=5, bootstrap=bool(bootstrap))
     np.testing.assert_allclose(e.losses(), o.losses, rtol=1e-3)
+
+
+@pytest.mark.parametrize("hidden", [17, 64])
+@pytest.mark.parametrize("m", [1, 15, 17, 64, 65, 3264, 3265, 6500])
+def test_maps_of_any_size_agree(ctx, hidden, m):
+    # one turn per wavefront up to a workgroup per compute unit (3,264 queries
+    # of 5 members), two beyond: a query's outputs do not depend on it
+    X, y = data(40, 6)
+    e = B.Ensemble(ctx, X, y, B.ens_cfg(members=5, hidden=hidden, iters=20))
+    q, _ = data(m, 7)
+    mean, std = e.predict(q)
+    pick = np.unique(np.linspace(0, m - 1, 40).astype(int))
+    alone = [e.predict(q[i:i + 1]) for i in pick]
+    assert np.array_equal(mean[pick], np.concatenate([a[0] for a in alone]))
+    assert np.array_equal(std[pick], np.concatenate([a[1] for a in alone]))
