@@ -1096,15 +1096,26 @@ int refit(hmd_gp* g, bool upload = true) {
 
 // Queues the predictions at m device queries (row-major, d columns).  Few
 // queries of a small database: a workgroup each, the shortest chain (its work
-// grows as m n^2, 11 us at 200 x 256, where the tiles' chain of barriers and
-// exponentials alone is about 20 us).  Else the matrix cores, in row groups of
-// 256 where that fills the chip, of 64 where it does not.
+// grows as m n^2, 13 us a call at 200 x 256, where the tiles' chain of barriers
+// and exponentials alone is about 20 us), with four threads a row as far as
+// two workgroups per compute unit go, with two up to twice that (513 queries of
+// 256 points: 18 us, 24 with four, 26 by tiles; 1,024: 24, 32 and 27; 1,100:
+// 28, 39 and 27).  Else the matrix cores (512 queries of 512 points: 45 us by
+// workgroups, 48 by tiles; of 513: 59 and 52; 513 of 300: 26 with two threads a
+// row and 33 by tiles, 800 of 300: 37 and 33), in row groups of 256 where that
+// fills the chip, of 64 where it does not.
 int enqueue_predict(hmd_gp* g, int m, const double* dXq, double* dmean, double* dvar, hipStream_t s) {
   hmd_ctx* ctx = g->ctx;
   const int n = g->n;
   const KParams P = kparams(g);
   if (n <= 512 && m <= 512) {
     hipLaunchKernelGGL(k_gp_predict<4>, dim3(m), dim3(1024), sizeof(double) * size_t(n), s, n, g->ld, g->dX, dXq,
+                       g->dLi, g->dalpha, P, g->s_q, dmean, dvar);
+    HMD_HIP(ctx, hipGetLastError());
+    return HMD_OK;
+  }
+  if (n <= 256 && m <= 1024) {
+    hipLaunchKernelGGL(k_gp_predict<2>, dim3(m), dim3(512), sizeof(double) * size_t(n), s, n, g->ld, g->dX, dXq,
                        g->dLi, g->dalpha, P, g->s_q, dmean, dvar);
     HMD_HIP(ctx, hipGetLastError());
     return HMD_OK;

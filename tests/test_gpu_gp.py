@@ -81,6 +81,18 @@ def test_predict_kernels_match_oracle(ctx, n, m):
     assert np.abs(vg - vo).max() <= 1e-9 * o.s_q ** 2
 
 
+@pytest.mark.parametrize("n,m", [(1, 513), (40, 1024), (256, 513), (256, 1024), (40, 1025), (256, 1025), (257, 513)])
+def test_predict_kernels_of_small_databases_match_oracle(ctx, n, m):
+    # two threads a row, and the tiles on either side; bars of
+    # test_fit_predict_matches_oracle
+    X, y, se = data(n, 40 + n)
+    g, o = B.GP(ctx, X, y, se, B.gp_hyper(ranges=RANGES)), OGP(X, y, se, Hyper(ranges=RANGES))
+    Xs, _, _ = data(m, 70 + m)
+    (mg, vg), (mo, vo) = g.predict(Xs), o.predict(Xs)
+    assert np.abs(mg - mo).max() <= 1e-9 * np.abs(mo).max() + 1e-12
+    assert np.abs(vg - vo).max() <= 1e-9 * o.s_q ** 2
+
+
 def test_append_matches_oracle_refit(ctx):
     X, y, se = data(40, 7)
     g = B.GP(ctx, X[:30], y[:30], se[:30], B.gp_hyper(ranges=RANGES))
