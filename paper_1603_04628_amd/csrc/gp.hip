@@ -979,11 +979,17 @@ void normalise(hmd_gp* g) {
       // sum of |x_i - x_j| over pairs: in ascending order, x_i is the larger
       // of i pairs; from the smallest value on, so that no part cancels
       std::vector<double> v(n);
-      for (int i = 0; i < n; ++i) v[i] = g->X[size_t(i) * d + k];
-      std::sort(v.begin(), v.end());
-      double s = 0.0;
-      for (int i = 1; i < n; ++i) s += (v[i] - v[i - 1]) * (double(i) * double(n - i));
-      m = s / (0.5 * double(n) * double(n - 1));
+      bool ordered = true;  // a NaN has no place in the order: its mean distance is none either
+      for (int i = 0; i < n; ++i) {
+        v[i] = g->X[size_t(i) * d + k];
+        ordered = ordered && v[i] == v[i];
+      }
+      if (ordered) {
+        std::sort(v.begin(), v.end());
+        double s = 0.0;
+        for (int i = 1; i < n; ++i) s += (v[i] - v[i - 1]) * (double(i) * double(n - i));
+        m = s / (0.5 * double(n) * double(n - 1));
+      }
     }
     g->scale[k] = m > 0.0 ? m : fallback;
   }

@@ -165,6 +165,24 @@ def test_evidence_search_past_sets_that_are_not_spd(ctx, n):
     assert g.log_marginal() == pytest.approx(best, rel=1e-10)
 
 
+@pytest.mark.parametrize("n", [3, 40, 300])
+def test_nan_inputs_are_refused_and_leave_the_default_scale(ctx, n):
+    X, y, se = data(n, 8)
+    g = B.GP(ctx, X, y, se, B.gp_hyper(ranges=RANGES))
+    own = g.scales()[0]
+    with pytest.raises(B.HmdError) as e:
+        g.append([np.nan, 0.01], 0.1, 0.01)
+    assert e.value.code == B.HMD_ENOTSPD
+    sc = g.scales()[0]
+    assert sc[0] == 0.25 * RANGES[0] and sc[0] != own[0]
+    assert sc[1] != 0.25 * RANGES[1]
+    X[n // 2, 1] = np.nan
+    X[0, 1] = np.nan
+    with pytest.raises(B.HmdError) as e:
+        B.GP(ctx, X, y, se, B.gp_hyper(ranges=RANGES))
+    assert e.value.code == B.HMD_ENOTSPD
+
+
 def test_database_size_limit(ctx):
     X = np.column_stack([np.linspace(4, 20, 6145), np.full(6145, 0.01)])
     with pytest.raises(B.HmdError) as e:
