@@ -1129,7 +1129,13 @@ int enqueue_predict(hmd_gp* g, int m, const double* dXq, double* dmean, double* 
   const int qb = (m + PQ - 1) / PQ;
   const bool wide = int64_t(qb) * ((n + 255) / 256) >= 512;
   const int rows = wide ? 256 : 64, groups = (n + rows - 1) / rows;
-  const size_t need = size_t(groups) * size_t(m);
+  // scratch for any size of the database up to its reserved columns and for
+  // any fewer queries (groups of 64 rows: fewer than 512 workgroups of 256 rows
+  // by 32 queries): once a call of m queries has run, calls of up to m allocate
+  // nothing until the database outgrows its columns, so that they can be
+  // captured, and graphs that hold the scratch stay valid
+  const size_t cols = size_t(g->cap);
+  const size_t need = std::max((cols + 255) / 256 * m, std::min<size_t>((cols + 63) / 64 * m, 4 * 512 * PQ));
   if (need > g->part_cap) {
     HMD_HIP(ctx, hipStreamSynchronize(s));  // the old scratch may still be read
     if (g->dpart) (void)hipFree(g->dpart);

@@ -93,6 +93,34 @@ def test_predict_kernels_of_small_databases_match_oracle(ctx, n, m):
     assert np.abs(vg - vo).max() <= 1e-9 * o.s_q ** 2
 
 
+def test_predictions_under_capture_after_the_database_grew(ctx):
+    # a call of 1,000 queries on 600 points; then, with 700 points in the same
+    # reserved columns, 700 queries (in narrower row groups) and 1,000 are
+    # captured without an allocation, and replays match eager results with
+    # eager work between them
+    import torch
+    X, y, se = data(700, 9)
+    g = B.GP(ctx, X[:600], y[:600], se[:600], B.gp_hyper(ranges=RANGES))
+    q = torch.from_numpy(data(1000, 10)[0]).cuda()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g.predict_dev(q)
+    torch.cuda.synchronize()
+    for k in range(600, 700):
+        g.append(X[k], y[k], se[k])
+    for m in (700, 1000):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            mean, var = g.predict_dev(q[:m])
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            got = mean.clone(), var.clone()
+            want = g.predict_dev(q[:m])
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_append_matches_oracle_refit(ctx):
     X, y, se = data(40, 7)
     g = B.GP(ctx, X[:30], y[:30], se[:30], B.gp_hyper(ranges=RANGES))
