@@ -90,6 +90,7 @@ void hmd_destroy(hmd_ctx* ctx) {
     (void)hipDeviceSynchronize();
     (void)hipFree(ctx->d_series_scratch);
   }
+  if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
 }

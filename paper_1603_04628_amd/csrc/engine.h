@@ -23,6 +23,10 @@ struct hmd_ctx {
   // device scratch of md_series_stats_dev (autocovariances), grown on demand
   double* d_series_scratch = nullptr;
   int64_t series_scratch_n = 0;
+  // pinned host memory for downloads, grown on demand (every use ends before
+  // its call returns)
+  void* h_stage = nullptr;
+  size_t stage_bytes = 0;
 };
 
 namespace hmd {
@@ -176,8 +180,6 @@ struct hmd_batch {
   int64_t small_n = 0;              // its leading words that batch_results reads (Acc's per-system sums,
                                     // d_sout, d_flag, d_status)
   int* d_status = nullptr;
-  void* h_stage = nullptr;          // pinned host memory for downloads
-  size_t stage_bytes = 0;
 
   int cur = 0;  // cell path: which state copy is current (pair path: always 0)
   int64_t done = 0;

@@ -836,7 +836,6 @@ void batch_free(hmd_batch* b) {
                   b->d_tilerec, b->d_tbins, b->d_gam, b->d_stamps};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
-  if (b->h_stage) (void)hipHostFree(b->h_stage);
   for (int w = 0; w < 2; ++w)
     for (int a = 0; a < 6; ++a)
       if (b->d_state[w][a]) (void)hipFree(b->d_state[w][a]);
@@ -958,24 +957,25 @@ int batch_run(hmd_batch* b, int64_t steps, int graph_chunk, bool thermostat, dou
 
 namespace {
 
-// Pinned host memory of the batch for downloads, at least `bytes` (null: not to
-// be had; its earlier contents are dropped).  A copy into memory of the
-// caller's costs 15 to 25 us of staging each.
-void* stage(hmd_batch* b, size_t bytes) {
+// Pinned host memory of the context for downloads, at least `bytes` (null: not
+// to be had; its earlier contents are dropped).  A copy into memory of the
+// caller's costs 15 to 25 us of staging each; allocating it anew for every
+// batch took 40 us and now and then near a millisecond of the first download.
+void* stage(hmd_ctx* ctx, size_t bytes) {
   constexpr size_t kMaxStage = size_t(64) << 20;
   if (bytes > kMaxStage) return nullptr;
-  if (bytes > b->stage_bytes) {
-    if (b->h_stage) (void)hipHostFree(b->h_stage);
-    b->stage_bytes = 0;
-    const size_t want = std::max<size_t>(bytes, 1 << 16);
-    if (hipHostMalloc(&b->h_stage, want, hipHostMallocDefault) != hipSuccess) {
+  if (bytes > ctx->stage_bytes) {
+    if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
+    const size_t want = std::min(kMaxStage, std::max({bytes, 2 * ctx->stage_bytes, size_t(1) << 16}));
+    ctx->stage_bytes = 0;
+    if (hipHostMalloc(&ctx->h_stage, want, hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
-      b->h_stage = nullptr;
+      ctx->h_stage = nullptr;
       return nullptr;
     }
-    b->stage_bytes = want;
+    ctx->stage_bytes = want;
   }
-  return b->h_stage;
+  return ctx->h_stage;
 }
 
 }  // namespace
@@ -996,7 +996,7 @@ int batch_results(hmd_batch* b, hmd_md_result* out) {
     series_stats_enqueue(s, b->acc.blocks, n, b->nser, b->nser, 1.0 / double(b->ser_B), b->P.n_blocks, b->d_gam,
                          b->d_sout);
   std::vector<double> pageable;
-  double* h = static_cast<double*>(stage(b, 8 * size_t(b->small_n)));
+  double* h = static_cast<double*>(stage(ctx, 8 * size_t(b->small_n)));
   if (!h) {
     pageable.resize(b->small_n);
     h = pageable.data();
@@ -1055,7 +1055,7 @@ int batch_series(hmd_batch* b, int sim, double* q, int64_t* n, int which) {
   if (!q) return HMD_OK;
   HMD_HIP(ctx, hipSetDevice(ctx->device));
   const double* src = which ? b->acc.pblocks : b->acc.blocks;
-  double* h = static_cast<double*>(stage(b, 8 * size_t(b->nser)));
+  double* h = static_cast<double*>(stage(ctx, 8 * size_t(b->nser)));
   if (!h) h = q;
   HMD_HIP(ctx, hipMemcpyAsync(h, src + int64_t(sim) * b->nser, 8 * size_t(b->nser), hipMemcpyDeviceToHost,
                               ctx->stream));
@@ -1151,7 +1151,7 @@ int batch_get_state(hmd_batch* b, int sim, double* x, double* v) {
   const SimDev& D = b->sims[sim];
   const size_t n = size_t(D.nf), bytes = 8 * (6 * n + 1) + 4 * n;
   std::vector<char> pageable;
-  char* h = static_cast<char*>(stage(b, bytes));
+  char* h = static_cast<char*>(stage(ctx, bytes));
   if (!h) {
     pageable.resize(bytes);
     h = pageable.data();

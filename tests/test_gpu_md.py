@@ -596,6 +596,33 @@ def test_batch_equals_single_systems():
         assert r1["pe"] == pytest.approx(r["pe"], rel=1e-3)
 
 
+def test_downloads_of_batches_that_share_a_context():
+    # the context's pinned buffer serves every batch of it and grows with the
+    # largest download: small and large in turn, after the small one is freed
+    # too, as from contexts of their own
+    small, large = (dict(h=5.0, n=40), dict(h=15.0, n=9000))
+    own = []
+    for c in (small, large):
+        b = hmd.Batch(hmd.Context(hmd.Params(**SMALL_L)), [(c["h"], 0.02, 3, c["n"])])
+        b.run(20, graph_chunk=0)
+        own.append((b.get_state(0), b.series(0), b.results()))
+    ctx = hmd.Context(hmd.Params(**SMALL_L))
+    bs = [hmd.Batch(ctx, [(c["h"], 0.02, 3, c["n"])]) for c in (small, large)]
+    for b in bs:
+        b.run(20, graph_chunk=0)
+    for k in (0, 1, 0, 1):
+        if bs[k] is None:
+            continue
+        (x, v), q, r = own[k]
+        xs, vs = bs[k].get_state(0)
+        assert np.abs(xs - x).max() <= 1e-6 and np.abs(vs - v).max() <= 1e-4
+        assert np.abs(bs[k].series(0) - q).max() <= 1e-4
+        assert bs[k].results()[0]["pe"] == pytest.approx(r[0]["pe"], rel=1e-5)
+        if k == 0:
+            bs[0].close()
+            bs[0] = None
+
+
 @pytest.mark.parametrize("path", PATHS)
 def test_graph_replay_equals_direct_launches(path):
     # same steps as direct launches and as graph replays: trajectories agree
