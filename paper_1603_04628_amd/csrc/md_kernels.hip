@@ -758,17 +758,17 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
     if ((threadIdx.x & (WAVE - 1)) == 0) {
       const SimDev& Dw = sims[sw];
       atomicAdd(&acc.blocks[int64_t(sw) * K.nb + b], q0 * Dw.inv_area);
-      atomicAdd(&acc.tsum[3 * sw + 0], q1 * Dw.inv_nf);
-      atomicAdd(&acc.tsum[3 * sw + 1], q2 * Dw.inv_nf);
-      atomicAdd(&acc.tsum[3 * sw + 2], q3 * Dw.inv_nf);
+      atomicAdd(&acc.tsum[sw], q1 * Dw.inv_nf);
+      atomicAdd(&acc.tsum[acc.tpitch + sw], q2 * Dw.inv_nf);
+      atomicAdd(&acc.tsum[2 * acc.tpitch + sw], q3 * Dw.inv_nf);
       if (K.press_on) atomicAdd(&acc.pblocks[int64_t(sw) * K.nb + b], q4 * Dw.inv_area);
     }
   } else if (valid) {
     const SimDev& D = sims[s];
     atomicAdd(&acc.blocks[int64_t(s) * K.nb + b], q0 * D.inv_area);
-    atomicAdd(&acc.tsum[3 * s + 0], q1 * D.inv_nf);
-    atomicAdd(&acc.tsum[3 * s + 1], q2 * D.inv_nf);
-    atomicAdd(&acc.tsum[3 * s + 2], q3 * D.inv_nf);
+    atomicAdd(&acc.tsum[s], q1 * D.inv_nf);
+    atomicAdd(&acc.tsum[acc.tpitch + s], q2 * D.inv_nf);
+    atomicAdd(&acc.tsum[2 * acc.tpitch + s], q3 * D.inv_nf);
     if (K.press_on) atomicAdd(&acc.pblocks[int64_t(s) * K.nb + b], q4 * D.inv_area);
   }
   if (!K.bins_on) return;
@@ -783,8 +783,8 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
       if (bb < BIN_LDS) {
         atomicAdd(&tbin[bb], tbin_word(v0));
       } else {
-        atomicAdd(&acc.binvx[gb], v0);
-        atomicAdd(&acc.bincnt[gb], 1.0);
+        atomicAdd(&acc.binvx[gb * kBinPitch], v0);
+        atomicAdd(&acc.bincnt[gb * kBinPitch], 1.0);
       }
     }
   }
@@ -801,15 +801,15 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
       atomicAdd(&lds_vx[o], v0);
       atomicAdd(&lds_cnt[o], 1.0);
     } else {
-      atomicAdd(&acc.binvx[gb], v0);
-      atomicAdd(&acc.bincnt[gb], 1.0);
+      atomicAdd(&acc.binvx[gb * kBinPitch], v0);
+      atomicAdd(&acc.bincnt[gb * kBinPitch], 1.0);
     }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < BIN_LDS; k += blockDim.x)
     if (lds_cnt[k] != 0.0) {
-      atomicAdd(&acc.binvx[base + k], lds_vx[k]);
-      atomicAdd(&acc.bincnt[base + k], lds_cnt[k]);
+      atomicAdd(&acc.binvx[(base + k) * kBinPitch], lds_vx[k]);
+      atomicAdd(&acc.bincnt[(base + k) * kBinPitch], lds_cnt[k]);
     }
 }
 
@@ -1914,7 +1914,7 @@ __device__ __forceinline__ void force_tiles(
         else if (q == 2) dst = (p ? acc.pe[1] : acc.pe[0]) + s;
         else if (q == 3) { dst = acc.blocks + int64_t(s) * K.nb + (ns - K.r) / K.B; tot *= D.inv_area; }
         else if (q == 7) { dst = acc.pblocks + int64_t(s) * K.nb + (ns - K.r) / K.B; tot *= D.inv_area; }
-        else { dst = acc.tsum + 3 * s + (q - 4); tot *= D.inv_nf; }
+        else { dst = acc.tsum + (q - 4) * acc.tpitch + s; tot *= D.inv_nf; }
         atomicAdd(dst, tot);
       }
     }

@@ -581,6 +581,41 @@ def test_profile_bins_match_oracle(path):
     assert np.abs(mvx - mvo).max() <= 1e-6 * max(1.0, np.abs(mvo).max())
 
 
+@pytest.mark.parametrize("path", PATHS)
+def test_profiles_of_more_bins_than_a_workgroup_holds_match_oracle(path):
+    # 150 bins: those past 128 are added to atom by atom; bars of
+    # test_profile_bins_match_oracle
+    fine = dict(SMALL_L, bin_dy=0.04)
+    pre = omd.System(6.0, 0.05, 7, omd.Params(**fine))
+    pre.run(300)
+    x, v = pre.get_state()
+    ctx, g_sys, o_sys = _pair(6.0, 0.05, 7, path, n_equil=0, **fine)
+    g_sys.set_state(x, v)
+    o_sys.set_state(x, v)
+    g_sys.run(10)
+    o_sys.run(10)
+    mvx, cnt = g_sys.profile()
+    mvo, cno = o_sys.profile()
+    assert len(cnt) == 150 and cnt[128:].sum() > 0
+    assert np.array_equal(cnt, cno)
+    assert np.abs(mvx - mvo).max() <= 1e-6 * max(1.0, np.abs(mvo).max())
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("S", [1, 16, 17])
+def test_temperatures_of_a_batch_are_those_of_its_states(S, path):
+    # each component's sums start a cache line of their own (16 systems fill
+    # one).  Rounding of sums of a thousand terms, in another order.
+    ctx = hmd.Context(hmd.Params(force_path=path, **SMALL_L))
+    b = hmd.Batch(ctx, [(4.0 + 0.25 * k, 0.02, 3 + k, 4) for k in range(S)])
+    want = np.zeros((S, 3))
+    for _ in range(4):
+        b.run(1, 0)
+        want += [(b.get_state(k)[1] ** 2).mean(axis=0) for k in range(S)]
+    for r, w in zip(b.results(), want):
+        np.testing.assert_allclose(r["T"], w / 4.0, rtol=1e-12)
+
+
 def test_batch_equals_single_systems():
     p = hmd.Params(**SMALL_L)
     ctx = hmd.Context(p)
