@@ -30,6 +30,13 @@ constexpr int SER_TPB = 256;
 // autocovariances (consumed by then; gamma_0 is still needed).
 constexpr int kTotal = 1, kSmallest = 2, kDone = 3;
 
+// Orders LDS accesses of a wavefront's lanes to each other's data.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace
 
 // out[s*4 + 0] = mean, [2] = mean of the first n/2 samples, [3] = mean of
@@ -80,11 +87,12 @@ __global__ __launch_bounds__(MOM_TPB) void k_series_moments(const double* __rest
 // (see k_series_geyer) over 64 lags at a time, a lag per lane, each summed in
 // ascending i from LDS, until the sequence ends.  The matrix form below works
 // in pieces of 1024 samples and 304 lags, which rows of a few hundred samples
-// leave empty (65,535 rows of 16: 56 us, 2,020 in matrix form).  What bounds it
+// leave empty (65,535 rows of 16: 57 us, 520 in matrix form).  What bounds it
 // is the chain of a row's products and the LDS, two reads per product: for few
-// rows it is the better one up to about 256 samples (64 random walks of 200:
-// 13 against 18 us, of 384: 26 against 19), for many up to 512 (512 walks of
-// 384: 27 against 40 us; 20,000 of 384: 195 against 1,180).
+// rows it is the better one up to about 256 samples (a call with 64 random walks
+// of 200: 14 against 23 us, of 384: 28 against 23), for many up to 512 (1,024
+// white rows of 512 20 against 38 us, walks 45 against 39; 20,000 walks 297
+// against 476).
 constexpr int SHORT_N = 512;
 
 bool short_rows(int S, int64_t n) { return n <= std::min(256 + S / 4, SHORT_N); }
@@ -112,9 +120,7 @@ __global__ __launch_bounds__(SER_TPB) void k_series_short(const double* __restri
   const double mean = (a + b) / double(n);
   for (int i = l; i < n; i += 64) d[i] -= mean;  // the lane's own
   d[n + l] = 0.0;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_lds_fence();
   double total = 0.0, smallest = INFINITY, g0 = 0.0;
   bool any = false, stop = false;
   for (int t0 = 0; t0 < n && !stop; t0 += 64) {
@@ -158,8 +164,8 @@ __global__ __launch_bounds__(SER_TPB) void k_series_short(const double* __restri
 // consecutive samples, read from LDS without conflict, and one read feeds
 // 1024 products (a loop over lags made 64 of one, and the LDS bounded it at 13
 // TFLOP/s).  64 rows of 20,000 samples correlated over 1000: 2.09 ms before,
-// 0.24 ms with the batches below; what bounds a batch now is the matrix rate
-// (2,432 lags of 64 rows in 0.13 ms, 48 TFLOP/s).
+// 0.2 ms with the batches below; what bounds a batch now is the matrix rate
+// (2,432 lags of 64 rows in 0.125 ms, 50 TFLOP/s).
 //
 // A workgroup takes 4 NS shifts s, NS per wavefront, of one row: the lags
 // 16 s0 .. 16 (s0 + 4 NS - 1) - 1, (the last shift only completes them).  NS =
@@ -170,13 +176,12 @@ __global__ __launch_bounds__(SER_TPB) void k_series_short(const double* __restri
 constexpr int AC_CH = 1024;  // samples per pass
 
 template <int NS>
-__global__ __launch_bounds__(SER_TPB) void k_series_acov(const double* __restrict__ x, int64_t ld, int64_t n,
+__global__ __launch_bounds__(SER_TPB, NS == 5 ? 4 : 6) void k_series_acov(const double* __restrict__ x, int64_t ld, int64_t n,
                                                         double scale, const double* __restrict__ mom,
                                                         double* __restrict__ gam, int64_t gld, int tile0) {
   using f64x4 = __attribute__((ext_vector_type(4))) double;
   constexpr int SH = 4 * NS, LAGS = 16 * (SH - 1);
   __shared__ double a[AC_CH], b[AC_CH + 16 * SH];
-  __shared__ double lag[16 * SH];
   const int s = blockIdx.y, tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   double* const g = gam + int64_t(s) * gld;
   if (tile0 > 0 && g[kDone] != 0.0) return;
@@ -196,40 +201,47 @@ __global__ __launch_bounds__(SER_TPB) void k_series_acov(const double* __restric
       b[e] = i < n ? row[i] * scale - mean : 0.0;
     }
     __syncthreads();
-    for (int c = 0; c < AC_CH; c += 64) {
-      const double av = a[c + l];
+    auto products = [&](int end) {
+      for (int c = 0; c < end; c += 64) {
+        const double av = a[c + l];
 #pragma unroll
-      for (int k = 0; k < NS; ++k)
-        acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b[c + 16 * (w * NS + k) + l], acc[k], 0, 0, 0);
-    }
-  }
-  // lane l, element t holds G_s[4 t + l / 16][l % 16]: lag 16 s + r' - r
-  for (int e = tid; e < 16 * SH; e += SER_TPB) lag[e] = 0.0;
-  __syncthreads();
-#pragma unroll 1
-  for (int k = 0; k < SH; ++k) {  // shifts in turn: a fixed order of the sums
-    if (w == k / NS) {
-      double* const st = w & 1 ? b : a;  // 256 values of one shift (the samples are done with)
-#pragma unroll
-      for (int q = 0; q < NS; ++q)
-        if (q == k % NS)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) st[(4 * t + (l >> 4)) * 16 + (l & 15)] = acc[q][t];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (l < 31) {  // lag 16 k + l - 15
-        const int u = l - 15, lo = u < 0 ? -u : 0, hi = u < 0 ? 16 : 16 - u;
-        double v = 0.0;
-        for (int r = lo; r < hi; ++r) v += st[r * 16 + r + u];
-        const int t = 16 * k + u;
-        if (t >= 0) lag[t] += v;
+        for (int k = 0; k < NS; ++k)
+          acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b[c + 16 * (w * NS + k) + l], acc[k], 0, 0, 0);
       }
-    }
-    __syncthreads();
+    };
+    // the last pass stops with the row (a call with 300 rows of 512: 38 -> 34 us)
+    if (n - t0 - i0 >= AC_CH) products(AC_CH);
+    else products(int(n - t0 - i0));
   }
-  for (int e = tid; e < LAGS; e += SER_TPB)
-    if (t0 + e < n) g[t0 + e] = lag[e] / double(n);
+  // lane l, element t holds G_s[4 t + l / 16][l % 16]: lag 16 s + r' - r.  Each
+  // wavefront sums the 31 diagonals of its shifts (the samples are done with);
+  // a lag has one of its shift and one of the next.  Shift after shift, with a
+  // barrier each, this was most of a short row's time: 512 rows of 512 took 44 us,
+  // 16 now
+  __syncthreads();
+  double* const st = a + 256 * w;  // a shift's 256 values
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) st[(4 * t + (l >> 4)) * 16 + (l & 15)] = acc[k][t];
+    wave_lds_fence();
+    const int u = l - 15;  // lag 16 (w NS + k) + u
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const double x = st[r * 16 + min(max(r + u, 0), 15)];
+      v += r + u >= 0 && r + u < 16 ? x : 0.0;
+    }
+    if (l < 31) b[(w * NS + k) * 32 + l] = v;
+    wave_lds_fence();
+  }
+  __syncthreads();
+  for (int e = tid; e < LAGS; e += SER_TPB) {
+    const int u = e & 15;
+    const double* const d = b + (e >> 4) * 32 + u;
+    const double lag = d[15] + (u > 0 ? d[31] : 0.0);  // d[31]: the next shift's u - 16
+    if (t0 + e < n) g[t0 + e] = lag / double(n);
+  }
 }
 
 // Geyer's initial monotone sequence: Gamma_k = gamma_2k + gamma_2k+1 while
@@ -348,12 +360,14 @@ void series_stats_enqueue(hipStream_t st, const double* d_x, int S, int64_t n, i
     hipLaunchKernelGGL(k_series_blocks, dim3(S), dim3(SER_TPB), 0, st, d_x, ld, n, scale, n_blocks, d_out);
     return;
   }
-  // Batches of lag tiles: enough workgroups to fill the chip, then twice as
-  // many lags each time.  Where rows are few one batch holds every lag.
+  // Batches of lag tiles: enough workgroups to fill the chip (narrow tiles four
+  // per compute unit: a second batch's two launches cost more than the lags it
+  // may save, 200 rows of 512 28 against 23 us a call), then twice as many lags
+  // each time.  Where rows are few one batch holds every lag.
   const int64_t wide = 16 * (4 * 5 - 1), narrow = 16 * (4 * 2 - 1);
   const bool big = int64_t(S) * ((n + wide - 1) / wide) >= 512;
   const int64_t lags = big ? wide : narrow, tiles = (n + lags - 1) / lags, pairs = n / 2;
-  int64_t step = std::max<int64_t>(2, (512 + S - 1) / S);
+  int64_t step = std::max<int64_t>(2, ((big ? 512 : 1024) + S - 1) / S);
   for (int64_t t = 0; t < tiles; t += step, step = t) {
     // a last batch of a few tiles joins the one before (64 white rows of 1000:
     // 22.8 -> 19.5 us)

@@ -48,6 +48,22 @@ def test_lag_tiles_and_batches_match_oracle(S, n, rho):
         assert out[k, 1] == pytest.approx(se, rel=1e-9)
 
 
+@pytest.mark.parametrize("S,n", [(200, 511), (200, 512), (204, 600), (205, 600), (255, 513), (256, 513), (300, 575),
+                                 (300, 576), (300, 577), (3, 1023), (3, 1025), (3, 1087), (3, 1088), (3, 1135),
+                                 (9, 1136), (40, 2049)])
+def test_rows_that_end_inside_a_pass_match_oracle(S, n):
+    # ends of the last pass of 1,024 samples around whole steps of 64, on both
+    # sides of the choice of tiles and of their batches; bars of
+    # test_lag_tiles_and_batches_match_oracle
+    ctx = hmd.Context(hmd.Params(**SMALL_L))
+    rows = np.stack([_ar1(300 + k, (0.0, 0.9, 0.998)[k % 3], n) for k in range(S)])
+    out = B.series_stats(ctx, rows)
+    for k in sorted({0, 1, 2, S // 2, S - 1}):
+        m, se = ostats.geyer(rows[k])
+        assert out[k, 0] == pytest.approx(m, rel=1e-12, abs=1e-14)
+        assert out[k, 1] == pytest.approx(se, rel=1e-9)
+
+
 @pytest.mark.parametrize("S,n", [(1, 2), (5, 3), (4, 63), (4, 64), (4, 65), (9, 128), (2, 256), (2, 257), (1023, 511),
                                  (1024, 512), (1024, 513)])
 def test_short_rows_match_oracle(S, n):
