@@ -98,8 +98,7 @@ struct Acc {
   double* blocks;   // [S * nb] the sampled q' series: entry k of a system holds the sum of
                     // B consecutive steps' q' (B = 1 unless n_sample exceeds the series cap)
   double* pblocks;  // [S * nb] the sampled wall-pressure series, laid out as blocks
-  double* tsum;     // [3 * tpitch] sums of T_a over sampled steps: component a of a system at a * tpitch
-  int64_t tpitch;
+  double* tsum;     // [S * 3] sums of T_a over sampled steps
   double* binvx;    // [bins * kBinPitch] sum v_x
   double* bincnt;   // [bins * kBinPitch] counts
   double* tbins;    // [tiles * BIN_LDS * 2] the tiled path's bins: (sum v_x, count) per tile and bin,

@@ -709,15 +709,14 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   // per-system sums: what the results read first, in one piece (energies,
   // temperature sums, series statistics, flags and status), then the series
   // and the profile.  Atomics on one 64-byte piece of memory wait for each
-  // other, so the sums that a step's wavefronts add to lie apart: thermostat
-  // and temperature sums on cache lines of their own, profile bins a piece
-  // each (one channel of 78,400 atoms on the list path: 70 us a step, 95 with
-  // the sums side by side; a tiled channel of 160 bins and 39,200 atoms: 32 and
-  // 38 us)
+  // other unless one instruction makes them, so what a step's wavefronts add to
+  // one after another lies apart: thermostat and temperature sums on cache lines
+  // of their own, profile bins a piece each (one channel of 78,400 atoms on the
+  // list path: 69 us a step, 95 with the sums side by side; a tiled channel of
+  // 160 bins and 39,200 atoms: 32 and 38 us)
   auto lines = [](int64_t words) { return (words + 15) / 16 * 16; };
-  const int64_t n_sums = lines(6 * int64_t(n)), n_stat = lines(8 * int64_t(n));
-  b->acc.tpitch = lines(n);
-  b->small_n = n_sums + 3 * b->acc.tpitch + n_stat + lines((n + 5) / 2);
+  const int64_t n_sums = lines(6 * int64_t(n)), n_temp = lines(3 * int64_t(n)), n_stat = lines(8 * int64_t(n));
+  b->small_n = n_sums + n_temp + n_stat + lines((n + 5) / 2);
   const int64_t nacc = b->small_n + 2 * int64_t(n) * b->nser + 2 * b->nbins * kBinPitch;
   if ((rc = dalloc(ctx, &b->d_accbuf, nacc)) ||
       (rc = dalloc(ctx, &b->acc.pairs, kPairCounters * kPairPitch)))
@@ -729,7 +728,7 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   for (int p = 0; p < 2; ++p) { b->acc.ke[p] = q; q += n; }
   for (int p = 0; p < 2; ++p) { b->acc.pe[p] = q; q += n; }
   b->acc.tsum = b->d_accbuf + n_sums;
-  b->d_sout = b->acc.tsum + 3 * b->acc.tpitch;
+  b->d_sout = b->acc.tsum + n_temp;
   b->d_flag = reinterpret_cast<int*>(b->d_sout + n_stat);
   b->d_status = b->d_flag + 4;
   q = b->d_accbuf + b->small_n;
@@ -1035,7 +1034,7 @@ int batch_results(hmd_batch* b, hmd_md_result* out) {
         R.p_se = pout[4 * size_t(k) + 1];
       }
       // temperatures are summed over every sampled step
-      for (int a = 0; a < 3; ++a) R.T[a] = tsum[a * b->acc.tpitch + k] / double(b->n_sample);
+      for (int a = 0; a < 3; ++a) R.T[a] = tsum[3 * k + a] / double(b->n_sample);
       // non-convergence (critical shear, Sec. 3.2): the two halves of the
       // series differ by more than 8 SE, or the spanwise temperature runs away
       if (st == HMD_OK && (std::fabs(so[3] - so[2]) > 8.0 * R.flux_se || R.T[2] > 1.5 * b->P.T0))

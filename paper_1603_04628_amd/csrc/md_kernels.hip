@@ -755,20 +755,20 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
     q0 = wave_sum(q0); q1 = wave_sum(q1); q2 = wave_sum(q2); q3 = wave_sum(q3);
     if (K.press_on) q4 = wave_sum(q4);
     const int sw = TB ? s : __shfl(s, 0);
-    if ((threadIdx.x & (WAVE - 1)) == 0) {
-      const SimDev& Dw = sims[sw];
+    const SimDev& Dw = sims[sw];
+    const int lane = threadIdx.x & (WAVE - 1);
+    // the three temperatures by one instruction: one request to their line
+    if (lane < 3) atomicAdd(&acc.tsum[3 * sw + lane], (lane == 0 ? q1 : lane == 1 ? q2 : q3) * Dw.inv_nf);
+    if (lane == 0) {
       atomicAdd(&acc.blocks[int64_t(sw) * K.nb + b], q0 * Dw.inv_area);
-      atomicAdd(&acc.tsum[sw], q1 * Dw.inv_nf);
-      atomicAdd(&acc.tsum[acc.tpitch + sw], q2 * Dw.inv_nf);
-      atomicAdd(&acc.tsum[2 * acc.tpitch + sw], q3 * Dw.inv_nf);
       if (K.press_on) atomicAdd(&acc.pblocks[int64_t(sw) * K.nb + b], q4 * Dw.inv_area);
     }
   } else if (valid) {
     const SimDev& D = sims[s];
     atomicAdd(&acc.blocks[int64_t(s) * K.nb + b], q0 * D.inv_area);
-    atomicAdd(&acc.tsum[s], q1 * D.inv_nf);
-    atomicAdd(&acc.tsum[acc.tpitch + s], q2 * D.inv_nf);
-    atomicAdd(&acc.tsum[2 * acc.tpitch + s], q3 * D.inv_nf);
+    atomicAdd(&acc.tsum[3 * s + 0], q1 * D.inv_nf);
+    atomicAdd(&acc.tsum[3 * s + 1], q2 * D.inv_nf);
+    atomicAdd(&acc.tsum[3 * s + 2], q3 * D.inv_nf);
     if (K.press_on) atomicAdd(&acc.pblocks[int64_t(s) * K.nb + b], q4 * D.inv_area);
   }
   if (!K.bins_on) return;
@@ -1914,7 +1914,7 @@ __device__ __forceinline__ void force_tiles(
         else if (q == 2) dst = (p ? acc.pe[1] : acc.pe[0]) + s;
         else if (q == 3) { dst = acc.blocks + int64_t(s) * K.nb + (ns - K.r) / K.B; tot *= D.inv_area; }
         else if (q == 7) { dst = acc.pblocks + int64_t(s) * K.nb + (ns - K.r) / K.B; tot *= D.inv_area; }
-        else { dst = acc.tsum + (q - 4) * acc.tpitch + s; tot *= D.inv_nf; }
+        else { dst = acc.tsum + 3 * s + (q - 4); tot *= D.inv_nf; }
         atomicAdd(dst, tot);
       }
     }
