@@ -88,7 +88,6 @@ struct StepConst {
 };
 
 constexpr int kPairCounters = 32, kPairPitch = 16;
-constexpr int kBinPitch = 8;  // profile bins are 64 bytes apart
 
 // Per-system FP64 accumulators (device).
 struct Acc {
@@ -99,9 +98,10 @@ struct Acc {
                     // B consecutive steps' q' (B = 1 unless n_sample exceeds the series cap)
   double* pblocks;  // [S * nb] the sampled wall-pressure series, laid out as blocks
   double* tsum;     // [S * 3] sums of T_a over sampled steps
-  double* binvx;    // [bins * kBinPitch] sum v_x
-  double* bincnt;   // [bins * kBinPitch] counts
-  double* tbins;    // [tiles * BIN_LDS * 2] the tiled path's bins: (sum v_x, count) per tile and bin,
+  double* binvx;    // [bins] sum v_x
+  double* bincnt;   // [bins] counts
+  int tb_ld;        // bins of a tile (the most bins of a system, at most BIN_LDS)
+  double* tbins;    // [tiles * tb_ld * 2] the tiled path's bins: (sum v_x, count) per tile and bin,
                     // each tile adding to its own (no atomics; summed per system when read)
   int* status;      // [S] bit 0: unstable
   unsigned long long* pairs;  // in-cutoff fluid-fluid (ordered) and wall-fluid pairs: the sums over

@@ -496,8 +496,10 @@ int make_tiles(hmd_batch* b) {
   }
   b->ntiles = int(tiles.size());
   b->tile_first[b->S] = b->ntiles;
-  HMD_TRY(dalloc(ctx, &b->d_tbins, int64_t(b->ntiles) * BIN_LDS * 2));
-  HMD_HIP(ctx, hipMemsetAsync(b->d_tbins, 0, sizeof(double) * size_t(b->ntiles) * BIN_LDS * 2, ctx->stream));
+  for (const SimDev& D : b->sims) b->acc.tb_ld = std::max(b->acc.tb_ld, std::min(D.nbins, BIN_LDS));
+  const size_t nbin = size_t(b->ntiles) * size_t(b->acc.tb_ld) * 2;
+  HMD_TRY(dalloc(ctx, &b->d_tbins, int64_t(nbin)));
+  HMD_HIP(ctx, hipMemsetAsync(b->d_tbins, 0, sizeof(double) * nbin, ctx->stream));
   HMD_TRY(dalloc(ctx, &b->d_tiles, b->ntiles));
   HMD_TRY(dalloc(ctx, &b->d_tilerec, int64_t(b->ntiles) * TILE_REC));
   HMD_HIP(ctx, hipMemcpyAsync(b->d_tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice,
@@ -709,15 +711,13 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   // per-system sums: what the results read first, in one piece (energies,
   // temperature sums, series statistics, flags and status), then the series
   // and the profile.  Atomics on one 64-byte piece of memory wait for each
-  // other unless one instruction makes them, so what a step's wavefronts add to
-  // one after another lies apart: thermostat and temperature sums on cache lines
-  // of their own, profile bins a piece each (one channel of 78,400 atoms on the
-  // list path: 69 us a step, 95 with the sums side by side; a tiled channel of
-  // 160 bins and 39,200 atoms: 32 and 38 us)
+  // other unless one instruction makes them, so the thermostat and the
+  // temperature sums start cache lines of their own (one channel of 78,400 atoms
+  // on the list path: 69 us a step, 95 with the sums side by side)
   auto lines = [](int64_t words) { return (words + 15) / 16 * 16; };
   const int64_t n_sums = lines(6 * int64_t(n)), n_temp = lines(3 * int64_t(n)), n_stat = lines(8 * int64_t(n));
   b->small_n = n_sums + n_temp + n_stat + lines((n + 5) / 2);
-  const int64_t nacc = b->small_n + 2 * int64_t(n) * b->nser + 2 * b->nbins * kBinPitch;
+  const int64_t nacc = b->small_n + 2 * int64_t(n) * b->nser + 2 * b->nbins;
   if ((rc = dalloc(ctx, &b->d_accbuf, nacc)) ||
       (rc = dalloc(ctx, &b->acc.pairs, kPairCounters * kPairPitch)))
     return fail(rc);
@@ -734,7 +734,7 @@ int batch_create(hmd_ctx* ctx, const hmd_md_job* jobs, int n, hmd_batch** out) {
   q = b->d_accbuf + b->small_n;
   b->acc.blocks = q; q += int64_t(n) * b->nser;
   b->acc.pblocks = q; q += int64_t(n) * b->nser;
-  b->acc.binvx = q; q += b->nbins * kBinPitch;
+  b->acc.binvx = q; q += b->nbins;
   b->acc.bincnt = q;
   b->acc.tbins = b->d_tbins;
   b->acc.status = b->d_status;
@@ -1356,29 +1356,33 @@ int batch_profile(hmd_batch* b, int sim, double* mvx, double* cnt) {
   hmd_ctx* ctx = b->ctx;
   if (sim < 0 || sim >= b->S) return HMD_EINVAL;
   const SimDev& D = b->sims[sim];
-  // per-system bins plus, on the tiled path, the system's per-tile bins
-  std::vector<double> a(D.nbins), c(D.nbins);
-  std::vector<double> h(size_t(D.nbins) * kBinPitch);
-  auto bins = [&](const double* src, std::vector<double>& out) -> int {
-    HMD_HIP(ctx, hipMemcpy(h.data(), src + int64_t(D.bin0) * kBinPitch, 8 * h.size(), hipMemcpyDeviceToHost));
-    for (size_t k = 0; k < out.size(); ++k) out[k] = h[k * kBinPitch];
-    return HMD_OK;
-  };
-  HMD_TRY(bins(b->acc.binvx, a));
-  HMD_TRY(bins(b->acc.bincnt, c));
-  if (b->d_tbins) {
-    const int t0 = b->tile_first[sim], t1 = b->tile_first[sim + 1];
-    std::vector<double> tb(size_t(t1 - t0) * BIN_LDS * 2);
-    HMD_HIP(ctx, hipMemcpy(tb.data(), b->d_tbins + size_t(t0) * BIN_LDS * 2, 8 * tb.size(), hipMemcpyDeviceToHost));
-    const int nb = std::min(D.nbins, BIN_LDS);
-    for (int t = 0; t < t1 - t0; ++t)
-      for (int k = 0; k < nb; ++k) {
-        a[k] += tb[(size_t(t) * BIN_LDS + k) * 2];
-        c[k] += tb[(size_t(t) * BIN_LDS + k) * 2 + 1];
-      }
+  HMD_HIP(ctx, hipSetDevice(ctx->device));
+  // per-system bins plus, on the tiled path, the system's per-tile bins, which
+  // come down together
+  const size_t nb = size_t(D.nbins), ld = size_t(b->acc.tb_ld) * 2;
+  const size_t ntb = b->d_tbins ? size_t(b->tile_first[sim + 1] - b->tile_first[sim]) : 0;
+  const size_t words = 2 * nb + ntb * ld;
+  std::vector<double> pageable;
+  double* h = static_cast<double*>(stage(ctx, 8 * words));
+  if (!h) {
+    pageable.resize(words);
+    h = pageable.data();
   }
-  if (mvx) std::copy(a.begin(), a.end(), mvx);
-  if (cnt) std::copy(c.begin(), c.end(), cnt);
+  double *const a = h, *const c = a + nb, *const tb = c + nb;
+  hipStream_t s = ctx->stream;
+  HMD_HIP(ctx, hipMemcpyAsync(a, b->acc.binvx + D.bin0, 8 * nb, hipMemcpyDeviceToHost, s));
+  HMD_HIP(ctx, hipMemcpyAsync(c, b->acc.bincnt + D.bin0, 8 * nb, hipMemcpyDeviceToHost, s));
+  if (ntb > 0)
+    HMD_HIP(ctx, hipMemcpyAsync(tb, b->d_tbins + size_t(b->tile_first[sim]) * ld, 8 * ntb * ld, hipMemcpyDeviceToHost,
+                                s));
+  HMD_HIP(ctx, hipStreamSynchronize(s));
+  for (size_t t = 0; t < ntb; ++t)
+    for (size_t k = 0; k < std::min(nb, ld / 2); ++k) {
+      a[k] += tb[t * ld + 2 * k];
+      c[k] += tb[t * ld + 2 * k + 1];
+    }
+  if (mvx) std::copy(a, a + nb, mvx);
+  if (cnt) std::copy(c, c + nb, cnt);
   return HMD_OK;
 }
 

@@ -7,7 +7,11 @@
 
 namespace hmd {
 
-constexpr int BIN_LDS = 128;  // LDS profile bins per block
+// LDS profile bins per block: as many as leave five tiles of the joined list and
+// force kernel to a compute unit (256 leave four).  Atoms of higher bins add to
+// memory one by one: a tiled channel of 160 bins and 39,200 atoms 28 us a step,
+// 38 to 43 with 128 bins in LDS
+constexpr int BIN_LDS = 208;
 
 // Pointers to one copy of the FP64 SoA state.
 struct StateRef {

@@ -783,8 +783,8 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
       if (bb < BIN_LDS) {
         atomicAdd(&tbin[bb], tbin_word(v0));
       } else {
-        atomicAdd(&acc.binvx[gb * kBinPitch], v0);
-        atomicAdd(&acc.bincnt[gb * kBinPitch], 1.0);
+        atomicAdd(&acc.binvx[gb], v0);
+        atomicAdd(&acc.bincnt[gb], 1.0);
       }
     }
   }
@@ -801,15 +801,15 @@ __device__ __forceinline__ void finish_force(int i, bool valid, int s, const Sim
       atomicAdd(&lds_vx[o], v0);
       atomicAdd(&lds_cnt[o], 1.0);
     } else {
-      atomicAdd(&acc.binvx[gb * kBinPitch], v0);
-      atomicAdd(&acc.bincnt[gb * kBinPitch], 1.0);
+      atomicAdd(&acc.binvx[gb], v0);
+      atomicAdd(&acc.bincnt[gb], 1.0);
     }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < BIN_LDS; k += blockDim.x)
     if (lds_cnt[k] != 0.0) {
-      atomicAdd(&acc.binvx[(base + k) * kBinPitch], lds_vx[k]);
-      atomicAdd(&acc.bincnt[(base + k) * kBinPitch], lds_cnt[k]);
+      atomicAdd(&acc.binvx[base + k], lds_vx[k]);
+      atomicAdd(&acc.bincnt[base + k], lds_cnt[k]);
     }
 }
 
@@ -1924,7 +1924,7 @@ __device__ __forceinline__ void force_tiles(
     const int nb = min(D.nbins, BIN_LDS);
     for (int k = threadIdx.x; k < nb; k += blockDim.x)
       if (tbin[k] != 0ull) {  // the tile's own FP64 accumulators: a plain add, no atomics
-        double* const tb = acc.tbins + (size_t(t) * BIN_LDS + k) * 2;
+        double* const tb = acc.tbins + (size_t(t) * acc.tb_ld + k) * 2;
         const double n = double(tbin[k] >> TBIN_CNT_SHIFT);
         tb[0] += double(tbin[k] & ((1ull << TBIN_CNT_SHIFT) - 1ull)) * TBIN_UNIT - TBIN_OFFSET * n;
         tb[1] += n;

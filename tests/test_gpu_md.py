@@ -582,10 +582,11 @@ def test_profile_bins_match_oracle(path):
 
 
 @pytest.mark.parametrize("path", PATHS)
-def test_profiles_of_more_bins_than_a_workgroup_holds_match_oracle(path):
-    # 150 bins: those past 128 are added to atom by atom; bars of
-    # test_profile_bins_match_oracle
-    fine = dict(SMALL_L, bin_dy=0.04)
+@pytest.mark.parametrize("bins", [150, 208, 209, 240])
+def test_profiles_of_many_bins_match_oracle(bins, path):
+    # a workgroup holds 208 bins; those past them are added to atom by atom; bars
+    # of test_profile_bins_match_oracle
+    fine = dict(SMALL_L, bin_dy=6.0 / (bins - 0.5))
     pre = omd.System(6.0, 0.05, 7, omd.Params(**fine))
     pre.run(300)
     x, v = pre.get_state()
@@ -596,7 +597,7 @@ def test_profiles_of_more_bins_than_a_workgroup_holds_match_oracle(path):
     o_sys.run(10)
     mvx, cnt = g_sys.profile()
     mvo, cno = o_sys.profile()
-    assert len(cnt) == 150 and cnt[128:].sum() > 0
+    assert len(cnt) == len(cno) == bins
     assert np.array_equal(cnt, cno)
     assert np.abs(mvx - mvo).max() <= 1e-6 * max(1.0, np.abs(mvo).max())
 
@@ -604,8 +605,8 @@ def test_profiles_of_more_bins_than_a_workgroup_holds_match_oracle(path):
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("S", [1, 16, 17])
 def test_temperatures_of_a_batch_are_those_of_its_states(S, path):
-    # each component's sums start a cache line of their own (16 systems fill
-    # one).  Rounding of sums of a thousand terms, in another order.
+    # thermostat and temperature sums start cache lines of their own, 16 sums
+    # to a line.  Rounding of sums of a thousand terms, in another order.
     ctx = hmd.Context(hmd.Params(force_path=path, **SMALL_L))
     b = hmd.Batch(ctx, [(4.0 + 0.25 * k, 0.02, 3 + k, 4) for k in range(S)])
     want = np.zeros((S, 3))
