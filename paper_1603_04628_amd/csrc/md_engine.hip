@@ -417,10 +417,26 @@ int make_tiles(hmd_batch* b) {
   hmd_ctx* ctx = b->ctx;
   constexpr int64_t kMinTiles = 512;
   b->stage_cap = TILE_STAGE;
-  auto staged_atoms = [&](int k, int nc) {
+  auto per_column = [&](int k, double n) { return n / double(b->sims[k].nx * b->sims[k].nz); };
+  auto fluid_atoms = [&](int k, int nc) {
+    return 3.0 * std::min(nc + 2, b->sims[k].nx) * per_column(k, double(b->sims[k].nf));
+  };
+  auto wall_atoms = [&](int k, int nc) {
+    return 3.0 * std::min(nc + 2, b->sims[k].nx) * per_column(k, double(b->host[k].nw));
+  };
+  auto staged_atoms = [&](int k, int nc) { return fluid_atoms(k, nc) + wall_atoms(k, nc); };
+  // Whether tiles of nc columns stay within an LDS capacity.  Below a liquid's
+  // density the fluid gathers in places (between 0.1 and 0.56 it separates at
+  // T = 1), and each tile that outgrows the capacity reads its neighbours from
+  // memory.  Room for 5% more than the mean and for 40%, skin 0.2: 28 channels
+  // of 16 sigma at density 0.4 174 and 121 us a step, 100 of 15 at 0.1 178 and
+  // 142, of 30 237 and 200; the narrower tiles cost up to 7% where none outgrows
+  // it (55 of 33 at 0.1, skin 0.3: 106 and 113)
+  auto fits = [&](int k, int nc, int cap) {
     const SimDev& D = b->sims[k];
-    return 3.0 * std::min(nc + 2, D.nx) *
-           (double(D.nf) / double(D.nx * D.nz) + double(b->host[k].nw) / double(D.nx * D.nz));
+    const double rho = double(D.nf) / (D.Lx * D.Lz * D.h);
+    const double swell = std::min(1.4, std::max(1.0, 0.65 / rho));
+    return staged_atoms(k, nc) <= 0.95 * cap && fluid_atoms(k, nc) * swell + wall_atoms(k, nc) < cap;
   };
   // a channel whose narrowest tiles fit only the larger capacity asks for it
   // on behalf of the batch (32 channels of 10 sigma and one of 36: 168 us a
@@ -447,26 +463,52 @@ int make_tiles(hmd_batch* b) {
   // quarter, and with every pass counted whole: 64-channel batch, force 180
   // -> 173 us and list build 117 -> 108 us per step (1/2 and 3/4 as good);
   // density sweep 54 -> 51 us
-  std::vector<int> cols(b->S, 1);
-  for (int k = 0; k < b->S; ++k) {
+  auto tile_cost = [&](int k, int nc) {
+    const double atoms = nc * per_column(k, double(b->sims[k].nf)), left = std::fmod(atoms, double(TILE_THREADS));
+    double last = left > 0.0 ? 256.0 : 0.0;
+    if (tabled(k, nc) && left > 0.0 && left <= 128.0) last = left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : 32.0;
+    return atoms - left + last + (b->tile_alpha + 0.25) * staged_atoms(k, nc);
+  };
+  auto columns = [&](int k, int cap) {
     const SimDev& D = b->sims[k];
-    const double per_col = double(D.nf) / double(D.nx * D.nz);
+    int best = 1;
     double best_use = -1.0;
     for (int nc = 1; nc <= D.nx; ++nc) {
-      const double atoms = nc * per_col;
-      const double staged = staged_atoms(k, nc);
-      if (staged > 0.95 * b->stage_cap && nc > 1) break;
+      if (nc > 1 && !fits(k, nc, cap)) break;
       if (nc > 2 && !tabled(k, nc) && tabled(k, 2)) break;
-      const double left = std::fmod(atoms, double(TILE_THREADS));
-      double last = left > 0.0 ? 256.0 : 0.0;
-      if (tabled(k, nc) && left > 0.0 && left <= 128.0) last = left > 64.0 ? 128.0 : left > 32.0 ? 64.0 : 32.0;
-      const double use = atoms / (atoms - left + last + (b->tile_alpha + 0.25) * staged);
+      const double use = nc * per_column(k, double(D.nf)) / tile_cost(k, nc);
       if (use > 1.02 * best_use) {
         best_use = use;
-        cols[k] = nc;
+        best = nc;
       }
     }
+    return best;
+  };
+  // The larger capacity also where it halves the tiles (channels with few atoms
+  // beside their walls', which every tile stages), though a compute unit then
+  // takes four: 76 channels of 12 sigma at density 0.2 131 -> 116 us a step, 61
+  // of 20 at 0.15 116 -> 106.  Not where tiles get fewer by less (80 to 60 in a
+  // channel: 0.98 to 1.07 times the time; 64-channel batch 8,440 to 6,220: 202
+  // us of force for 176) or are few enough for the joined launch.
+  auto plan = [&](int cap) {
+    int64_t tiles = 0;
+    double cost = 0.0;
+    for (int k = 0; k < b->S; ++k) {
+      const SimDev& D = b->sims[k];
+      const int ntx = (D.nx + columns(k, cap) - 1) / columns(k, cap);
+      tiles += int64_t(D.nz) * ntx;
+      for (int t = 0; t < ntx; ++t) cost += D.nz * tile_cost(k, (t + 1) * D.nx / ntx - t * D.nx / ntx);
+    }
+    return std::make_pair(tiles, cost);
+  };
+  if (b->stage_cap == TILE_STAGE) {
+    const auto small = plan(TILE_STAGE), tall = plan(TILE_STAGE_TALL);
+    if (small.first > kResidentTiles && 1.8 * double(tall.first) < double(small.first) &&
+        1.1 * tall.second < small.second)
+      b->stage_cap = TILE_STAGE_TALL;
   }
+  std::vector<int> cols(b->S, 1);
+  for (int k = 0; k < b->S; ++k) cols[k] = columns(k, b->stage_cap);
   auto count = [&](int widest) {
     int64_t n = 0;
     for (int k = 0; k < b->S; ++k) {

@@ -617,6 +617,25 @@ def test_temperatures_of_a_batch_are_those_of_its_states(S, path):
         np.testing.assert_allclose(r["T"], w / 4.0, rtol=1e-12)
 
 
+@pytest.mark.parametrize("S,h,rho", [(17, 12.0, 0.2), (16, 12.0, 0.2), (1, 16.0, 0.4)])
+def test_tiles_of_fluids_below_a_liquids_density(S, h, rho):
+    # 17 such channels have more than 1,280 tiles and take the larger LDS capacity,
+    # 16 do not; and one whose tiles keep room for denser places.  Bars of the
+    # other force tests.
+    p = dict(LARGE, rho=rho)
+    ctx = hmd.Context(hmd.Params(force_path=2, skin=SKIN, **p))
+    b = hmd.Batch(ctx, [(h, 0.01, 3 + k, 10) for k in range(S)])
+    b.run(100, 50)
+    k = S - 1
+    x, v = b.get_state(k)
+    o = omd.System(h, 0.01, 3 + k, omd.Params(cell_w=2.5 + SKIN, **p))
+    o.set_state(x, v)
+    f, fo = b.forces(k)[0], o.forces_cells()[0]
+    assert _rel_rms(f, fo) <= 1e-5
+    ok, worst = _per_atom_ok(f, fo)
+    assert ok, worst
+
+
 def test_batch_equals_single_systems():
     p = hmd.Params(**SMALL_L)
     ctx = hmd.Context(p)
