@@ -712,6 +712,9 @@ def main():
                         "steps each, direct launches",
         "kernel_ms": kern,
         "kernel_ms_windows": kern_windows,
+        "kernel_ms_note": "of stamped steps, which launch keys, scan and scatter, and list and force, one by one; the "
+                          "other steps sort in two launches (k_sort, k_reorder), and up to 1,280 tiles list and force "
+                          "are one (k_list_force)",
         "autotune": None if tune_table is None else {
             "seconds": tune_s, "probe_steps": args.tune_steps,
             "candidates": [dict(zip(("path", "skin", "tpb", "tile_alpha", "cell_w", "chunk", "ms_per_step"),

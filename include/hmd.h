@@ -79,8 +79,8 @@ typedef struct {
      * choice.  cell_w: minimum cell width (0: rc, or rc + skin for the pair
      * lists).  tile_alpha (tiled path): each system's tiles take the column
      * count that minimises (lanes + (tile_alpha + 1/4) x staged atoms) per
-     * home atom: larger values favour wider tiles that stage less halo per
-     * atom.  graph_chunk: steps per captured graph of
+     * home atom, among those that the LDS holds with room to spare: larger
+     * values favour wider tiles that stage less halo per atom.  graph_chunk: steps per captured graph of
      * the whole-run calls (even; 0 = 100).  force_path -1 applies what
      * md_autotune chose for the workload, where it has run. */
     int force_path;

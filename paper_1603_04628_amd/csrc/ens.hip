@@ -522,8 +522,9 @@ __global__ void k_ens_tick(int* tbase, int k) { *tbase += k; }
 // (query lane % 16, units 16 t + 4 (lane / 16) + u) itself, and the output
 // layer is a sum over 16 lanes.  What bounds it is the tanh of two layers (128
 // per query and member, about 40 instructions each) and the matrix rate:
-// 50,000 queries of 5 members of 64 units took 300 us with W2 in LDS and a lane
-// per unit, 65 us with all weights in registers and two, 50 us now.
+// 50,000 queries of 5 members of 64 units: a whole call took 277 us with W2 in
+// LDS and a lane per unit and takes 55 us now; this kernel took 65 us with all
+// weights in registers and two wavefronts a SIMD, 50 us now.
 template <int HT>
 __global__ __launch_bounds__(256, 3) void k_ens_member_out(int m, int H, const float* __restrict__ params,
                                                         const double* __restrict__ Xq, double mu0, double mu1,

@@ -14,7 +14,9 @@
 // hyperparameters that maximise the evidence (gp_optimize).
 // One elimination gives the factor, its inverse and the weights, a launch per
 // panel; the evidence search factors many hyperparameter sets at once;
-// prediction gives each query a workgroup of its own.
+// prediction takes 32 queries a workgroup on the matrix cores, or, where
+// queries are few and the database small, a workgroup per query
+// (enqueue_predict).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -54,7 +56,7 @@ namespace hmd {
 namespace {
 
 constexpr int GP_MAXD = 4;
-constexpr int GP_MAXN = 6144;  // database points: k* and the substitution vectors fit one workgroup's LDS
+constexpr int GP_MAXN = 6144;  // database points (the limit that gp_fit states; L and L^-1 then take 0.6 GB)
 
 struct KParams {
   double inv_scale[GP_MAXD];
